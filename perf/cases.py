@@ -304,3 +304,69 @@ def run(state):
     for call in s["calls"]:
         call()
     return _tables(s) + [[g["y"], g["h"]] for g in s["groups"]]
+
+
+# ---- the same pass in 64 bits, in plain torch ----------------------------------------------------------------------------
+def _hash32(v):
+    s = (v * 747796405 + 2891336453) & 0xffffffff
+    w = (((s >> ((s >> 28) + 4)) ^ s) * 277803737) & 0xffffffff
+    return (w >> 22) ^ w
+
+
+def _kept(T, d, seed, p):
+    """The dropout contract's mask: one 32-bit word per pair of columns, its halves compared with round(p 65536)."""
+    key = _hash32(_hash32(torch.arange(T, device="cuda", dtype=torch.int64)) ^ seed)
+    word = _hash32((key[:, None] + torch.arange(d // 2, device="cuda", dtype=torch.int64)) & 0xffffffff)
+    return torch.stack([word & 0xffff, word >> 16], dim=2).reshape(T, d) >= int(round(p * 65536))
+
+
+def exact(case, seed):
+    c = dict(_BASE, **case)
+    if c["what"] == "rows":
+        return None                                       # (copies and whole numbers)
+    s = prepare(case, seed)
+    ranks, T = _ranks(c), len(s["ta"])
+    ta, tk = s["ta"].long(), s["tk"].long()
+    scale = s["scales"].double() if s["scales"] is not None else torch.full((T,), 2.0, dtype=torch.float64, device="cuda")
+    live_ft = (tk == FT) & (ta >= 0)
+    groups = []
+    for g in s["groups"]:
+        x = g["x"].double()
+        keep = _kept(T, x.shape[1], 1234, c["dropout"]) | ~live_ft[:, None] if c["dropout"] else None
+        if keep is not None:
+            x = x * keep
+        ys, hs, dxs, dAs, dBs = [], [], [], [], []
+        for k, ad in enumerate(g["ad"]):
+            y = g["y"][k].double() if c["what"] != "backward" else None
+            h_out = torch.zeros(g["h"][k].numel(), dtype=torch.float64, device="cuda") if g["h"][k] is not None else None
+            back = c["what"] in ("backward", "train")
+            dx = g["dx"][k].double() if back else None
+            dA, dB, at = {}, {}, 0
+            for a in range(c["adapters"]):
+                A, B = ad.A[a].double(), ad.B[a].double()
+                for kind in ((FT,) if c["what"] == "backward" else (FT, PREFILL, DECODE)):
+                    rows = torch.nonzero((ta == a) & (tk == kind)).flatten()
+                    if not len(rows):
+                        continue
+                    h = x[rows] @ A.T
+                    if y is not None:
+                        y[rows] += scale[rows, None] * (h @ B)
+                    if kind == FT and h_out is not None:
+                        h_out[at: at + h.numel()] = h.flatten()
+                        at += h.numel()
+                    if kind == FT and back:
+                        dy = g["dy"][k][rows].double()
+                        gr = scale[rows, None] * (dy @ B.T)
+                        dx[rows] += gr @ A
+                        dA[a], dB[a] = gr.T @ x[rows], (scale[rows, None] * h).T @ dy
+            if back and keep is not None:
+                dx = dx * keep
+            on = list(g["dA"][k]) if back else []
+            ys.append(y), hs.append(h_out), dxs.append(dx)
+            dAs.append([dA[a] for a in on]), dBs.append([dB[a] for a in on])
+        groups.append([ys, hs, dxs, dAs, dBs])
+    if c["what"] == "backward":
+        return [g[2:] for g in groups]
+    if c["what"] == "train":
+        return [None] * 6 + groups[0]
+    return [None] * 6 + [[g[0], g[1]] for g in groups]
