@@ -1320,13 +1320,30 @@ hipError_t launch_fused(const FwdParams& p, hipStream_t st)
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// LQ_VARIANT_AUTO: slab or fused, from the host arguments alone.  Measured on the layer-stack shapes (5632 tokens,
-// rank 32): slab wins up to 14336 output columns in all (q 40 vs 47 us, k 25 vs 30, q+k+v 64 vs 72, down 71 vs 76, gate
-// 96 vs 101), fused beyond (gate+up 167 vs 178: a slab re-reads all of B for its 32 rows, the fused expand phase stages a
-// block of B once per 512 rows) and for ranks above 32 (the Zipf batch with ranks up to 64: 125 vs 152 us).
-int auto_variant(int max_rank, long long out_columns)
+// LQ_VARIANT_AUTO: slab or fused, from the host arguments alone.  A slab re-reads its adapter's matrices for its 32 rows,
+// the fused kernel pays its barrier and the h slices' round trip through memory; so the slab wins until the batch needs
+// several rounds of slabs, and the sooner it stops the more an adapter weighs.  Measured (slab vs fused, us):
+//   ranks up to 32 (5632 tokens, rank 32): slab up to 14336 output columns in all (q 40 vs 47, k 25 vs 30, q+k+v 64 vs 72,
+//   down 71 vs 76, gate 96 vs 101), fused beyond (gate+up 178 vs 167; 92 vs 81 at 2048 tokens of rank 16).  Up to 1024
+//   tokens the slabs are one round with several column parts each, and win there too (gate+up at 1024 tokens: rank 16
+//   35 vs 49, rank 32 44 vs 56; 256 tokens 23 vs 31).  But a few decode rows make so few slabs that each streams the
+//   A of several layers alone, while the fused kernel cuts d_in (16 and 64 rows, rank 16: q+k+v 16.5 vs 13.9, gate+up
+//   17.8 vs 14.1; rank 32: 22 vs 17).
+//   ranks above 32, single calls, by rows x (columns read + written).  Rank 64, 4096 -> 4096: 22 vs 39 at 1024 rows,
+//   35 vs 49 at 4096, 79 vs 70 at 8192; 4096 -> 14336: 51 vs 68 at 2048, 98 vs 90 at 4096; 1024 -> 1024: 12 vs 36 at
+//   2048, 30 vs 35 at 8192.  Rank 128, 4096 -> 4096: 32 vs 58 at 1024, 52 vs 72 at 4096, 118 vs 109 at 8192;
+//   4096 -> 14336: 55 vs 80 at 1024, 125 vs 105 at 2048.  Between 34 and 67 million (rank 64) or 38 million (rank 128) the
+//   two meet.  Few rows of a wide input are the fused kernel's again (14336 -> 4096, rank 64: 16 decode rows 32 vs 28,
+//   512 of them 35 vs 29), and so are groups, whose slabs take one projection at a time (q+k+v, rank 64: 38 vs 23, 79 vs 79).
+int auto_variant(int max_rank, int n_tokens, int n_proj, int in_columns, long long out_columns)
 {
-    return max_rank <= 32 && out_columns <= 16384 ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
+    if (max_rank <= 32) {
+        if (n_proj > 1 && n_tokens <= 128) return LQ_VARIANT_FUSED;
+        return out_columns <= 16384 || n_tokens <= 1024 ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
+    }
+    if (n_proj > 1 || (in_columns > 8192 && n_tokens <= 1024)) return LQ_VARIANT_FUSED;
+    const long long most = max_rank <= 64 ? 48000000ll : 36000000ll;
+    return (long long)n_tokens * (in_columns + out_columns) <= most ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
 }
 
 int rstride_for(int max_rank) { return max_rank <= 32 ? 32 : max_rank <= 64 ? 64 : 128; }  // what the expand kernel reads per row
@@ -1406,7 +1423,7 @@ lq_status forward_checked(const void* x, int64_t ldx, int32_t d_in, int32_t n_pr
     if (variant == LQ_VARIANT_AUTO) {
         long long columns = 0;
         for (int k = 0; k < n_proj; ++k) columns += projs[k].d_out;
-        variant = auto_variant(max_rank, columns);
+        variant = auto_variant(max_rank, n_tokens, n_proj, d_in, columns);
         if (variant == LQ_VARIANT_FUSED && h_bytes > 0x7fffffffull) variant = LQ_VARIANT_SLAB;  // (beyond the fused variant's reach)
     }
     if (!workspace || workspace_bytes < (size_t)kWsHeaderBytes + h_bytes || !aligned16(workspace)) return LQ_ERR_WORKSPACE;

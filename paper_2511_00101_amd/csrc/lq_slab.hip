@@ -85,8 +85,18 @@ __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegI
 {
     slab_unit_rows(p, u, s0, reinterpret_cast<int*>(lds + kRowsOffset));
     __syncthreads();
-    constexpr int NPP = GROUP ? pass_projections<NT>() : 1;
     const int n_proj = n_proj_of(p);
+    if constexpr (NT >= 4) {
+        // a launch with adapters of different ranks: every unit runs with as many 16-rank tiles as its own adapter needs
+        for (int pi = 0; pi < n_proj; ++pi) {
+            if (NT >= 8 && s0.rank > 64) slab_pass<NT, 1>(p, u, s0, pi, part, parts, lds);  // workgroup uniform
+            else if (s0.rank > 32) slab_pass<4, 1>(p, u, s0, pi, part, parts, lds);
+            else if (s0.rank > 16) slab_pass<2, 1>(p, u, s0, pi, part, parts, lds);
+            else slab_pass<1, 1>(p, u, s0, pi, part, parts, lds);
+        }
+        return;
+    }
+    constexpr int NPP = GROUP ? pass_projections<NT>() : 1;
     for (int pi0 = 0; pi0 < n_proj; pi0 += NPP) {
         const int np = min(NPP, n_proj - pi0);  // workgroup uniform
         if (NPP >= 4 && np == 4) slab_pass<NT, (NPP >= 4 ? 4 : 1)>(p, u, s0, pi0, part, parts, lds);
