@@ -307,6 +307,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_segments_multi_kernel(
         if (base0 != t_begin) load_keys(base0);
 #pragma unroll
         for (int r = 0; r < kKeyRounds; ++r) {
+            if (__ballot(keys[r] >= 0) == 0) continue;  // wave uniform: nothing in this round
             groups[r] = key_group(keys[r], key_bits);
             if (keys[r] >= 0 && (groups[r] & 0xff) == lane) atomicAdd(lds_hist + keys[r] * kBuildWaves + w, groups[r] >> 16);
         }
@@ -333,10 +334,16 @@ __global__ __launch_bounds__(kBuildThreads) void build_segments_multi_kernel(
     // key k: tokens in all workgroups, and in the workgroups before this one
     int total = 0, before = 0;
     if (tid < n_keys) {
-        for (int i = 0; i < n_groups; ++i) {
-            const int c = __hip_atomic_load(counts + tid * n_groups + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            total += c;
-            if (i < g) before += c;
+        // (requested together: a loop that adds one count at a time is a chain of up to 16 trips past the L2 caches.
+        // 4864 tokens 9.2 -> 8.6 us, 16384 in 16 workgroups 10.5 -> 9.4)
+        int c[kMultiMaxGroups];
+#pragma unroll
+        for (int i = 0; i < kMultiMaxGroups; ++i)
+            c[i] = __hip_atomic_load(counts + tid * n_groups + min(i, n_groups - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int i = 0; i < kMultiMaxGroups; ++i) {
+            total += i < n_groups ? c[i] : 0;
+            before += i < min(g, n_groups) ? c[i] : 0;
         }
     }
     int n_live = 0;
