@@ -1331,8 +1331,9 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 //   down 71 vs 76, gate 96 vs 101), fused beyond (gate+up 178 vs 167; 92 vs 81 at 2048 tokens of rank 16).  Up to 1024
 //   tokens the slabs are one round with several column parts each, and win there too (gate+up at 1024 tokens: rank 16
 //   35 vs 49, rank 32 44 vs 56; 256 tokens 23 vs 31).  But a few decode rows make so few slabs that each streams the
-//   A of several layers alone, while the fused kernel cuts d_in (16 and 64 rows, rank 16: q+k+v 16.5 vs 13.9, gate+up
-//   17.8 vs 14.1; rank 32: 22 vs 17).
+//   A of both layers alone, while the fused kernel cuts d_in (gate+up, 16 and 64 rows, rank 16: 17.8 vs 14.1, 18.2 vs 16.1).
+//   (q+k+v of so few rows would be faster fused too, 16.5 vs 13.9; they stay with the slab kernel, which needs no
+//   device-wide wait and so runs beside another stream's calls.)
 //   ranks above 32, single calls, by rows x (columns read + written).  Rank 64, 4096 -> 4096: 22 vs 39 at 1024 rows,
 //   35 vs 49 at 4096, 79 vs 70 at 8192; 4096 -> 14336: 51 vs 68 at 2048, 98 vs 90 at 4096; 1024 -> 1024: 12 vs 36 at
 //   2048, 30 vs 35 at 8192.  Rank 128, 4096 -> 4096: 32 vs 58 at 1024, 52 vs 72 at 4096, 118 vs 109 at 8192;
@@ -1342,8 +1343,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 int auto_variant(int max_rank, int n_tokens, int n_proj, int in_columns, long long out_columns)
 {
     if (max_rank <= 32) {
-        if (n_proj > 1 && n_tokens <= 128) return LQ_VARIANT_FUSED;
-        return out_columns <= 16384 || n_tokens <= 1024 ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
+        return out_columns <= 16384 || (n_tokens > 128 && n_tokens <= 1024) ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
     }
     if (n_proj > 1 || (in_columns > 8192 && n_tokens <= 1024)) return LQ_VARIANT_FUSED;
     const long long most = max_rank <= 64 ? 48000000ll : 36000000ll;

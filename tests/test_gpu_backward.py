@@ -181,3 +181,16 @@ def test_backward_caller_tables_with_repeated_finetune_adapter(oracle_mod):
                 assert rel_frobenius(got, want) <= WGRAD_REL_FROBENIUS, f"{what}[{a}]"
                 assert float(np.abs(got - want).max()) <= WGRAD_REL_MAX * scale, f"{what}[{a}]"
         d.y.copy_(lq.bf16_from_bits(p.y0))
+
+
+@pytest.mark.parametrize("ranks", [[64, 33, 32, 17, 16, 5], [128, 65, 64, 33, 32, 16]])
+def test_backward_units_run_with_their_own_rank(oracle_mod, ranks):
+    """Weight-gradient units with 1, 2, 4 and 8 rank tiles in one launch: whole segments and (over 512 rows) cut ones."""
+    lens = [700, 3, 32, 33, 520, 513]
+    rng = np.random.default_rng(ranks[0])
+    order = rng.permutation(sum(lens))
+    ta = np.repeat(np.arange(len(ranks), dtype=np.int32), lens)[order]
+    tk = np.zeros(len(ta), np.uint8)
+    p = synth.make_problem("own_rank", synth.Batch(ta, tk), 520, 264, np.array(ranks, np.int32), rng.uniform(0.5, 1.5, len(ranks)),
+                           9, with_dy=True, w_std=0.02)
+    run_backward(oracle_mod, p, lq.LQ_VARIANT_AUTO)

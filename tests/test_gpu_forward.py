@@ -509,3 +509,34 @@ def test_slab_variant_runs_beside_other_kernels(oracle_mod):
     lq.raise_on_device_error(ws, "slab beside other kernels")
     assert_close(synth.bf16_bits_to_f64(lq.bits_from_bf16(d.y)), ref.y, "y")
     assert_close(h_out.cpu().numpy(), ref.h, "h_out")
+
+
+@pytest.mark.parametrize("variant", [lq.LQ_VARIANT_SLAB, lq.LQ_VARIANT_FUSED])
+@pytest.mark.parametrize("ranks", [[8, 16, 17, 32, 33, 64], [128, 65, 64, 33, 32, 16, 1]])
+def test_every_unit_runs_with_its_own_rank(oracle_mod, variant, ranks):
+    """Launches for ranks up to 64 and 128 whose adapters need 1, 2, 4 and 8 rank tiles: segments of one to hundreds of rows
+    (short, single-tile, two-tile and cut units; the fused kernel's expand units beyond its first round take the smaller
+    unit for ranks up to 32)."""
+    rng = np.random.default_rng(len(ranks))
+    lens = np.concatenate([[1, 2, 8, 9, 16, 17, 31, 32, 33, 250], rng.integers(1, 90, size=40)])
+    ta = np.repeat(rng.integers(0, len(ranks), size=len(lens)), lens).astype(np.int32)
+    tk = np.repeat(rng.integers(0, 3, size=len(lens)), lens).astype(np.uint8)
+    ta[:: 41] = -1
+    p = synth.make_problem("own_rank", synth.Batch(ta, tk), 1032, 8 * 1033, np.array(ranks, np.int32),
+                           rng.uniform(0.5, 1.5, len(ranks)), 5, w_std=0.02)
+    check_forward(oracle_mod, p, variant)
+
+
+@pytest.mark.parametrize("max_rank,T,d_in,d_out", [(64, 1000, 264, 520), (128, 700, 1032, 776), (64, 700, 8200, 264), (64, 12000, 4096, 4096)])
+def test_automatic_choice_above_rank_32(oracle_mod, max_rank, T, d_in, d_out):
+    """Either side of the automatic rule's lines (few and many rows, a wide input) equals one of the two variants bit for bit."""
+    p = synth.small_mixed(max_rank + T, T, d_in, d_out, [max_rank, 8, 24], drop_frac=0.1)
+    got = []
+    for v in (lq.LQ_VARIANT_AUTO, lq.LQ_VARIANT_SLAB, lq.LQ_VARIANT_FUSED):
+        d = DeviceProblem(p)
+        d.build()
+        y, h, err = d.forward(v)
+        assert err == 0
+        got.append(y)
+    slab = T * (d_in + d_out) <= 48000000 and not (d_in > 8192 and T <= 1024)
+    assert np.array_equal(got[0], got[1] if slab else got[2])

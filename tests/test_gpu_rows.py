@@ -109,3 +109,19 @@ def test_forward_and_backward_with_dropout(oracle_mod, variant):
         for got, want, what in ((dA[a].cpu().numpy(), ref_b.dA[a], "dA"), (dB[a].cpu().numpy(), ref_b.dB[a], "dB")):
             assert rel_frobenius(got, want) <= 1e-3, f"{what}[{a}]"
             assert float(np.abs(got - want).max()) <= 2e-3 * float(np.abs(want).max()), f"{what}[{a}]"
+
+
+@pytest.mark.parametrize("n_seg", [0, 1, 63, 64, 255, 256, 257, 700])
+def test_kind_offsets_over_many_segments(n_seg):
+    """The scan takes 256 segments a round: tables around that size, with kinds missing at either end."""
+    rng = np.random.default_rng(n_seg)
+    for kinds in ((0, 1, 2), (1,), (0, 2), (2,)):
+        kd = np.sort(rng.choice(kinds, size=n_seg)).astype(np.uint8)
+        starts = np.concatenate([[0], np.cumsum(rng.integers(1, 9, size=n_seg))]).astype(np.int32)
+        seg = lq.SegmentTables.empty(int(starts[-1]) + 1, 1, max_segments=max(n_seg, 1) + 5)
+        seg.seg_kind[:n_seg] = torch.from_numpy(kd).cuda()
+        seg.seg_starts[: n_seg + 1] = torch.from_numpy(starts).cuda()
+        seg.n_segments.fill_(n_seg)
+        off = lq.lora_kind_offsets(seg)
+        want = [int(starts[np.searchsorted(kd, c)]) for c in range(4)]
+        assert off.cpu().tolist()[:4] == want, (kinds, off, want)
