@@ -502,7 +502,7 @@ def main():
         ms_per_step=head["ms_per_step"], higher_is_better=True, scaling="weak", vs_baseline=None, dtype="bf16",
         data="synthetic",
         config=dict(workload=workload, variant={lq.LQ_VARIANT_FUSED: "fused", lq.LQ_VARIANT_SPLIT: "split", lq.LQ_VARIANT_SLAB: "slab",
-                             lq.LQ_VARIANT_AUTO: "auto (one launch per call: the slab or the fused kernel, picked by the library from rank and output width)"}[variant], step=step, **extra),
+                             lq.LQ_VARIANT_AUTO: "auto (one launch per call: the slab or the fused kernel, picked by the library from rank, rows and widths)"}[variant], step=step, **extra),
         roofline=head["roofline"], cpu_baseline=cpu,
         forward=dict(us=head["forward_us"], gbps=head["forward_gbps"], tflops=head["forward_tflops"],
                      hbm_frac=head["forward_hbm_frac"], mfma_frac=head["forward_mfma_frac"], kernels=head["kernels"],
