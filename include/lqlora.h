@@ -70,7 +70,7 @@ enum { LQ_SEG_FINETUNE = 0, LQ_SEG_PREFILL = 1, LQ_SEG_DECODE = 2 };
  * LQ_VARIANT_AUTO: the library picks between the slab and the fused variant from the host arguments alone (a pure
  * function of max_rank, n_tokens, the number of layers and the widths): slab for ranks up to 32 and up to 16384 output
  * columns in all (beyond that only for 129 to 1024 tokens), and for larger ranks where the rows x columns of a single
- * call are few; fused otherwise (where re-reading A and B per slab costs more than the partial-h round trip).  Where it
+ * call are few and its input is at most 8192 wide; fused otherwise (where re-reading A and B per slab costs more than the partial-h round trip).  Where it
  * picks fused, that variant's residency requirement applies. */
 enum { LQ_VARIANT_SPLIT = 0, LQ_VARIANT_FUSED = 1, LQ_VARIANT_SHRINK_ONLY = 2, LQ_VARIANT_EXPAND_ONLY = 3,
        LQ_VARIANT_SLAB = 4, LQ_VARIANT_AUTO = 5 };

@@ -1338,14 +1338,15 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 //   35 vs 49 at 4096, 79 vs 70 at 8192; 4096 -> 14336: 51 vs 68 at 2048, 98 vs 90 at 4096; 1024 -> 1024: 12 vs 36 at
 //   2048, 30 vs 35 at 8192.  Rank 128, 4096 -> 4096: 32 vs 58 at 1024, 52 vs 72 at 4096, 118 vs 109 at 8192;
 //   4096 -> 14336: 55 vs 80 at 1024, 125 vs 105 at 2048.  Between 34 and 67 million (rank 64) or 38 million (rank 128) the
-//   two meet.  Few rows of a wide input are the fused kernel's again (14336 -> 4096, rank 64: 16 decode rows 32 vs 28,
-//   512 of them 35 vs 29), and so are groups, whose slabs take one projection at a time (q+k+v, rank 64: 38 vs 23, 79 vs 79).
+//   two meet.  Wide inputs stay with the fused kernel, which cuts d_in (14336 -> 4096, rank 64: 16 decode rows 32 vs 28, 512 of
+//   them 35 vs 29; 11008 -> 1024, 1324 rows in two segments 55 vs 31; with more segments 0.6 to 0.9 of it), and so
+//   do groups, whose slabs take one projection at a time (q+k+v, rank 64: 38 vs 23, 79 vs 79).
 int auto_variant(int max_rank, int n_tokens, int n_proj, int in_columns, long long out_columns)
 {
     if (max_rank <= 32) {
         return out_columns <= 16384 || (n_tokens > 128 && n_tokens <= 1024) ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
     }
-    if (n_proj > 1 || (in_columns > 8192 && n_tokens <= 1024)) return LQ_VARIANT_FUSED;
+    if (n_proj > 1 || in_columns > 8192) return LQ_VARIANT_FUSED;
     const long long most = max_rank <= 64 ? 48000000ll : 36000000ll;
     return (long long)n_tokens * (in_columns + out_columns) <= most ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
 }
