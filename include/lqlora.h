@@ -66,7 +66,8 @@ enum { LQ_SEG_FINETUNE = 0, LQ_SEG_PREFILL = 1, LQ_SEG_DECODE = 2 };
  * through both products, so that h stays on the compute unit: no partial-h traffic and no device-wide wait
  * (hence no residency requirement); every slab re-reads its adapter's matrices, which come from the L2 cache
  * when slabs of one segment run side by side.  The faster variant on batches whose segments are long compared
- * with the adapters' rank (fine-tuning and prefill rows); same results up to fp32 summation order.
+ * with the adapters' rank (fine-tuning and prefill rows); same results up to fp32 summation order.  Where max_rank x
+ * d_in or max_rank x d_out exceeds 2^31 (matrices beyond 4 GiB) its calls run as LQ_VARIANT_SPLIT.
  * LQ_VARIANT_AUTO: the library picks between the slab and the fused variant from the host arguments alone (a pure
  * function of max_rank, n_tokens, the number of layers and the widths): slab for ranks up to 32 and up to 16384 output
  * columns in all (beyond that only for 129 to 1024 tokens), and for larger ranks where the rows x columns of a single

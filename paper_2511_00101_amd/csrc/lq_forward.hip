@@ -1431,6 +1431,11 @@ lq_status forward_checked(const void* x, int64_t ldx, int32_t d_in, int32_t n_pr
         variant = auto_variant(max_rank, n_tokens, n_proj, d_in, columns);
         if (variant == LQ_VARIANT_FUSED && h_bytes > 0x7fffffffull) variant = LQ_VARIANT_SLAB;  // (beyond the fused variant's reach)
     }
+    if (variant == LQ_VARIANT_SLAB) {
+        bool reaches = slab_reaches(max_rank, d_in);
+        for (int k = 0; k < n_proj; ++k) reaches = reaches && slab_reaches(max_rank, projs[k].d_out);
+        if (!reaches) variant = LQ_VARIANT_SPLIT;
+    }
     if (!workspace || workspace_bytes < (size_t)kWsHeaderBytes + h_bytes || !aligned16(workspace)) return LQ_ERR_WORKSPACE;
     // the fused variant addresses the partial-h region through a buffer descriptor with 32-bit offsets
     if (variant == LQ_VARIANT_FUSED && h_bytes > 0x7fffffffull) return LQ_ERR_UNSUPPORTED;

@@ -27,7 +27,7 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// 16 bytes of an adapter matrix at element offset `off` (< 2^31): a wave-uniform base and a 32-bit byte offset per
+// 16 bytes of an adapter matrix at element offset `off` (< 2^31, see slab_reaches): a wave-uniform base and a 32-bit byte offset per
 // lane, the form that needs no 64-bit address arithmetic in vector registers
 __device__ __forceinline__ u32x4 load_at(gconst_u16 base, unsigned int off)
 {

@@ -194,3 +194,25 @@ def test_backward_units_run_with_their_own_rank(oracle_mod, ranks):
     p = synth.make_problem("own_rank", synth.Batch(ta, tk), 520, 264, np.array(ranks, np.int32), rng.uniform(0.5, 1.5, len(ranks)),
                            9, with_dy=True, w_std=0.02)
     run_backward(oracle_mod, p, lq.LQ_VARIANT_AUTO)
+
+
+def test_backward_of_a_matrix_beyond_4_gib():
+    """dx against an A of 128 x 16.8 million elements (over 2^31: beyond 32-bit byte offsets); the automatic choice."""
+    rank, d_in, d_out, T = 128, 16_800_000, 64, 2
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    A, B, dy = new(rank, d_in, rank ** -0.5), new(rank, d_out, d_out ** -0.5), new(T, d_out, 1.0)
+    x = torch.zeros(T, d_in, dtype=torch.bfloat16, device="cuda")
+    dx = torch.zeros(T, d_in, dtype=torch.bfloat16, device="cuda")
+    ad = lq.AdapterTable.from_tensors([A], [B], [1.0])
+    seg = lq.SegmentTables.empty(T, 1)
+    lq.lora_build_segments(torch.zeros(T, dtype=torch.int32, device="cuda"), torch.zeros(T, dtype=torch.uint8, device="cuda"),
+                           ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, 1)))
+    ws = lq.workspace(lq.lora_backward_workspace_bytes(T, 1, rank, d_in, d_out))
+    lq.lora_segmented_backward(x, dy, dx, ad, None, None, seg, torch.zeros(T * rank, device="cuda"), ws, lq.LQ_VARIANT_AUTO)
+    torch.cuda.synchronize()
+    lq.raise_on_device_error(ws)
+    g = dy.double() @ B.double().T
+    for i in range(0, d_in, 1 << 20):
+        want = g @ A[:, i: i + (1 << 20)].double()
+        assert float((dx[:, i: i + (1 << 20)].double() - want).norm() / want.norm()) <= 5e-3, i

@@ -6,7 +6,7 @@ import torch
 from paper_2511_00101_amd import binding as lq
 from paper_2511_00101_amd import synth
 
-from gpu_util import (long_batch_problem, DeviceProblem, assert_close, assert_tables_equal, check_forward,
+from gpu_util import (REL_FROBENIUS, rel_frobenius, long_batch_problem, DeviceProblem, assert_close, assert_tables_equal, check_forward,
                       check_forward_group, group_of)
 
 pytestmark = pytest.mark.gpu
@@ -540,3 +540,40 @@ def test_automatic_choice_above_rank_32(oracle_mod, max_rank, T, d_in, d_out):
         got.append(y)
     slab = T * (d_in + d_out) <= 48000000 and d_in <= 8192
     assert np.array_equal(got[0], got[1] if slab else got[2])
+
+
+@pytest.mark.parametrize("variant", [lq.LQ_VARIANT_SLAB, lq.LQ_VARIANT_AUTO])
+@pytest.mark.parametrize("wide_in", [False, True])
+def test_matrices_beyond_4_gib(variant, wide_in):
+    """128 x 16.8 million elements of one adapter's B (or A): just over 2^31, so the last columns of the last rank row lie
+    beyond 32-bit byte offsets from the matrix's start.  A wrapped offset still reads inside the matrix, but the wrong
+    element of one of the 128 rank rows: an error of sqrt(2 / 128) in the columns concerned."""
+    rank, wide, narrow, T = 128, 16_800_000, 64, 2
+    d_in, d_out = (wide, narrow) if wide_in else (narrow, wide)
+    if variant == lq.LQ_VARIANT_AUTO and wide_in:
+        rank, wide = 32, 67_200_000
+        d_in = wide
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    std = lambda n: 1.0 / float(np.sqrt(n))
+    A = torch.empty(rank, d_in, dtype=torch.bfloat16, device="cuda").normal_(0.0, std(d_in), generator=gen)
+    B = torch.empty(rank, d_out, dtype=torch.bfloat16, device="cuda").normal_(0.0, std(rank), generator=gen)
+    x = torch.empty(T, d_in, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    if wide_in:   # only the last columns count: there every rank row's offset is at its largest
+        x[:, : d_in - 2048] = 0
+        A[:, d_in - 2048:] *= float(np.sqrt(d_in / 2048))
+    y = torch.zeros(T, d_out, dtype=torch.bfloat16, device="cuda")
+    ad = lq.AdapterTable.from_tensors([A], [B], [1.0])
+    seg = lq.SegmentTables.empty(T, 1)
+    lq.lora_build_segments(torch.zeros(T, dtype=torch.int32, device="cuda"), torch.zeros(T, dtype=torch.uint8, device="cuda"),
+                           ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, 1)))
+    h = torch.zeros(T * rank, device="cuda")
+    ws = lq.workspace(lq.lora_forward_workspace_bytes(T, rank, d_in, d_out, variant))
+    lq.lora_segmented_forward(x, y, ad, seg, h, ws, variant)
+    torch.cuda.synchronize()
+    lq.raise_on_device_error(ws)
+    lo = d_in - 2048 if wide_in else 0
+    ref_h = x[:, lo:].double() @ A[:, lo:].double().T
+    assert rel_frobenius(h.view(T, rank).cpu().numpy(), ref_h.cpu().numpy()) <= 1e-4
+    at = range(0, d_out, 1 << 20)
+    worst = max(float(((y[:, i: i + (1 << 20)].double() - (r := ref_h @ B[:, i: i + (1 << 20)].double())).norm() / r.norm())) for i in at)
+    assert worst <= REL_FROBENIUS, worst
