@@ -123,7 +123,9 @@ __global__ __launch_bounds__(kThreads) void slab_kernel(KernelArg<GROUP> p)
     // A batch with few chunks is also cut by columns: every part of a chunk repeats phase 1 and takes its share of
     // the column blocks in phase 2; the parts of one chunk get ids r, r + 8, ..., the same XCD again.
     const int n8 = (cc.total + 7) >> 3;  // chunks per XCD
-    const int parts = cc.total > 0 && 2 * cc.total <= grid ? min(kMaxParts, small_div(grid, cc.total)) : 1;
+    // (The parts go by the padded count.  By the chunks themselves, 36 of them in 7 parts were 280 ids for a grid of 256: a
+    // second round for a few units.  4096 -> 2 x 11008, 512 rows of rank 16 in 12 segments: 35.2 -> 22.7 us.)
+    const int parts = n8 > 0 && 2 * cc.total <= grid ? max(1, min(kMaxParts, small_div(grid, 8 * n8))) : 1;
     const int n_units = 8 * n8 * parts;
     int* stash = reinterpret_cast<int*>(lds_raw + kStashOffset);
     for_each_unit(p.tickets + 0, n_units, s_slot, [&](int gid, int) {

@@ -577,3 +577,17 @@ def test_matrices_beyond_4_gib(variant, wide_in):
     at = range(0, d_out, 1 << 20)
     worst = max(float(((y[:, i: i + (1 << 20)].double() - (r := ref_h @ B[:, i: i + (1 << 20)].double())).norm() / r.norm())) for i in at)
     assert worst <= REL_FROBENIUS, worst
+
+
+@pytest.mark.parametrize("chunks", [8, 9, 33, 36, 41, 49, 51, 81, 85, 120, 121, 128, 129])
+def test_slab_column_parts(oracle_mod, chunks):
+    """Few slabs are cut into column parts: counts on either side of where the number of parts changes and of a multiple of
+    eight (the ids are padded to one), with fewer, as many and more 64-column blocks than parts."""
+    rng = np.random.default_rng(chunks)
+    lens = rng.integers(1, 17, size=chunks)                  # one slab per segment
+    ta = np.repeat(np.arange(chunks, dtype=np.int32), lens)
+    tk = np.repeat(rng.integers(0, 3, size=chunks), lens).astype(np.uint8)
+    for d_out in (72, 456, 1032):
+        p = synth.make_problem("parts", synth.Batch(ta, tk), 136, d_out, rng.integers(1, 17, size=chunks).astype(np.int32),
+                               rng.uniform(0.5, 1.5, chunks), chunks, w_std=0.05)
+        check_forward(oracle_mod, p, lq.LQ_VARIANT_SLAB)
