@@ -69,10 +69,11 @@ enum { LQ_SEG_FINETUNE = 0, LQ_SEG_PREFILL = 1, LQ_SEG_DECODE = 2 };
  * with the adapters' rank (fine-tuning and prefill rows); same results up to fp32 summation order.  Where max_rank x
  * d_in or max_rank x d_out exceeds 2^31 (matrices beyond 4 GiB) its calls run as LQ_VARIANT_SPLIT.
  * LQ_VARIANT_AUTO: the library picks between the slab and the fused variant from the host arguments alone (a pure
- * function of max_rank, n_tokens, the number of layers and the widths): slab for ranks up to 32 and up to 16384 output
- * columns in all (beyond that only for 129 to 1024 tokens), and for larger ranks where the rows x columns of a single
- * call are few and its input is at most 8192 wide; fused otherwise (where re-reading A and B per slab costs more than the partial-h round trip).  Where it
- * picks fused, that variant's residency requirement applies. */
+ * function of max_rank, n_tokens, the number of layers and the widths).  Slab for ranks up to 32 and up to 16384 output
+ * columns in all (from 384 to 1024 tokens up to 28672, for one layer or two that read up to 4096 columns); and above
+ * rank 32 for single calls of up to 8192 tokens, 4096 input and 16384 output columns, as far as the rows are neither too
+ * many (rows x output columns) nor too few for the width.  Fused otherwise, where re-reading A and B per slab costs more
+ * than the partial-h round trip.  Where it picks fused, that variant's residency requirement applies. */
 enum { LQ_VARIANT_SPLIT = 0, LQ_VARIANT_FUSED = 1, LQ_VARIANT_SHRINK_ONLY = 2, LQ_VARIANT_EXPAND_ONLY = 3,
        LQ_VARIANT_SLAB = 4, LQ_VARIANT_AUTO = 5 };
 
@@ -244,8 +245,9 @@ lq_status lora_segmented_forward_static(const void* x, int64_t ldx, void* y, int
  *   variant  LQ_VARIANT_FUSED: g and dx in one launch (same residency requirement as the forward's fused
  *            variant; falls back to two launches where the partial-g region would reach 2 GiB);
  *            LQ_VARIANT_SPLIT: two launches, no device-wide wait; LQ_VARIANT_SLAB: g and dx in one launch of the
- *            forward's slab variant, no device-wide wait; LQ_VARIANT_AUTO: slab or fused by the forward's rule
- *            applied to this step (its outputs are the d_in columns of dx).  Other values: LQ_ERR_INVALID_ARG.
+ *            forward's slab variant, no device-wide wait; LQ_VARIANT_AUTO: slab or fused by the forward's rule for a
+ *            single call, applied to this step (d_out columns of dy in, d_in columns of dx out).  Other values:
+ *            LQ_ERR_INVALID_ARG.
  *   workspace lora_backward_workspace_bytes(...) bytes; its first 4096 bytes zero as for the forward.
  *   Then the weight gradients: a fine-tune segment of up to 512 rows is accumulated straight into dA / dB;
  *   a longer one is cut into row chunks whose partial sums go to the workspace and are added in chunk

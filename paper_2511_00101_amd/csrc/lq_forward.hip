@@ -1325,30 +1325,45 @@ hipError_t launch_fused(const FwdParams& p, hipStream_t st)
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // LQ_VARIANT_AUTO: slab or fused, from the host arguments alone.  A slab re-reads its adapter's matrices for its 32 rows,
-// the fused kernel pays its barrier and the h slices' round trip through memory; so the slab wins until the batch needs
-// several rounds of slabs, and the sooner it stops the more an adapter weighs.  Measured (slab vs fused, us):
+// the fused kernel pays its barrier and the h slices' round trip through memory.  So the slab wins while the batch is one
+// round of slabs (8192 rows on 256 compute units), until the re-reads of B weigh more (rows x output columns), and where
+// there are enough rows for the A that every slab streams alone (the fused kernel cuts d_in instead).  all_rows: the
+// batch's rows all take part; otherwise (the backward: fine-tune rows only) n_tokens is no lower bound, and the
+// branches that need many rows are not taken.  Measured, slab vs fused, us (the worst of one segment, two, requests of 32
+// rows, single decode rows and a Zipf batch):
 //   ranks up to 32 (5632 tokens, rank 32): slab up to 14336 output columns in all (q 40 vs 47, k 25 vs 30, q+k+v 64 vs 72,
-//   down 71 vs 76, gate 96 vs 101), fused beyond (gate+up 178 vs 167; 92 vs 81 at 2048 tokens of rank 16).  Up to 1024
-//   tokens the slabs are one round with several column parts each, and win there too (gate+up at 1024 tokens: rank 16
-//   35 vs 49, rank 32 44 vs 56; 256 tokens 23 vs 31).  But a few decode rows make so few slabs that each streams the
-//   A of both layers alone, while the fused kernel cuts d_in (gate+up, 16 and 64 rows, rank 16: 17.8 vs 14.1, 18.2 vs 16.1).
-//   (q+k+v of so few rows would be faster fused too, 16.5 vs 13.9; they stay with the slab kernel, which needs no
+//   down 71 vs 76, gate 96 vs 101), fused beyond (gate+up 178 vs 167).  From 384 to 1024 rows the slabs are one round with
+//   column parts and win up to 28672 columns (gate+up of rank 32, 4096 -> 2 x 14336: 0.88 of the fused time at 512 rows, 0.84
+//   at 700, 1.01 at 1024; rank 16 0.77, 0.75, 0.83).  Fewer rows do not repay the slabs' A (130 rows: 1.1 to 1.3), nor do
+//   groups of three and four (4096 -> 4 x 4608, rank 32: 1.5 at 400 rows) or wide inputs of groups (8192 -> 2 x 8200: 1.2).
+//   (q+k+v of a few decode rows would be faster fused, 16.5 vs 13.9; they stay with the slab kernel, which needs no
 //   device-wide wait and so runs beside another stream's calls.)
-//   ranks above 32, single calls, by rows x (columns read + written).  Rank 64, 4096 -> 4096: 22 vs 39 at 1024 rows,
-//   35 vs 49 at 4096, 79 vs 70 at 8192; 4096 -> 14336: 51 vs 68 at 2048, 98 vs 90 at 4096; 1024 -> 1024: 12 vs 36 at
-//   2048, 30 vs 35 at 8192.  Rank 128, 4096 -> 4096: 32 vs 58 at 1024, 52 vs 72 at 4096, 118 vs 109 at 8192;
-//   4096 -> 14336: 55 vs 80 at 1024, 125 vs 105 at 2048.  Between 34 and 67 million (rank 64) or 38 million (rank 128) the
-//   two meet.  Wide inputs stay with the fused kernel, which cuts d_in (14336 -> 4096, rank 64: 16 decode rows 32 vs 28, 512 of
-//   them 35 vs 29; 11008 -> 1024, 1324 rows in two segments 55 vs 31; with more segments 0.6 to 0.9 of it), and so
-//   do groups, whose slabs take one projection at a time (q+k+v, rank 64: 38 vs 23, 79 vs 79).
-int auto_variant(int max_rank, int n_tokens, int n_proj, int in_columns, long long out_columns)
+//   ranks above 32, single calls: rank 64, 4096 -> 4096: 0.8 of the fused time up to 4096 rows, 0.89 at 5683, 1.1 at 7578;
+//   4096 -> 8192: 0.83 at 1950, 0.94 at 2734; 4096 -> 14336: 0.87 at 300, 0.79 at 1024, 1.17 at 1822; 64 -> 64: 0.6 up to 8192
+//   rows, 1.0 at 12000, 1.7 at 262500.  Rank 128, 4096 -> 4096: 0.76 at 300 rows, 0.80 at 4262; 4096 -> 8192: 0.85 at 2050,
+//   1.09 at 2643.  16 rows: rank 64, 4096 -> 8192 0.83, -> 14336 0.95, 2048 -> 14336 0.82; rank 128, 4096 -> 4096 0.98 (up to 1.1
+//   for rank 65), 2048 -> 8192 0.8, 4096 -> 14336 1.26.  Inputs of up to 8192 columns only for rank 64 and the rows whose slabs
+//   are about one round of 16 (8192 -> 4096: 1.03 at 16, 0.95 at 1950); wider ones and longer batches up to 1.25.  Groups take one
+//   projection at a time (q+k+v, rank 64: 38 vs 23 at 16 rows, 79 vs 79 at 4096) and stay fused.
+// 12000 random calls above rank 32 that the rule gives to the slab kernel: half take less than 0.57 of the fused time, 99 of
+// 100 less than 0.91, ten more than 1.03 (the worst 1.20).
+int auto_variant(int max_rank, int n_tokens, bool all_rows, int n_proj, int in_columns, long long out_columns)
 {
     if (max_rank <= 32) {
-        return out_columns <= 16384 || (n_tokens > 128 && n_tokens <= 1024) ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
+        if (out_columns <= 16384) return LQ_VARIANT_SLAB;
+        const bool one_round = all_rows && n_tokens >= 384 && n_tokens <= 1024;
+        return one_round && out_columns <= 28672 && (n_proj == 1 || (n_proj == 2 && in_columns <= 4096)) ? LQ_VARIANT_SLAB
+                                                                                                         : LQ_VARIANT_FUSED;
     }
-    if (n_proj > 1 || in_columns > 8192) return LQ_VARIANT_FUSED;
-    const long long most = max_rank <= 64 ? 48000000ll : 36000000ll;
-    return (long long)n_tokens * (in_columns + out_columns) <= most ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
+    const bool upto64 = max_rank <= 64;
+    if (n_proj > 1 || n_tokens > 8192 || out_columns > 16384) return LQ_VARIANT_FUSED;
+    if (in_columns > 4096)
+        return upto64 && in_columns <= 8192 && out_columns <= 8192 && all_rows && n_tokens >= 1024 && n_tokens <= 3000
+                   ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
+    const long long most = upto64 ? (out_columns <= 8192 ? 27000000 : 24000000) : (out_columns <= 4096 ? 24000000 : 20000000);
+    if (n_tokens * out_columns > most) return LQ_VARIANT_FUSED;
+    const int any_rows = out_columns <= 4096 ? 4096 : out_columns <= 8192 ? (upto64 ? 4096 : 2048) : (upto64 ? 2048 : 0);
+    return in_columns <= any_rows || (all_rows && n_tokens >= 256) ? LQ_VARIANT_SLAB : LQ_VARIANT_FUSED;
 }
 
 int rstride_for(int max_rank) { return max_rank <= 32 ? 32 : max_rank <= 64 ? 64 : 128; }  // what the expand kernel reads per row
@@ -1428,7 +1443,7 @@ lq_status forward_checked(const void* x, int64_t ldx, int32_t d_in, int32_t n_pr
     if (variant == LQ_VARIANT_AUTO) {
         long long columns = 0;
         for (int k = 0; k < n_proj; ++k) columns += projs[k].d_out;
-        variant = auto_variant(max_rank, n_tokens, n_proj, d_in, columns);
+        variant = auto_variant(max_rank, n_tokens, true, n_proj, d_in, columns);
         if (variant == LQ_VARIANT_FUSED && h_bytes > 0x7fffffffull) variant = LQ_VARIANT_SLAB;  // (beyond the fused variant's reach)
     }
     if (variant == LQ_VARIANT_SLAB) {

@@ -163,8 +163,9 @@ struct DeviceGrid {
 
 bool aligned16(const void* p);
 int rstride_for(int max_rank);
-// LQ_VARIANT_AUTO's choice: LQ_VARIANT_SLAB or LQ_VARIANT_FUSED (out_columns: summed over the call's linear layers)
-int auto_variant(int max_rank, int n_tokens, int n_proj, int in_columns, long long out_columns);
+// LQ_VARIANT_AUTO's choice: LQ_VARIANT_SLAB or LQ_VARIANT_FUSED (all_rows: the call runs every token's row, not only the
+// fine-tune rows; out_columns: summed over the call's linear layers)
+int auto_variant(int max_rank, int n_tokens, bool all_rows, int n_proj, int in_columns, long long out_columns);
 // The slab kernel addresses a matrix by 32-bit byte offsets from its start: at most 2^31 elements.  Beyond, its calls run
 // as the two launches of LQ_VARIANT_SPLIT, which need no residency either.
 inline bool slab_reaches(int max_rank, int width) { return (long long)max_rank * width <= 1ll << 31; }

@@ -527,19 +527,59 @@ def test_every_unit_runs_with_its_own_rank(oracle_mod, variant, ranks):
     check_forward(oracle_mod, p, variant)
 
 
-@pytest.mark.parametrize("max_rank,T,d_in,d_out", [(64, 1000, 264, 520), (128, 700, 1032, 776), (64, 700, 8200, 264), (64, 12000, 4096, 4096)])
-def test_automatic_choice_above_rank_32(oracle_mod, max_rank, T, d_in, d_out):
-    """Either side of the automatic rule's lines (few and many rows, a wide input) equals one of the two variants bit for bit."""
-    p = synth.small_mixed(max_rank + T, T, d_in, d_out, [max_rank, 8, 24], drop_frac=0.1)
-    got = []
-    for v in (lq.LQ_VARIANT_AUTO, lq.LQ_VARIANT_SLAB, lq.LQ_VARIANT_FUSED):
-        d = DeviceProblem(p)
-        d.build()
-        y, h, err = d.forward(v)
-        assert err == 0
-        got.append(y)
-    slab = T * (d_in + d_out) <= 48000000 and d_in <= 8192
-    assert np.array_equal(got[0], got[1] if slab else got[2])
+# either side of every line of the automatic rule: max_rank, tokens, d_in, d_out of each layer, the kernel it picks
+AUTO_LINES = [
+    # ranks up to 32: output columns, tokens, layers, input columns
+    (32, 40, 264, [16384], "slab"), (32, 40, 264, [16392], "fused"), (16, 383, 264, [16392], "fused"),
+    (16, 384, 264, [16392], "slab"), (16, 1024, 264, [28672], "slab"), (16, 1025, 264, [16392], "fused"),
+    (16, 500, 264, [28680], "fused"), (32, 500, 4096, [8200, 8200], "slab"), (32, 500, 4104, [8200, 8200], "fused"),
+    (32, 500, 4104, [16400], "slab"), (32, 500, 264, [5528, 5528, 5528], "fused"), (32, 2000, 264, [5456, 5456, 5456], "slab"),
+    # above: groups, tokens, rows x output columns
+    (33, 500, 264, [520], "slab"), (33, 500, 264, [520, 520], "fused"), (64, 8192, 264, [264], "slab"), (64, 8193, 264, [264], "fused"),
+    (64, 6591, 264, [4096], "slab"), (64, 6592, 264, [4096], "fused"), (65, 5859, 264, [4096], "slab"), (65, 5860, 264, [4096], "fused"),
+    (128, 2441, 264, [8192], "slab"), (128, 2442, 264, [8192], "fused"), (64, 1464, 264, [16384], "slab"), (64, 1465, 264, [16384], "fused"),
+    (64, 700, 264, [16392], "fused"), (64, 12000, 4096, [4096], "fused"),
+    # few rows, by the widths
+    (64, 1, 4096, [8192], "slab"), (64, 1, 2048, [8200], "slab"), (64, 255, 2056, [8200], "fused"), (64, 256, 2056, [8200], "slab"),
+    (128, 1, 4096, [4096], "slab"), (128, 1, 2048, [8192], "slab"), (128, 255, 2056, [4104], "fused"), (128, 256, 2056, [4104], "slab"),
+    (128, 255, 264, [8200], "fused"), (128, 256, 264, [8200], "slab"),
+    # wide inputs
+    (64, 1023, 4104, [264], "fused"), (64, 1024, 4104, [264], "slab"), (64, 3000, 4104, [264], "slab"), (64, 3001, 4104, [264], "fused"),
+    (128, 1024, 4104, [264], "fused"), (64, 1024, 8200, [264], "fused"), (64, 1024, 4104, [8200], "fused"),
+]
+
+
+@pytest.mark.parametrize("max_rank,T,d_in,d_outs,kernel", AUTO_LINES)
+def test_automatic_choice(max_rank, T, d_in, d_outs, kernel):
+    """The automatic rule's lines: the kernel that ran, and the explicit variant's y and h bit for bit."""
+    gen = torch.Generator(device="cuda").manual_seed(T + d_in)
+    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    ranks = [max_rank, 8, 24]
+    x = new(T, d_in, 1.0)
+    y0 = [new(T, d, 1.0) for d in d_outs]
+    ads = [lq.AdapterTable.from_tensors([new(r, d_in, 0.02) for r in ranks], [new(r, d, 0.02) for r in ranks], [0.5, 1.0, 2.0]) for d in d_outs]
+    seg = lq.SegmentTables.empty(T, 3)
+    lq.lora_build_segments(torch.randint(-1, 3, (T,), dtype=torch.int32, device="cuda", generator=gen),
+                           torch.randint(0, 3, (T,), dtype=torch.uint8, device="cuda", generator=gen), ads[0].ranks, seg,
+                           lq.workspace(lq.lora_build_workspace_bytes(T, 3)))
+    ws = lq.workspace(lq.lora_forward_group_workspace_bytes(len(d_outs), T, max_rank))
+
+    def run(variant):
+        ys, hs = [y.clone() for y in y0], [torch.zeros(T * max_rank, device="cuda") for _ in y0]
+        lq.lora_profile_enable(True)
+        if len(ys) == 1:
+            lq.lora_segmented_forward(x, ys[0], ads[0], seg, hs[0], ws, variant)
+        else:
+            lq.lora_segmented_forward_group(x, ys, ads, seg, hs, ws, variant)
+        ran = [name for name, (_, n) in lq.lora_profile_read().items() if n]
+        lq.lora_profile_enable(False)
+        lq.raise_on_device_error(ws)
+        return ran, ys + hs
+
+    ran, got = run(lq.LQ_VARIANT_AUTO)
+    assert ran == ["forward_" + kernel]
+    _, want = run({"slab": lq.LQ_VARIANT_SLAB, "fused": lq.LQ_VARIANT_FUSED}[kernel])
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
 
 
 @pytest.mark.parametrize("variant", [lq.LQ_VARIANT_SLAB, lq.LQ_VARIANT_AUTO])
