@@ -246,8 +246,9 @@ lq_status lora_segmented_forward_static(const void* x, int64_t ldx, void* y, int
  *            variant; falls back to two launches where the partial-g region would reach 2 GiB);
  *            LQ_VARIANT_SPLIT: two launches, no device-wide wait; LQ_VARIANT_SLAB: g and dx in one launch of the
  *            forward's slab variant, no device-wide wait; LQ_VARIANT_AUTO: slab or fused by the forward's rule for a
- *            single call, applied to this step (d_out columns of dy in, d_in columns of dx out).  Other values:
- *            LQ_ERR_INVALID_ARG.
+ *            single call, applied to this step (d_out columns of dy in, d_in columns of dx out; n_tokens only bounds
+ *            the fine-tune rows from above, so what takes a least number of tokens is left to the fused variant).
+ *            Other values: LQ_ERR_INVALID_ARG.
  *   workspace lora_backward_workspace_bytes(...) bytes; its first 4096 bytes zero as for the forward.
  *   Then the weight gradients: a fine-tune segment of up to 512 rows is accumulated straight into dA / dB;
  *   a longer one is cut into row chunks whose partial sums go to the workspace and are added in chunk

@@ -364,7 +364,7 @@ extern "C" lq_status lora_segmented_backward(const void* x, int64_t ldx, const v
         return LQ_ERR_INVALID_ARG;
     if (variant != LQ_VARIANT_SPLIT && variant != LQ_VARIANT_FUSED && variant != LQ_VARIANT_SLAB && variant != LQ_VARIANT_AUTO)
         return LQ_ERR_INVALID_ARG;
-    if (variant == LQ_VARIANT_AUTO) variant = auto_variant(max_rank, n_tokens, true, 1, d_out, d_in);  // (the step reads dy and writes dx)
+    if (variant == LQ_VARIANT_AUTO) variant = auto_variant(max_rank, n_tokens, false, 1, d_out, d_in);  // (reads dy, writes dx, of the fine-tune rows)
     if (variant == LQ_VARIANT_SLAB && !(slab_reaches(max_rank, d_in) && slab_reaches(max_rank, d_out))) variant = LQ_VARIANT_SPLIT;
     if (!A_ptrs || !B_ptrs || !ranks || !scales || !seg_starts || !seg_adapter || !seg_kind || !n_segments)
         return LQ_ERR_INVALID_ARG;

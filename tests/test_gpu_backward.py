@@ -216,3 +216,34 @@ def test_backward_of_a_matrix_beyond_4_gib():
     for i in range(0, d_in, 1 << 20):
         want = g @ A[:, i: i + (1 << 20)].double()
         assert float((dx[:, i: i + (1 << 20)].double() - want).norm() / want.norm()) <= 5e-3, i
+
+
+@pytest.mark.parametrize("max_rank,T,d_out,d_in,kernel", [
+    (32, 500, 264, 16384, "slab"), (32, 500, 264, 16392, "fused"),            # the forward takes the slab kernel for both
+    (64, 500, 4096, 8192, "slab"), (64, 500, 2048, 8200, "slab"), (64, 500, 2056, 8200, "fused"),
+    (128, 500, 4096, 4096, "slab"), (128, 500, 2048, 8192, "slab"), (128, 500, 2056, 4104, "fused"),
+    (64, 1500, 4104, 264, "fused"), (64, 8193, 264, 264, "fused")])
+def test_automatic_choice_of_the_backward(max_rank, T, d_out, d_in, kernel):
+    """Only the fine-tune rows run (here one token in ten), so the branches of the rule that need many rows are not taken."""
+    gen = torch.Generator(device="cuda").manual_seed(T + d_in)
+    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    ad = lq.AdapterTable.from_tensors([new(max_rank, d_in, 0.02)], [new(max_rank, d_out, 0.02)], [1.0])
+    x, dy, dx0 = new(T, d_in, 1.0), new(T, d_out, 1.0), new(T, d_in, 1.0)
+    kind = (torch.arange(T, device="cuda") % 10 != 0).to(torch.uint8)
+    seg = lq.SegmentTables.empty(T, 1)
+    lq.lora_build_segments(torch.zeros(T, dtype=torch.int32, device="cuda"), kind, ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, 1)))
+    ws = lq.workspace(lq.lora_backward_workspace_bytes(T, 1, max_rank, d_in, d_out))
+
+    def run(variant):
+        dx = dx0.clone()
+        lq.lora_profile_enable(True)
+        lq.lora_segmented_backward(x, dy, dx, ad, None, None, seg, torch.zeros(T * max_rank, device="cuda"), ws, variant)
+        ran = [name for name, (_, n) in lq.lora_profile_read().items() if n]
+        lq.lora_profile_enable(False)
+        lq.raise_on_device_error(ws)
+        return ran, dx
+
+    ran, got = run(lq.LQ_VARIANT_AUTO)
+    assert ran == ["forward_" + kernel]
+    _, want = run({"slab": lq.LQ_VARIANT_SLAB, "fused": lq.LQ_VARIANT_FUSED}[kernel])
+    assert torch.equal(got, want)
