@@ -1266,16 +1266,15 @@ int shrink_grid()
 // A 128-row shrink unit streams its rows at the rate of one compute unit, so a batch has to be cut into
 // enough units for the launch to draw the full HBM rate and to end evenly: d_in is cut into slices (each
 // at least four stages long) as long as that leaves less than one row chunk x slice per workgroup (more
-// slices cost the expand kernel, which adds them up).  The first cut is also taken where it makes exactly one unit per
-// workgroup: uncut, half of them would have none (16384 rows of rank 64, 4096 -> 4096: 135 -> 126 us); a further cut to the
-// full grid costs more than it gives (8192 Zipf rows, 4096 -> 11008: 125 -> 136 us with four slices instead of two).
-// A pure function of host arguments.
+// slices cost the expand kernel, which adds them up).  The chunks are counted without the segments' remainders, which the
+// host does not know; so a cut that would just fill the grid is not made: 16384 rows of rank 64, 4096 -> 4096, gain 6 %
+// by it in one segment (132 -> 124 us) but lose 7 to 11 % in ragged ones (12 segments 124 -> 138, Zipf lengths 121 -> 130),
+// whose units no longer fit one round; four layers of 4096 rows -17 and +12 %.  A pure function of host arguments.
 int choose_ksplit(int n_tokens, int n_proj, int d_in, int grid)
 {
     const long long chunks = (long long)((n_tokens + kTallRows - 1) / kTallRows) * n_proj;
     int ks = 1;
-    while (ks < ksplit_cap(n_tokens) && (chunks * ks * 2 < grid || (ks == 1 && chunks * 2 <= grid)) && d_in >= ks * 2 * 4 * kStageK)
-        ks *= 2;
+    while (ks < ksplit_cap(n_tokens) && chunks * ks * 2 < grid && d_in >= ks * 2 * 4 * kStageK) ks *= 2;
     return ks;
 }
 
