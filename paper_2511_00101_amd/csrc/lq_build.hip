@@ -334,16 +334,19 @@ __global__ __launch_bounds__(kBuildThreads) void build_segments_multi_kernel(
     // key k: tokens in all workgroups, and in the workgroups before this one
     int total = 0, before = 0;
     if (tid < n_keys) {
-        // (requested together: a loop that adds one count at a time is a chain of up to 16 trips past the L2 caches.
-        // 4864 tokens 9.2 -> 8.6 us, 16384 in 16 workgroups 10.5 -> 9.4)
+        // (requested together: a loop that adds one count at a time is a chain of up to 16 trips past the L2 caches; and only
+        // the counts there are: 16 requests whatever the grid cost up to 12 % with hundreds of keys.  Adding one at a time,
+        // 16 requests, these: 8192 tokens of 96 keys 9.1, 8.5, 8.3 us; 8192 of 900 keys 19.9, 22.4, 19.4; 16384 of 96 10.4, 8.9, 8.8)
         int c[kMultiMaxGroups];
 #pragma unroll
-        for (int i = 0; i < kMultiMaxGroups; ++i)
-            c[i] = __hip_atomic_load(counts + tid * n_groups + min(i, n_groups - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < kMultiMaxGroups; ++i) {
+            c[i] = 0;
+            if (i < n_groups) c[i] = __hip_atomic_load(counts + tid * n_groups + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
 #pragma unroll
         for (int i = 0; i < kMultiMaxGroups; ++i) {
-            total += i < n_groups ? c[i] : 0;
-            before += i < min(g, n_groups) ? c[i] : 0;
+            total += c[i];
+            before += i < g ? c[i] : 0;
         }
     }
     int n_live = 0;

@@ -57,6 +57,21 @@ def test_build_segments_one_and_many_workgroups_agree(oracle_mod):
     assert int(ws[0].item() & 0xffffffff) == 0
 
 
+@pytest.mark.parametrize("groups", range(2, 17))
+def test_build_segments_any_number_of_workgroups(oracle_mod, groups):
+    """One workgroup per 1024 tokens, from two to sixteen: every workgroup adds up the counts of the ones there are."""
+    T, n_ad = 1024 * groups - (groups % 3), 341      # 1023 keys, as many as this builder takes
+    rng = np.random.default_rng(groups)
+    ranks = rng.integers(1, 65, size=n_ad).astype(np.int32)
+    ta, tk = rng.integers(-1, n_ad, size=T).astype(np.int32), rng.integers(0, 3, size=T).astype(np.uint8)
+    ref = oracle_mod.build_segments(ta, tk, ranks)
+    seg = lq.SegmentTables.empty(T, n_ad)
+    ws = lq.workspace(lq.lora_build_workspace_bytes(T, n_ad))
+    ws[4096 // 8:] = -1                              # what an earlier call may have left behind the header
+    lq.lora_build_segments(torch.from_numpy(ta).cuda(), torch.from_numpy(tk).cuda(), torch.from_numpy(ranks).cuda(), seg, ws)
+    assert_tables_equal(seg.to_host(), ref)
+
+
 def test_build_segments_configs(oracle_mod):
     for p in (synth.config1(), synth.config2()):
         d = DeviceProblem(p)
