@@ -86,8 +86,10 @@ __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegI
     slab_unit_rows(p, u, s0, reinterpret_cast<int*>(lds + kRowsOffset));
     __syncthreads();
     const int n_proj = n_proj_of(p);
-    if constexpr (NT >= 4) {
-        // a launch with adapters of different ranks: every unit runs with as many 16-rank tiles as its own adapter needs
+    if constexpr (NT >= 4 && !(GROUP && NT >= 8)) {
+        // a launch with adapters of different ranks: every unit runs with as many 16-rank tiles as its own adapter needs.
+        // (Not the groups above rank 64: eight tiles spill already, and the other passes beside them took the spills from
+        // 40 to 61 registers: 4096 -> 4096, 1024, 1024, 1024 rows of rank 96: 61.5 -> 69.1 us, of mixed ranks 64.4 -> 68.8.)
         for (int pi = 0; pi < n_proj; ++pi) {
             if (NT >= 8 && s0.rank > 64) slab_pass<NT, 1>(p, u, s0, pi, part, parts, lds);  // workgroup uniform
             else if (s0.rank > 32) slab_pass<4, 1>(p, u, s0, pi, part, parts, lds);
