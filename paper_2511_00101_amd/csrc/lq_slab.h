@@ -42,7 +42,7 @@ template <int NT> constexpr int pass_projections() { return NT == 1 ? kMaxProj :
 // phase 1: acc[q][mt][nt] = this wave's share of x[rows] . A_q[ranks]^T for the NP projections of the pass
 // (D[row][rank]: lane (c, kg) receives rows 4 kg .. + 3 of tile mt, rank c of tile nt)
 // =================================================================================================
-template <int NT, int NP, int MT, class PP>
+template <int NT, int NP, int MT, bool ZERO_X, class PP>
 __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegInfo (&s)[NP], const int* lds_row,
                                             u16* slab, f32x4 (&acc)[NP][2][NT])
 {
@@ -80,7 +80,14 @@ __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegI
 #pragma unroll
     for (int i = 0; i < NA; ++i) aoff[i] = (unsigned int)(min(r8 + 8 * i, rank - 1) * p.d_in);
 
-    // a lane's 8 columns lie wholly inside or wholly beyond d_in; beyond, it re-reads column 0 (and A counts as zero)
+    // a lane's 8 columns lie wholly inside or wholly beyond d_in; beyond, it re-reads column 0 and A counts as zero.  With
+    // ZERO_X (launches above rank 32) so does x, or an infinity in column 0 would make the row's h a NaN: the zeros are the 16
+    // bytes that pad every row of the slab.  (It costs no time there; a rank-16 decode batch would pay up to 4 %.)
+    if (ZERO_X && lane < 32) {
+        constexpr u32x4 zero = {0u, 0u, 0u, 0u};
+        *reinterpret_cast<u32x4*>(xs + lane * kPitch + kKB) = zero;
+    }
+    static_assert(kPitch >= kKB + 8, "a row's padding holds 16 bytes");
     auto col_of = [&](int k0) { return k0 + piece * 8 < p.d_in ? k0 : -piece * 8; };
     constexpr int XS = NP >= 3 ? 1 : 2;  // register sets of x = blocks it is requested ahead (one where registers are short)
     u32x4 xv[XS][NJ];
@@ -113,8 +120,7 @@ __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegI
     if constexpr (XS == 2) x_load(1, xv[1]);
     __builtin_amdgcn_sched_barrier(0);
 
-    // (live: false for the block that pads an odd count to the pair the loop below runs; it adds zeros)
-    auto block = [&](int j, auto slot, bool live_block) {
+    auto block = [&](int j, auto slot) {
         constexpr int J = decltype(slot)::value;
         // x of block j: registers -> slab -> fragments; the registers take block j + XS
 #pragma unroll
@@ -122,12 +128,15 @@ __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegI
         x_load(j + XS, xv[J % XS]);
         __builtin_amdgcn_sched_barrier(0);
         wave_sync();
+        int at[2];  // columns beyond d_in are read from the slab's padding
+#pragma unroll
+        for (int h = 0; h < 2; ++h) at[h] = !ZERO_X || k_of(j) + 32 * h + kg * 8 < p.d_in ? 32 * h + kg * 8 : kKB;
         u32x4 xf[MT][2];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) xf[mt][h] = *reinterpret_cast<const u32x4*>(xs + (mt * 16 + c) * kPitch + 32 * h + kg * 8);
-        const bool in_cur = live_block && k_of(j) + piece * 8 < p.d_in;
+            for (int h = 0; h < 2; ++h) xf[mt][h] = *reinterpret_cast<const u32x4*>(xs + (mt * 16 + c) * kPitch + at[h]);
+        const bool in_cur = k_of(j) + piece * 8 < p.d_in;
         auto chunk = [&](auto index) {
             constexpr int N = decltype(index)::value;
             constexpr int q = N / NCH, ch = N % NCH, S = (J * NC + N) & 1;
@@ -166,11 +175,14 @@ __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegI
         static_assert(NC <= 4, "the chunks of a block are listed by name");
         wave_sync();  // the x slab is rewritten by the next block
     };
-    // (pairs of blocks with a single exit: the accumulators stay where they are across the loop)
-    for (int j = 0; j < n_mine; j += 2) {
-        block(j, std::integral_constant<int, 0>{}, true);
-        block(j + 1, std::integral_constant<int, 1>{}, j + 1 < n_mine);
+    // (pairs of blocks with a single exit: the accumulators stay where they are across the loop.  An odd last block runs alone:
+    // padding it to a pair, with zeros for A, made the h of a row with an infinity there a NaN, and cost 1 to 2 %)
+    int j = 0;
+    for (; j + 1 < n_mine; j += 2) {
+        block(j, std::integral_constant<int, 0>{});
+        block(j + 1, std::integral_constant<int, 1>{});
     }
+    if (j < n_mine) block(j, std::integral_constant<int, 0>{});
 }
 
 // =================================================================================================
@@ -330,7 +342,7 @@ __device__ __forceinline__ void slab_expand(const PP&, const Unit& u, const SegI
 // eight partial sums as a balanced tree and hand every live element to emit(projection q of the pass (as an
 // integral constant), row i of the unit, rank j, sum).  work: kWaves x kWaveBytes of LDS.  Ends without a barrier.
 // =================================================================================================
-template <int NT, int NP, class PP, class Emit>
+template <int NT, int NP, bool ZERO_X, class PP, class Emit>
 __device__ __forceinline__ void slab_shrink_sum(const PP& p, const Unit& u0, const SegInfo (&s)[NP], const int* lds_row,
                                                 unsigned char* work, Emit&& emit)
 {
@@ -347,8 +359,8 @@ __device__ __forceinline__ void slab_shrink_sum(const PP& p, const Unit& u0, con
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[q][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
     u16* slab = reinterpret_cast<u16*>(work + (size_t)w * kWaveBytes);
-    if (u0.len <= 16) slab_shrink<NT, NP, 1>(p, u0, s, lds_row, slab, acc);  // workgroup uniform
-    else slab_shrink<NT, NP, 2>(p, u0, s, lds_row, slab, acc);
+    if (u0.len <= 16) slab_shrink<NT, NP, 1, ZERO_X>(p, u0, s, lds_row, slab, acc);  // workgroup uniform
+    else slab_shrink<NT, NP, 2, ZERO_X>(p, u0, s, lds_row, slab, acc);
     {
         float* mine = reinterpret_cast<float*>(slab) + lane;
 #pragma unroll

@@ -19,9 +19,9 @@ constexpr size_t kStashOffset = kRowsOffset + 2 * kSlabRows * sizeof(int);
 constexpr size_t kSlabLdsBytes = kStashOffset + kStashBytes;
 
 // =================================================================================================
-// one pass of a unit: NP projections (pi0 ..) through phase 1, the sum over the waves, and phase 2
+// one pass of a unit: NP projections (pi0 ..) through phase 1, the sum over the waves, and phase 2 (ZERO_X: see slab_shrink)
 // =================================================================================================
-template <int NT, int NP, class PP>
+template <int NT, int NP, bool ZERO_X, class PP>
 __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const SegInfo& s0, int pi0, int part, int parts,
                                           unsigned char* lds)
 {
@@ -48,7 +48,7 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
     // low part, into the fragments phase 2 reads
     u16* hf16 = reinterpret_cast<u16*>(hfrag);
     const bool save = u0.kd == LQ_SEG_FINETUNE && p.h_offsets && part == 0;
-    slab_shrink_sum<NT, NP>(p, u0, s, lds_row, work, [&](auto qc, int i, int j, float sum) {
+    slab_shrink_sum<NT, NP, ZERO_X>(p, u0, s, lds_row, work, [&](auto qc, int i, int j, float sum) {
         constexpr int q = decltype(qc)::value;
         if (save) {
             float* h_out = proj_of(p, pi0 + q).h_out;
@@ -56,7 +56,8 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
         }
         const float scaled = sum * lds_scale[i];
         const unsigned int hi = pack_bf16x2(scaled, 0.f) & 0xffffu;
-        const unsigned int lo = pack_bf16x2(scaled - bf16_lo(hi), 0.f) & 0xffffu;
+        // (no low part of an infinity: the difference would be a NaN)
+        const unsigned int lo = (hi & 0x7fffu) == 0x7f80u ? 0u : pack_bf16x2(scaled - bf16_lo(hi), 0.f) & 0xffffu;
         // fragment (projection q, row tile i / 16, k step j / 32): lane (j % 32 / 8) * 16 + i % 16 holds ranks 8 (j / 8) .. + 7
         const int slot = ((q * 2 + (i >> 4)) * KSTEPS + (j >> 5)) * 2;
         const int ln = ((j >> 3) & 3) * 16 + (i & 15);
@@ -91,20 +92,20 @@ __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegI
         // (Not the groups above rank 64: eight tiles spill already, and the other passes beside them took the spills from
         // 40 to 61 registers: 4096 -> 4096, 1024, 1024, 1024 rows of rank 96: 61.5 -> 69.1 us, of mixed ranks 64.4 -> 68.8.)
         for (int pi = 0; pi < n_proj; ++pi) {
-            if (NT >= 8 && s0.rank > 64) slab_pass<NT, 1>(p, u, s0, pi, part, parts, lds);  // workgroup uniform
-            else if (s0.rank > 32) slab_pass<4, 1>(p, u, s0, pi, part, parts, lds);
-            else if (s0.rank > 16) slab_pass<2, 1>(p, u, s0, pi, part, parts, lds);
-            else slab_pass<1, 1>(p, u, s0, pi, part, parts, lds);
+            if (NT >= 8 && s0.rank > 64) slab_pass<NT, 1, true>(p, u, s0, pi, part, parts, lds);  // workgroup uniform
+            else if (s0.rank > 32) slab_pass<4, 1, true>(p, u, s0, pi, part, parts, lds);
+            else if (s0.rank > 16) slab_pass<2, 1, true>(p, u, s0, pi, part, parts, lds);
+            else slab_pass<1, 1, true>(p, u, s0, pi, part, parts, lds);
         }
         return;
     }
     constexpr int NPP = GROUP ? pass_projections<NT>() : 1;
     for (int pi0 = 0; pi0 < n_proj; pi0 += NPP) {
         const int np = min(NPP, n_proj - pi0);  // workgroup uniform
-        if (NPP >= 4 && np == 4) slab_pass<NT, (NPP >= 4 ? 4 : 1)>(p, u, s0, pi0, part, parts, lds);
-        else if (NPP >= 3 && np == 3) slab_pass<NT, (NPP >= 3 ? 3 : 1)>(p, u, s0, pi0, part, parts, lds);
-        else if (NPP >= 2 && np == 2) slab_pass<NT, (NPP >= 2 ? 2 : 1)>(p, u, s0, pi0, part, parts, lds);
-        else slab_pass<NT, 1>(p, u, s0, pi0, part, parts, lds);
+        if (NPP >= 4 && np == 4) slab_pass<NT, (NPP >= 4 ? 4 : 1), (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
+        else if (NPP >= 3 && np == 3) slab_pass<NT, (NPP >= 3 ? 3 : 1), (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
+        else if (NPP >= 2 && np == 2) slab_pass<NT, (NPP >= 2 ? 2 : 1), (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
+        else slab_pass<NT, 1, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
     }
 }
 

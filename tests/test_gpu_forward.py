@@ -646,3 +646,44 @@ def test_slab_column_parts(oracle_mod, chunks):
         p = synth.make_problem("parts", synth.Batch(ta, tk), 136, d_out, rng.integers(1, 17, size=chunks).astype(np.int32),
                                rng.uniform(0.5, 1.5, chunks), chunks, w_std=0.05)
         check_forward(oracle_mod, p, lq.LQ_VARIANT_SLAB)
+
+
+@pytest.mark.parametrize("variant", [lq.LQ_VARIANT_FUSED, lq.LQ_VARIANT_SLAB, lq.LQ_VARIANT_AUTO])
+@pytest.mark.parametrize("d_in", [200, 256, 264, 776, 1032, 4096])
+@pytest.mark.parametrize("ranks", [(33,), (128,), (64, 5, 17), (128, 5, 17, 40)])
+def test_infinities_in_x_above_rank_32(variant, d_in, ranks):
+    """One infinity per row, in the first column, in the last ones and in every 64-column block: with positive adapters h and
+    y are infinite, not NaN, also where a width is no multiple of the block and a wave has an odd number of blocks; rows
+    without one are not touched by their neighbours'.  Segments of 15 rows, fine-tune (h is saved) and decode."""
+    cols = sorted({0, d_in - 1, d_in - 8, *range(5, d_in, 64)})
+    T, d_out = 2 * len(cols), 136
+    gen = torch.Generator(device="cuda").manual_seed(d_in)
+    pos = lambda r, c: torch.rand(r, c, device="cuda", generator=gen).add_(0.5).div_(c ** 0.5).to(torch.bfloat16)
+    x = torch.randn(T, d_in, device="cuda", generator=gen).to(torch.bfloat16)
+    for i, c in enumerate(cols):                       # the even rows; the odd ones stay finite
+        x[2 * i, c] = float("inf")
+    n_ad = max(len(ranks), (T + 29) // 30)
+    A, B = [pos(ranks[a % len(ranks)], d_in) for a in range(n_ad)], [pos(ranks[a % len(ranks)], d_out) for a in range(n_ad)]
+    ad = lq.AdapterTable.from_tensors(A, B, [0.5] * n_ad)
+    at = torch.arange(T, device="cuda")
+    seg = lq.SegmentTables.empty(T, n_ad)
+    lq.lora_build_segments((at // 30).to(torch.int32), (at // 15 % 2 * 2).to(torch.uint8), ad.ranks, seg,
+                           lq.workspace(lq.lora_build_workspace_bytes(T, n_ad)))
+    y, h = torch.zeros(T, d_out, dtype=torch.bfloat16, device="cuda"), torch.zeros(T * ad.max_rank, device="cuda")
+    ws = lq.workspace(lq.lora_forward_workspace_bytes(T, ad.max_rank, d_in, d_out, variant))
+    lq.lora_segmented_forward(x, y, ad, seg, h, ws, variant)
+    torch.cuda.synchronize()
+    lq.raise_on_device_error(ws)
+    used = 0
+    for first in range(0, T, 15):                      # a segment: adapter first // 30, fine-tune or decode
+        a, rows = first // 30, torch.arange(first, min(T, first + 15), device="cuda")
+        inf, fin = rows[rows % 2 == 0], rows[rows % 2 == 1]
+        assert bool((y[inf] == float("inf")).all()), (first, ranks[a % len(ranks)])
+        if len(fin):
+            want = 0.5 * (x[fin].double() @ A[a].double().T) @ B[a].double()
+            assert rel_frobenius(y[fin].float().cpu().numpy(), want.cpu().numpy()) <= REL_FROBENIUS
+        if first // 15 % 2 == 0:                       # fine-tune segments save their h, in adapter order
+            r = ranks[a % len(ranks)]
+            hs = h[used: used + len(rows) * r].view(len(rows), r)
+            used += len(rows) * r
+            assert bool((hs[rows % 2 == 0] == float("inf")).all()) and bool(torch.isfinite(hs[rows % 2 == 1]).all())
