@@ -184,8 +184,9 @@ def test_backward_caller_tables_with_repeated_finetune_adapter(oracle_mod):
 
 
 @pytest.mark.parametrize("ranks", [[64, 33, 32, 17, 16, 5], [128, 65, 64, 33, 32, 16]])
-def test_backward_units_run_with_their_own_rank(oracle_mod, ranks):
-    """Weight-gradient units with 1, 2, 4 and 8 rank tiles in one launch: whole segments and (over 512 rows) cut ones."""
+def test_backward_of_mixed_ranks(oracle_mod, ranks):
+    """Adapters that need 1, 2, 4 and 8 rank tiles in one launch.  The slab kernel's units (g and dx) run with their own
+    adapter's, all weight-gradient units with those of the largest rank: whole segments and (over 512 rows) cut ones."""
     lens = [700, 3, 32, 33, 520, 513]
     rng = np.random.default_rng(ranks[0])
     order = rng.permutation(sum(lens))

@@ -530,8 +530,8 @@ def test_slab_variant_runs_beside_other_kernels(oracle_mod):
 @pytest.mark.parametrize("ranks", [[8, 16, 17, 32, 33, 64], [128, 65, 64, 33, 32, 16, 1]])
 def test_every_unit_runs_with_its_own_rank(oracle_mod, variant, ranks):
     """Launches for ranks up to 64 and 128 whose adapters need 1, 2, 4 and 8 rank tiles: segments of one to hundreds of rows
-    (short, single-tile, two-tile and cut units; the fused kernel's expand units beyond its first round take the smaller
-    unit for ranks up to 32)."""
+    (short, single-tile, two-tile and cut units).  The slab kernel's units and the fused kernel's shrink units run with their
+    own adapter's tiles, the fused kernel's expand units with the launch's."""
     rng = np.random.default_rng(len(ranks))
     lens = np.concatenate([[1, 2, 8, 9, 16, 17, 31, 32, 33, 250], rng.integers(1, 90, size=40)])
     ta = np.repeat(rng.integers(0, len(ranks), size=len(lens)), lens).astype(np.int32)
