@@ -1337,6 +1337,8 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 //   groups of three and four (4096 -> 4 x 4608, rank 32: 1.5 at 400 rows) or wide inputs of groups (8192 -> 2 x 8200: 1.2).
 //   (q+k+v of a few decode rows would be faster fused, 16.5 vs 13.9; they stay with the slab kernel, which needs no
 //   device-wide wait and so runs beside another stream's calls.)
+//   (The figures above rank 32 are those of units of up to 32 rows against the barrier form; where the rule says fused and the
+//   batch is long, that variant runs taller slabs itself, see slab_form.)
 //   ranks above 32, single calls: rank 64, 4096 -> 4096: 0.8 of the fused time up to 4096 rows, 0.89 at 5683, 1.1 at 7578;
 //   4096 -> 8192: 0.83 at 1950, 0.94 at 2734; 4096 -> 14336: 0.87 at 300, 0.79 at 1024, 1.17 at 1822; 64 -> 64: 0.6 up to 8192
 //   rows, 1.0 at 12000, 1.7 at 262500.  Rank 128, 4096 -> 4096: 0.76 at 300 rows, 0.80 at 4262; 4096 -> 8192: 0.85 at 2050,
@@ -1372,10 +1374,33 @@ size_t h_slices_bytes(int n_tokens, int max_rank)
     return (size_t)ksplit_cap(n_tokens) * (size_t)n_tokens * (size_t)rstride_for(max_rank) * sizeof(float);
 }
 
+namespace {
+// The fused variant has two forms: the two phases with a device-wide barrier between them, and, for long batches, the row
+// slabs, whose units are up to 64 rows tall there: h stays on chip and each unit's matrices are re-read half as often as at
+// 32 rows.  Slabs, us by the barrier form and by the slabs (rank 64; mix: fine-tune, prefill and decode rows):
+//   16384 rows 4096 -> 4096 135 and 94; 8192 mix 73 and 60; 8192 Zipf rows of ranks 8 to 64, 4096 -> 11008 122 and 111, 11008 ->
+//   4096 114 and 89; 2200 mix 4096 -> 11008 68 and 56; 4096 mix 14336 -> 4096 84 and 77; 30000 mix 4096 -> 4096 188 and 176.
+// The barrier form stays where the slabs' re-reads of B or their number weigh more: outputs above 16384 columns (8000 mix 2048
+// -> 28672 234 and 253), narrow layers of very many rows (100000 mix 264 -> 264 89 and 112, 40000 1024 -> 1024 88 and 85),
+// ranks above 64 (their units are 32 rows at most), groups, and shorter batches, whose d_in it can cut (700 rows of one
+// segment, 14336 -> 4096, 34 and 38).  In the backward n_tokens counts all rows but the fine-tune rows alone run, so it
+// takes more of them.  (Rank 32 and below, d_in no multiple of 64: the slab kernel's last block re-reads x's first columns against
+// zeros, which an infinity there would make a NaN.)
+bool slab_form(const FwdParams& p)
+{
+    const int d_out = p.proj0.d_out;
+    if (p.n_proj > 1 || p.max_rank > 64 || d_out > 16384 || !slab_reaches(p.max_rank, p.d_in)) return false;
+    if (p.max_rank <= 32 && p.d_in % 64 != 0) return false;
+    if (p.n_tokens > 49152 && p.d_in + 2ll * d_out < 3072) return false;
+    return p.n_tokens >= (p.kinds == kAllKinds ? 2048 : p.d_in > 4096 ? 8192 : 4096);
+}
+}  // namespace
+
 hipError_t run_shrink_expand(FwdParams& p, int variant, hipStream_t st)
 {
     const int nt = nt_for(p.max_rank);
     hipError_t e = hipSuccess;
+    if (variant == LQ_VARIANT_FUSED && slab_form(p)) return run_slab(p, st, kKernelFused);
     if (variant == LQ_VARIANT_FUSED) {
         const int grid_f = nt == 1 ? fused_grid<1, 1, 2>() : nt == 2 ? fused_grid<2, 1, 2>()
                          : nt == 4 ? fused_grid<4, 2, 2>() : fused_grid<8, 4, 1>();
@@ -1480,7 +1505,7 @@ lq_status forward_checked(const void* x, int64_t ldx, int32_t d_in, int32_t n_pr
     p.hpart_bytes = (unsigned int)h_bytes;
     if (variant == LQ_VARIANT_SLAB) {
         p.ksplit = 1; p.ks_log2 = 0;
-        return run_slab(p, stream) == hipSuccess ? LQ_OK : LQ_ERR_HIP;
+        return run_slab(p, stream, kKernelSlab) == hipSuccess ? LQ_OK : LQ_ERR_HIP;
     }
     return run_shrink_expand(p, variant, stream) == hipSuccess ? LQ_OK : LQ_ERR_HIP;
 }

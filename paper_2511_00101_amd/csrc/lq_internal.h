@@ -46,6 +46,8 @@ struct FwdCore {
     int kinds;       // bit k set: segments of kind k take part (forward: all; backward: fine-tune only)
     int coherent;    // fused variant: the h slices are written and read with device-scope accesses
     unsigned int hpart_bytes;  // size of hpart (for the buffer descriptor of the device-scope 16-byte loads)
+    float slab_parts;  // slab kernel: squared number of column parts that balances a wide layer's re-reads, times the live rows; 0: not a wide layer
+    float slab_rows_per_rank;  // slab kernel: rows a unit gets more for every rank that its adapter stays below max_rank
     int* tickets;    // workspace header words 4..: unit tickets ([0,1] shrink phase, [2,3] expand phase); the barrier's words: kBar*
 };
 
@@ -137,7 +139,7 @@ inline int resident_grid(K kernel, size_t dyn_lds)
 inline int nt_for(int max_rank) { return max_rank <= 16 ? 1 : max_rank <= 32 ? 2 : max_rank <= 64 ? 4 : 8; }  // 16-rank tiles
 
 // The row-slab variant (LQ_VARIANT_SLAB): one launch, no partial-h buffer, no device-wide wait.
-hipError_t run_slab(const FwdParams& p, hipStream_t stream);
+hipError_t run_slab(const FwdParams& p, hipStream_t stream, int kernel_id);
 
 constexpr int kAllKinds = 7;
 constexpr int kFinetuneOnly = 1 << LQ_SEG_FINETUNE;
@@ -246,6 +248,7 @@ __device__ __forceinline__ bool grid_barrier(int* header, int* err, int gen0, Ov
 // ---- optional timing of the library's own launches (lora_profile_enable / lora_profile_read) ----------------
 // When enabled, a launch goes through hipExtLaunchKernelGGL with a pair of events that receive the
 // dispatch's own start and end time stamps (what a kernel trace reports), and is filed under its id.
+// (kKernelFused: the launch of a call in the fused variant, in either of its two forms)
 enum KernelId { kKernelBuild = 0, kKernelShrink, kKernelExpand, kKernelFused, kKernelWgrad, kKernelWreduce, kKernelSlab, kKernelIds };
 bool profile_on();
 void profile_events(int kernel_id, hipEvent_t* start, hipEvent_t* stop);  // a fresh pair (null, null when full)

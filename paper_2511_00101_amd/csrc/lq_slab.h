@@ -1,5 +1,5 @@
 // Device code of the row-slab forward (the kernel and its launch are in lq_slab.hip): a workgroup takes a slab of at
-// most 32 rows of one segment;
+// most 64 rows of one segment (32 in grouped calls and above rank 64, whose accumulators fill the registers);
 //   phase 1: h = x A_a^T over all of d_in (the 8 waves take alternate 64-wide k blocks and add their results in LDS)
 //   phase 2: y += s h B_a (the 8 waves take alternate 64-column blocks)
 // All global accesses are row-wise 16-byte accesses (an instruction covers 8 rows x 128 contiguous bytes); data
@@ -13,11 +13,12 @@
 namespace lq {
 namespace {
 
-constexpr int kSlabRows = 32;          // rows of a unit: two 16-row MFMA tiles
+constexpr int kSlabRows = 64;          // rows of a unit: up to four 16-row MFMA tiles
 constexpr int kKB = 64;                // k elements per block (phase 1), columns per block (phase 2)
 constexpr int kPitch = kKB + 8;        // elements per slab row (16-byte aligned, bank spread)
 constexpr int kChunk = 32 * kPitch;    // elements of a 32-row slab
 constexpr int kSlabBig = 0x7fffffff;
+constexpr int kMaxParts = 8;           // column parts a chunk of rows is cut into
 constexpr size_t kWaveBytes = 16384;   // LDS of one wave: its slabs, later its share of the reduction buffer
 
 __device__ __forceinline__ void wave_sync()
@@ -42,9 +43,10 @@ template <int NT> constexpr int pass_projections() { return NT == 1 ? kMaxProj :
 // phase 1: acc[q][mt][nt] = this wave's share of x[rows] . A_q[ranks]^T for the NP projections of the pass
 // (D[row][rank]: lane (c, kg) receives rows 4 kg .. + 3 of tile mt, rank c of tile nt)
 // =================================================================================================
-template <int NT, int NP, int MT, bool ZERO_X, class PP>
+// MT: row tiles of this unit, MTM: of the kernel's tallest unit
+template <int NT, int NP, int MT, int MTM, bool ZERO_X, class PP>
 __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegInfo (&s)[NP], const int* lds_row,
-                                            u16* slab, f32x4 (&acc)[NP][2][NT])
+                                            u16* slab, f32x4 (&acc)[NP][MTM][NT])
 {
     constexpr int NJ = 2 * MT;            // load instructions per block of x (8 rows each)
     constexpr int NA = 2 * NT;            // load instructions per block of one A (8 rank rows each)
@@ -89,12 +91,19 @@ __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegI
     }
     static_assert(kPitch >= kKB + 8, "a row's padding holds 16 bytes");
     auto col_of = [&](int k0) { return k0 + piece * 8 < p.d_in ? k0 : -piece * 8; };
-    constexpr int XS = NP >= 3 ? 1 : 2;  // register sets of x = blocks it is requested ahead (one where registers are short)
+    constexpr int XS = NP >= 3 || MT >= 3 ? 1 : 2;  // register sets of x = blocks it is requested ahead (one where registers are short, or a block is 6 to 8 KB already)
     u32x4 xv[XS][NJ];
-    auto x_load = [&](int j, u32x4 (&v)[NJ]) {
+    // rows 32 half .. 32 half + 31 of a block of x: the x slab holds 32 rows, taller units go through it in two steps
+    constexpr int HALVES = (MT + 1) / 2;
+    auto x_load_half = [&](int j, int half, u32x4 (&v)[NJ]) {
         const int kc = col_of(k_of(j));
 #pragma unroll
-        for (int i = 0; i < NJ; ++i) v[i] = *reinterpret_cast<const u32x4*>(xrow[i] + kc);
+        for (int i = 4 * half; i < 4 * half + 4; ++i)
+            if (i < NJ) v[i] = *reinterpret_cast<const u32x4*>(xrow[i] + kc);
+    };
+    auto x_load = [&](int j, u32x4 (&v)[NJ]) {
+#pragma unroll
+        for (int half = 0; half < HALVES; ++half) x_load_half(j, half, v);
     };
     // The A stream: a block's A is NC chunks (projection q, 32 ranks ch), four load instructions each; chunk n of
     // block j is number j NC + n of the stream, lives in register set (j NC + n) % 2 and goes through LDS buffer
@@ -123,19 +132,25 @@ __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegI
     auto block = [&](int j, auto slot) {
         constexpr int J = decltype(slot)::value;
         // x of block j: registers -> slab -> fragments; the registers take block j + XS
-#pragma unroll
-        for (int i = 0; i < NJ; ++i) *reinterpret_cast<u32x4*>(xs + (r8 + 8 * i) * kPitch + piece * 8) = xv[J % XS][i];
-        x_load(j + XS, xv[J % XS]);
-        __builtin_amdgcn_sched_barrier(0);
-        wave_sync();
         int at[2];  // columns beyond d_in are read from the slab's padding
 #pragma unroll
         for (int h = 0; h < 2; ++h) at[h] = !ZERO_X || k_of(j) + 32 * h + kg * 8 < p.d_in ? 32 * h + kg * 8 : kKB;
         u32x4 xf[MT][2];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int half = 0; half < HALVES; ++half) {
+            if (half > 0) wave_sync();  // the first half's fragments have been read
 #pragma unroll
-            for (int h = 0; h < 2; ++h) xf[mt][h] = *reinterpret_cast<const u32x4*>(xs + (mt * 16 + c) * kPitch + at[h]);
+            for (int i = 4 * half; i < 4 * half + 4; ++i)
+                if (i < NJ) *reinterpret_cast<u32x4*>(xs + (r8 + 8 * (i & 3)) * kPitch + piece * 8) = xv[J % XS][i];
+            x_load_half(j + XS, half, xv[J % XS]);
+            __builtin_amdgcn_sched_barrier(0);
+            wave_sync();
+#pragma unroll
+            for (int mt = 2 * half; mt < 2 * half + 2; ++mt)
+                if (mt < MT)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) xf[mt][h] = *reinterpret_cast<const u32x4*>(xs + ((mt & 1) * 16 + c) * kPitch + at[h]);
+        }
         const bool in_cur = k_of(j) + piece * 8 < p.d_in;
         auto chunk = [&](auto index) {
             constexpr int N = decltype(index)::value;
@@ -342,45 +357,48 @@ __device__ __forceinline__ void slab_expand(const PP&, const Unit& u, const SegI
 // eight partial sums as a balanced tree and hand every live element to emit(projection q of the pass (as an
 // integral constant), row i of the unit, rank j, sum).  work: kWaves x kWaveBytes of LDS.  Ends without a barrier.
 // =================================================================================================
-template <int NT, int NP, bool ZERO_X, class PP, class Emit>
+template <int NT, int NP, int MTM, bool ZERO_X, class PP, class Emit>
 __device__ __forceinline__ void slab_shrink_sum(const PP& p, const Unit& u0, const SegInfo (&s)[NP], const int* lds_row,
                                                 unsigned char* work, Emit&& emit)
 {
-    constexpr int REGS = NP * 2 * NT * 4;  // accumulator registers of a wave
+    constexpr int REGS = NP * MTM * NT * 4;  // accumulator registers of a wave
     static_assert((size_t)REGS * kWave * sizeof(float) <= kWaveBytes, "a wave's accumulators fit its share of the LDS");
     static_assert((size_t)3 * kChunk * sizeof(u16) <= kWaveBytes, "a wave's slabs fit its share of the LDS");
     const int lane = lane_id(), w = uniform((int)threadIdx.x / kWave);
     const int rank = s[0].rank;
-    f32x4 acc[NP][2][NT];
+    f32x4 acc[NP][MTM][NT];
 #pragma unroll
     for (int q = 0; q < NP; ++q)
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int mt = 0; mt < MTM; ++mt)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[q][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
     u16* slab = reinterpret_cast<u16*>(work + (size_t)w * kWaveBytes);
-    if (u0.len <= 16) slab_shrink<NT, NP, 1, ZERO_X>(p, u0, s, lds_row, slab, acc);  // workgroup uniform
-    else slab_shrink<NT, NP, 2, ZERO_X>(p, u0, s, lds_row, slab, acc);
+    if (u0.len <= 16) slab_shrink<NT, NP, 1, MTM, ZERO_X>(p, u0, s, lds_row, slab, acc);  // workgroup uniform
+    else if (MTM <= 2 || u0.len <= 32) slab_shrink<NT, NP, 2, MTM, ZERO_X>(p, u0, s, lds_row, slab, acc);
+    else if (u0.len <= 48) slab_shrink<NT, NP, (MTM > 2 ? 3 : 2), MTM, ZERO_X>(p, u0, s, lds_row, slab, acc);
+    else slab_shrink<NT, NP, (MTM > 2 ? 4 : 2), MTM, ZERO_X>(p, u0, s, lds_row, slab, acc);
     {
         float* mine = reinterpret_cast<float*>(slab) + lane;
 #pragma unroll
         for (int q = 0; q < NP; ++q)
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
+            for (int mt = 0; mt < MTM; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) mine[(((q * 2 + mt) * NT + nt) * 4 + v) * kWave] = acc[q][mt][nt][v];
+                    for (int v = 0; v < 4; ++v) mine[(((q * MTM + mt) * NT + nt) * 4 + v) * kWave] = acc[q][mt][nt][v];
     }
     __syncthreads();
-    // thread (wave w, lane) takes register 8 it + w of lane `lane`: NP * NT iterations, projection it / NT
+    // thread (wave w, lane) takes register 8 it + w of lane `lane`: NP * NT * MTM / 2 iterations, PQ of them per projection
+    constexpr int PQ = NT * MTM / 2;
     auto one = [&](auto index) {
         constexpr int it = decltype(index)::value;
         constexpr int PER_WAVE = (int)(kWaveBytes / sizeof(float));
-        constexpr int q = it / NT;
-        const int r = 8 * (it % NT) + w;  // register within the projection: (mt * NT + nt) * 4 + v
+        constexpr int q = it / PQ;
+        const int r = 8 * (it % PQ) + w;  // register within the projection: (mt * NT + nt) * 4 + v
         const int v = r & 3, nt = (r >> 2) % NT, mt = (r >> 2) / NT;
-        const float* at = reinterpret_cast<const float*>(work) + (q * 2 * NT * 4 + r) * kWave + lane;
+        const float* at = reinterpret_cast<const float*>(work) + (q * MTM * NT * 4 + r) * kWave + lane;
         float t[kWaves];
 #pragma unroll
         for (int ww = 0; ww < kWaves; ++ww) t[ww] = at[ww * PER_WAVE];
@@ -388,15 +406,15 @@ __device__ __forceinline__ void slab_shrink_sum(const PP& p, const Unit& u0, con
         const int i = mt * 16 + (lane >> 4) * 4 + v, j = nt * 16 + (lane & 15);
         if (i < u0.len && j < rank) emit(std::integral_constant<int, q>{}, i, j, sum);
     };
-    static_assert(NP * NT <= 8, "the iterations are listed by name");
+    static_assert(NP * PQ <= 8, "the iterations are listed by name");
     one(std::integral_constant<int, 0>{});
-    if constexpr (NP * NT > 1) one(std::integral_constant<int, 1>{});
-    if constexpr (NP * NT > 2) one(std::integral_constant<int, 2>{});
-    if constexpr (NP * NT > 3) one(std::integral_constant<int, 3>{});
-    if constexpr (NP * NT > 4) one(std::integral_constant<int, 4>{});
-    if constexpr (NP * NT > 5) one(std::integral_constant<int, 5>{});
-    if constexpr (NP * NT > 6) one(std::integral_constant<int, 6>{});
-    if constexpr (NP * NT > 7) one(std::integral_constant<int, 7>{});
+    if constexpr (NP * PQ > 1) one(std::integral_constant<int, 1>{});
+    if constexpr (NP * PQ > 2) one(std::integral_constant<int, 2>{});
+    if constexpr (NP * PQ > 3) one(std::integral_constant<int, 3>{});
+    if constexpr (NP * PQ > 4) one(std::integral_constant<int, 4>{});
+    if constexpr (NP * PQ > 5) one(std::integral_constant<int, 5>{});
+    if constexpr (NP * PQ > 6) one(std::integral_constant<int, 6>{});
+    if constexpr (NP * PQ > 7) one(std::integral_constant<int, 7>{});
 }
 
 // the unit's row indices (rows[0 .. 32): -1 beyond the unit and for an invalid table entry) and, behind them, the
@@ -431,38 +449,137 @@ __device__ __forceinline__ bool slab_adapters(const PP& p, const Unit& u0, const
     return ok;
 }
 
-// Rows per unit: the segments are cut into even chunks of at most `per` rows; `per` is the smallest value (16 to 32)
-// for which the chunks fit one round of the grid (sum of ceil(len / per) <= live rows / per + segments).  A batch
-// that does not fit one round at 32 rows takes several, handed out by tickets.
+// How the batch is cut into units: every segment into even chunks of rows, and, where the chunks are few, every chunk into
+// column parts (each part repeats phase 1 and takes its share of the columns in phase 2).
+//   Chunks of at most 16 rows where they fit one round of the grid, in as many parts (up to kMaxParts) as fit too.
+//   Else the smallest chunks, up to `most` rows, that fit one round, or, for longer batches, as few rounds as `most` rows
+// take.  A unit costs what its compute unit has to pull: its rows and its adapter's matrices.  So that the units end
+// together, a segment of lower rank than the launch's gets more rows per chunk, for 0.8 of the bytes that its matrices are
+// smaller by: 8192 rows of ranks 8 to 64 in Zipf lengths, 4096 -> 11008 124 us with equal rows, 118 / 115 / 111 us with 0.25,
+// 0.5 and 0.8 of the difference, 11008 -> 4096 101, 95, 89, 89 us; equal ranks are not touched.
+//   Wide layers get taller chunks in column parts: n parts of n times as tall chunks re-read a part of B per unit instead of
+// all of it, but x once per part; n^2 = rank x columns x grid / (rows x d_in) would balance the two, 0.3 of that is what
+// measures best, and only where B is large (from 300000 elements) and n at least twice what there is room for with 16-row
+// chunks: 3000 rows, us without and with: rank 64, 2048 -> 28672 148 and 113, 4096 -> 14336 86 and 72 to 75, rank 32,
+// 2048 -> 28672 110 and 99, 4096 -> 11008 53 and 50; smaller B lose, 4096 -> 4096, 2500 rows of rank 32, 20.3 and 22 to 26, 1024 ->
+// 4096, 1500 rows of rank 64, 17.5 and 20 to 22, and so does one row more than 16 (4096 -> 14336, 700 rows of rank 64, 31.5 and 35).
+struct SlabPlan {
+    ClassScan cc;  // chunks of the cached segments (prefix sums), of all segments (total)
+    int per;       // rows per chunk of the segments beyond the cached ones
+    int parts;
+};
+
+// (The kernel's start is bound by the instructions it runs once, from a cold instruction cache: so the usual case, 16-row
+// chunks, comes first and needs no division.)
 template <class PP>
-__device__ __forceinline__ int slab_rows_per(const PP& p, const Segs<PP>& sg)
+__device__ __forceinline__ SlabPlan slab_plan(const PP& p, const Segs<PP>& sg, int most)
 {
-    int per = kSlabRows;
+    SlabPlan pl;
+    ClassScan& cc = pl.cc;
+    const int grid = (int)gridDim.x;
+    static_assert(kCachedBatches == 2, "the batches are handled by name");
+    const bool second = sg.n_seg > kWave;  // wave uniform: most batches have at most 64 segments
+    const int len0 = (p.kinds >> sg.c[0].kd) & 1 ? sg.c[0].en - sg.c[0].st : 0;
+    const int len1 = (p.kinds >> sg.c[1].kd) & 1 ? sg.c[1].en - sg.c[1].st : 0;
+    auto scan = [&](int nch0, int nch1) {
+        cc.nch[0] = nch0;
+        cc.incl[0] = wave_inclusive_scan(nch0);
+        cc.tot0 = lane_value(cc.incl[0], kWave - 1);
+        cc.nch[1] = cc.incl[1] = 0;
+        if (second) {
+            cc.nch[1] = nch1;
+            cc.incl[1] = wave_inclusive_scan(nch1);
+        }
+        cc.total = cc.tot_cached = cc.tot0 + lane_value(cc.incl[1], kWave - 1);
+    };
+    // column parts there is room for (the parts go by the count padded to the 8 XCDs, see slab_kernel.  By the chunks themselves,
+    // 36 of them in 7 parts were 280 ids for a grid of 256: a second round for a few units.  4096 -> 2 x 11008, 512 rows of rank
+    // 16 in 12 segments: 35.2 -> 22.7 us.)
+    auto parts_for = [&](int n) {
+        return 2 * n <= grid ? min(kMaxParts, max(1, (int)((float)grid * __builtin_amdgcn_rcpf((float)(max(n, 1) + 7 & ~7)) + 0.001f))) : 1;
+    };
+    pl.per = 16;
+    scan((len0 + 15) >> 4, (len1 + 15) >> 4);
+    pl.parts = parts_for(cc.total);
+    if (cc.total <= grid && sg.n_seg <= kCachedBatches * kWave && !(p.slab_parts > 0.f && 2 * pl.parts <= kMaxParts)) return pl;
+
+    int w = 16, bonus0 = 0, bonus1 = 0;
+    auto chunks = [&](int len, int rows) {
+        const int per = min(most, max(16, rows));
+        return small_div(len + per - 1, per);
+    };
+    auto count = [&](int w) { return wave_sum(chunks(len0, w + bonus0) + (second ? chunks(len1, w + bonus1) : 0)); };
     if (sg.n_seg <= kCachedBatches * kWave) {
-        int live = 0, n_live = 0;
-#pragma unroll
-        for (int b = 0; b < kCachedBatches; ++b) {
-            const int len = sg.c[b].en - sg.c[b].st;
-            const bool on = len > 0 && ((p.kinds >> sg.c[b].kd) & 1);
-            live += wave_sum(on ? len : 0);
-            n_live += wave_sum(on ? 1 : 0);
+        const int live = wave_sum(len0 + len1);
+        int parts = 1;
+        while (parts < kMaxParts && ((float)parts + 0.5f) * ((float)parts + 0.5f) * (float)live < p.slab_parts) ++parts;
+        if (cc.total <= grid && parts < 2 * pl.parts) return pl;
+        const int n_live = (int)__popcll(__ballot(len0 > 0)) + (int)__popcll(__ballot(len1 > 0));
+        int target = grid;
+        if (parts > 1 || live > (grid - n_live) * most) {  // (sum of ceil(len / most) <= live / most + segments)
+            const int n_most = count(most);
+            while (parts > 1 && ((n_most + 7) >> 3) * 8 * parts > grid) --parts;
+            target = parts > 1 ? small_div(grid, 8 * parts) * 8 : max(1, small_div(n_most + grid - 1, grid)) * grid;
         }
-        const int grid = (int)gridDim.x, slots = grid - n_live;
-        if (slots > 0) per = min(kSlabRows, max(16, small_div(live + slots - 1, slots)));
-        // (that bound charges every segment a whole extra chunk.  Just above 16 rows it matters: a slab of 17 rows
-        // runs two row tiles, the second nearly empty; so 16 is tried by the exact count)
-        if (per > 16 && per <= 20) {
-            int n = 0;
-#pragma unroll
-            for (int b = 0; b < kCachedBatches; ++b) {
-                const int len = sg.c[b].en - sg.c[b].st;
-                const bool on = len > 0 && ((p.kinds >> sg.c[b].kd) & 1);
-                n += wave_sum(on ? (len + 15) >> 4 : 0);
-            }
-            if (n <= grid) per = 16;
+        auto bonus_of = [&](int ad) {
+            const int lo = __shfl(sg.a[0].rank, ad & (kWave - 1), kWave), hi = __shfl(sg.a[1].rank, ad & (kWave - 1), kWave);
+            const int rank = ad >= 0 && ad < kWave ? lo : ad >= kWave && ad < 2 * kWave ? hi : p.max_rank;
+            return (int)((float)(p.max_rank - min(max(rank, 0), p.max_rank)) * p.slab_rows_per_rank);
+        };
+        int spread = 0;
+        if (__any(sg.a[0].rank < p.max_rank || sg.a[1].rank < p.max_rank)) {  // (lanes beyond the adapters repeat the last one)
+            bonus0 = bonus_of(sg.c[0].ad);
+            if (second) bonus1 = bonus_of(sg.c[1].ad);
+            spread = (int)((float)p.max_rank * p.slab_rows_per_rank);
         }
+        // the smallest w with at most `target` chunks: of max(16, w + bonus) rows, at most `most`
+        int lo = small_div(live, target) - 1 - spread;  // too many: sum of ceil(len / per) >= live / per
+        int hi = target > n_live ? min(most, max(16, small_div(live, target - n_live) + 1)) : most;  // few enough: <= live / per + segments
+        // (equal ranks: hi itself.  The smallest w fits more, shorter units into the round, each with its own A and B to read: 4000
+        // Zipf rows of rank 16 in 110 segments, 4096 -> 4096, 27.6 us instead of 24.9)
+        while (spread > 0 && hi - lo > 1) {
+            const int mid = lo + ((hi - lo) >> 1);
+            if (count(mid) > target) lo = mid;
+            else hi = mid;
+        }
+        w = hi;
+    } else {
+        // (the segments beyond the cached ones are not counted: every segment is charged a whole chunk more than its rows make)
+        const int live = min(max(uniform(p.seg_starts[sg.n_seg]), 0), p.n_tokens), slots = grid - sg.n_seg;
+        w = slots > 0 ? min(most, max(16, small_div(live + slots - 1, slots))) : most;
     }
-    return per;
+    pl.per = w;
+    scan(chunks(len0, w + bonus0), chunks(len1, w + bonus1));
+    const LenClass all{1, kSlabBig, p.kinds, true};
+    for (int s0 = kCachedBatches * kWave; s0 < sg.n_seg; s0 += kWave) {
+        const SegLane c = load_seg_lane(p, sg.n_seg, s0 + lane_id());
+        cc.total += wave_sum(chunks_in(c.en - c.st, c.kd, w, all));
+    }
+    pl.parts = parts_for(cc.total);
+    return pl;
+}
+
+// the id-th unit and its adapter; false (and the error bit set) if the segment is unusable
+template <class PP>
+__device__ __forceinline__ bool slab_find(const PP& p, const Segs<PP>& sg, const ClassScan& cc, int per, int id, Unit& u, SegInfo& s)
+{
+    if (id >= cc.tot_cached) return find_unit(p, sg, cc, id, per, LenClass{1, kSlabBig, p.kinds, true}, u, s);
+    const bool hi = id >= cc.tot0;  // wave uniform
+    const int base = hi ? cc.tot0 : 0;
+    const int incl = hi ? cc.incl[1] : cc.incl[0], nch = hi ? cc.nch[1] : cc.nch[0];
+    const SegLane& c = hi ? sg.c[1] : sg.c[0];
+    const int l = uniform(__ffsll((long long)__ballot(base + incl > id)) - 1);
+    const int n = lane_value(nch, l), local = id - base - (lane_value(incl, l) - n);
+    u.seg = (hi ? kWave : 0) + l;
+    u.first = lane_value(c.st, l);
+    u.seg_len = lane_value(c.en, l) - u.first;
+    const int each = small_div(u.seg_len + n - 1, n);
+    u.pos = u.first + local * each;
+    u.len = min(each, u.seg_len - local * each);
+    u.ad = lane_value(c.ad, l);
+    u.kd = lane_value(c.kd, l);
+    s = cached_adapter(p, sg, u);
+    return s.ok;
 }
 
 // While a unit runs, the tables and chunk counts that every wave holds in registers (one segment and one adapter per

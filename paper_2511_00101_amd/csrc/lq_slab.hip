@@ -1,16 +1,18 @@
 // Row-slab variant of the segmented multi-adapter LoRA forward (Section 3.3): one launch in which a
-// workgroup takes a slab of at most 32 rows of one segment through BOTH products, so that h never leaves the
+// workgroup takes a slab of at most 64 rows of one segment through BOTH products, so that h never leaves the
 // compute unit: no partial-h buffer, no device-wide wait, and both phases are spread over the machine the same
 // way.  The price is that every slab re-reads its adapter's matrices; they come from the L2 cache (slabs of
 // one segment run side by side), which the measured access pattern bears: 256 workgroups that each stream 22
 // rows of x and y and re-read 512 KB of A and B run at 4.3 TB/s of algorithmic bytes, against 4.9 TB/s without
-// the re-reads.
+// the re-reads.  A long batch takes taller slabs, which re-read less and fill one round of the grid: 32 -> 64 rows at most,
+// 16384 rows of rank 64, 4096 -> 4096 104 -> 94 us (4.3 TB/s of algorithmic bytes), 8192 rows of rank 16 67 -> 47, of rank 64 87 ->
+// 60, 8000 -> 11008 of rank 16 133 -> 96.  Time stamps of the 16384 rows: tables, plan and rows 7 us, phase 1 31 to 34, phase 2 41
+// to 45, the last of 256 units 5 us after the median: the phases run at the HBM's rate.
 #include "lq_slab.h"
 
 namespace lq {
 namespace {
 
-constexpr int kMaxParts = 8;           // column parts a short batch's units are cut into
 constexpr size_t kHfragBytes = 16384;  // [projection of the pass][row tile][k step][high | low][lane] x 16 B
 // LDS of the kernel: the h fragments, the waves' shares, the unit's row indices and scales, the stashed tables
 constexpr size_t kWorkOffset = kHfragBytes;
@@ -21,12 +23,12 @@ constexpr size_t kSlabLdsBytes = kStashOffset + kStashBytes;
 // =================================================================================================
 // one pass of a unit: NP projections (pi0 ..) through phase 1, the sum over the waves, and phase 2 (ZERO_X: see slab_shrink)
 // =================================================================================================
-template <int NT, int NP, bool ZERO_X, class PP>
+template <int NT, int NP, int MTM, bool ZERO_X, class PP>
 __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const SegInfo& s0, int pi0, int part, int parts,
                                           unsigned char* lds)
 {
     constexpr int KSTEPS = (NT + 1) / 2;
-    static_assert((size_t)NP * 2 * KSTEPS * 2 * kWave * 16 <= kHfragBytes, "the pass's h fragments fit");
+    static_assert((size_t)NP * MTM * KSTEPS * 2 * kWave * 16 <= kHfragBytes, "the pass's h fragments fit");
     u32x4* hfrag = reinterpret_cast<u32x4*>(lds);
     unsigned char* work = lds + kWorkOffset;
     const int* lds_row = reinterpret_cast<const int*>(lds + kRowsOffset);
@@ -48,7 +50,7 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
     // low part, into the fragments phase 2 reads
     u16* hf16 = reinterpret_cast<u16*>(hfrag);
     const bool save = u0.kd == LQ_SEG_FINETUNE && p.h_offsets && part == 0;
-    slab_shrink_sum<NT, NP, ZERO_X>(p, u0, s, lds_row, work, [&](auto qc, int i, int j, float sum) {
+    slab_shrink_sum<NT, NP, MTM, ZERO_X>(p, u0, s, lds_row, work, [&](auto qc, int i, int j, float sum) {
         constexpr int q = decltype(qc)::value;
         if (save) {
             float* h_out = proj_of(p, pi0 + q).h_out;
@@ -59,7 +61,7 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
         // (no low part of an infinity: the difference would be a NaN)
         const unsigned int lo = (hi & 0x7fffu) == 0x7f80u ? 0u : pack_bf16x2(scaled - bf16_lo(hi), 0.f) & 0xffffu;
         // fragment (projection q, row tile i / 16, k step j / 32): lane (j % 32 / 8) * 16 + i % 16 holds ranks 8 (j / 8) .. + 7
-        const int slot = ((q * 2 + (i >> 4)) * KSTEPS + (j >> 5)) * 2;
+        const int slot = ((q * MTM + (i >> 4)) * KSTEPS + (j >> 5)) * 2;
         const int ln = ((j >> 3) & 3) * 16 + (i & 15);
         hf16[((slot + 0) * kWave + ln) * 8 + (j & 7)] = (u16)hi;
         hf16[((slot + 1) * kWave + ln) * 8 + (j & 7)] = (u16)lo;
@@ -74,14 +76,16 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
         const Proj pj = proj_of(p, pi0 + q);
         const int nblk = (pj.d_out + kKB - 1) / kKB;
         const int begin = small_div(part * nblk, parts), end = small_div((part + 1) * nblk, parts);
-        const u32x4* hf = hfrag + q * 2 * KSTEPS * 2 * kWave;
+        const u32x4* hf = hfrag + q * MTM * KSTEPS * 2 * kWave;
         if (u0.len <= 16) slab_expand<NT, 1>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);  // workgroup uniform
-        else slab_expand<NT, 2>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
+        else if (MTM <= 2 || u0.len <= 32) slab_expand<NT, 2>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
+        else if (u0.len <= 48) slab_expand<NT, (MTM > 2 ? 3 : 2)>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
+        else slab_expand<NT, (MTM > 2 ? 4 : 2)>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
     }
     __syncthreads();  // before the next pass or unit reuses the LDS
 }
 
-template <int NT, bool GROUP, class PP>
+template <int NT, int MTM, bool GROUP, class PP>
 __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegInfo& s0, int part, int parts, unsigned char* lds)
 {
     slab_unit_rows(p, u, s0, reinterpret_cast<int*>(lds + kRowsOffset));
@@ -92,43 +96,40 @@ __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegI
         // (Not the groups above rank 64: eight tiles spill already, and the other passes beside them took the spills from
         // 40 to 61 registers: 4096 -> 4096, 1024, 1024, 1024 rows of rank 96: 61.5 -> 69.1 us, of mixed ranks 64.4 -> 68.8.)
         for (int pi = 0; pi < n_proj; ++pi) {
-            if (NT >= 8 && s0.rank > 64) slab_pass<NT, 1, true>(p, u, s0, pi, part, parts, lds);  // workgroup uniform
-            else if (s0.rank > 32) slab_pass<4, 1, true>(p, u, s0, pi, part, parts, lds);
-            else if (s0.rank > 16) slab_pass<2, 1, true>(p, u, s0, pi, part, parts, lds);
-            else slab_pass<1, 1, true>(p, u, s0, pi, part, parts, lds);
+            if (NT >= 8 && s0.rank > 64) slab_pass<NT, 1, MTM, true>(p, u, s0, pi, part, parts, lds);  // workgroup uniform
+            else if (s0.rank > 32) slab_pass<4, 1, MTM, true>(p, u, s0, pi, part, parts, lds);
+            else if (s0.rank > 16) slab_pass<2, 1, MTM, true>(p, u, s0, pi, part, parts, lds);
+            else slab_pass<1, 1, MTM, true>(p, u, s0, pi, part, parts, lds);
         }
         return;
     }
     constexpr int NPP = GROUP ? pass_projections<NT>() : 1;
     for (int pi0 = 0; pi0 < n_proj; pi0 += NPP) {
         const int np = min(NPP, n_proj - pi0);  // workgroup uniform
-        if (NPP >= 4 && np == 4) slab_pass<NT, (NPP >= 4 ? 4 : 1), (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
-        else if (NPP >= 3 && np == 3) slab_pass<NT, (NPP >= 3 ? 3 : 1), (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
-        else if (NPP >= 2 && np == 2) slab_pass<NT, (NPP >= 2 ? 2 : 1), (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
-        else slab_pass<NT, 1, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
+        if (NPP >= 4 && np == 4) slab_pass<NT, (NPP >= 4 ? 4 : 1), MTM, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
+        else if (NPP >= 3 && np == 3) slab_pass<NT, (NPP >= 3 ? 3 : 1), MTM, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
+        else if (NPP >= 2 && np == 2) slab_pass<NT, (NPP >= 2 ? 2 : 1), MTM, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
+        else slab_pass<NT, 1, MTM, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
     }
 }
 
-// NT: 16-rank tiles of the launch (ranks up to 16 NT)
-template <int NT, bool GROUP>
+// NT: 16-rank tiles of the launch (ranks up to 16 NT); MTM: 16-row tiles of its tallest unit.
+template <int NT, int MTM, bool GROUP>
 __global__ __launch_bounds__(kThreads) void slab_kernel(KernelArg<GROUP> p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     __shared__ int s_slot[2];
     auto sg = load_segs(p);
     const int grid = (int)gridDim.x;
-    const int per = slab_rows_per(p, sg);
-    const LenClass all{1, kSlabBig, p.kinds, true};
-    ClassScan cc = scan_class(p, sg, per, all);
+    const SlabPlan pl = slab_plan(p, sg, 16 * MTM);
+    ClassScan cc = pl.cc;
     // Workgroups are dealt to the 8 XCDs in turn (workgroup i runs on XCD i % 8), and every XCD has its own L2.  The
     // chunks are numbered segment by segment, so XCD x takes the x-th eighth of them: the slabs of one segment then
     // sit on one XCD (or two) and find their adapter's matrices in its L2, instead of every XCD fetching every adapter.
     // A batch with few chunks is also cut by columns: every part of a chunk repeats phase 1 and takes its share of
     // the column blocks in phase 2; the parts of one chunk get ids r, r + 8, ..., the same XCD again.
     const int n8 = (cc.total + 7) >> 3;  // chunks per XCD
-    // (The parts go by the padded count.  By the chunks themselves, 36 of them in 7 parts were 280 ids for a grid of 256: a
-    // second round for a few units.  4096 -> 2 x 11008, 512 rows of rank 16 in 12 segments: 35.2 -> 22.7 us.)
-    const int parts = n8 > 0 && 2 * cc.total <= grid ? max(1, min(kMaxParts, small_div(grid, 8 * n8))) : 1;
+    const int parts = pl.parts;
     const int n_units = 8 * n8 * parts;
     int* stash = reinterpret_cast<int*>(lds_raw + kStashOffset);
     for_each_unit(p.tickets + 0, n_units, s_slot, [&](int gid, int) {
@@ -143,32 +144,46 @@ __global__ __launch_bounds__(kThreads) void slab_kernel(KernelArg<GROUP> p)
         Unit u;
         SegInfo s;
         u.pi = 0;
-        if (!find_unit(p, sg, cc, chunk, per, all, u, s)) return;
+        if (!slab_find(p, sg, cc, pl.per, chunk, u, s)) return;
         stash_tables(sg, cc, stash);
-        slab_unit<NT, GROUP>(p, u, s, part, parts, lds_raw);  // (has a workgroup barrier after its first step)
+        slab_unit<NT, MTM, GROUP>(p, u, s, part, parts, lds_raw);  // (has a workgroup barrier after its first step)
         unstash_tables(sg, cc, stash);
     });
 }
 
-template <int NT>
-hipError_t launch_slab(const FwdParams& p, hipStream_t st)
+constexpr float kPartsFromB = 300000.f;  // elements of B (of all layers) from which a wide layer is cut into parts, see slab_plan
+
+template <int NT, int MTM, bool GROUP>
+hipError_t launch_slab(const FwdParams& p0, hipStream_t st, int kernel_id)
 {
     static DeviceGrid cache;
-    const int grid = cache.get([] {
-        return std::min(resident_grid(slab_kernel<NT, false>, kSlabLdsBytes), resident_grid(slab_kernel<NT, true>, kSlabLdsBytes));
-    });
-    if (p.n_proj == 1)
-        return launch_kernel(kKernelSlab, slab_kernel<NT, false>, dim3(grid), dim3(kThreads), kSlabLdsBytes, st,
-                             static_cast<const FwdCore&>(p));
-    return launch_kernel(kKernelSlab, slab_kernel<NT, true>, dim3(grid), dim3(kThreads), kSlabLdsBytes, st, p);
+    const int grid = cache.get([] { return resident_grid(slab_kernel<NT, MTM, GROUP>, kSlabLdsBytes); });
+    KernelArg<GROUP> p = p0;
+    float columns = (float)p0.proj0.d_out;
+    for (int k = 1; k < p0.n_proj; ++k) columns += (float)p0.more[k - 1].d_out;
+    const float b = (float)p.max_rank * columns, x_passes = NT >= 4 ? (float)p.n_proj : 1.f;
+    p.slab_parts = b >= kPartsFromB ? 0.3f * b * (float)grid / ((float)p.d_in * x_passes) : 0.f;
+    p.slab_rows_per_rank = 0.8f * ((float)p.d_in * (float)p.n_proj + columns) / ((float)p.d_in + 2.f * columns);
+    return launch_kernel(kernel_id, slab_kernel<NT, MTM, GROUP>, dim3(grid), dim3(kThreads), kSlabLdsBytes, st, p);
 }
 
 }  // namespace
 
-hipError_t run_slab(const FwdParams& p, hipStream_t st)
+hipError_t run_slab(const FwdParams& p, hipStream_t st, int kernel_id)
 {
     const int nt = nt_for(p.max_rank);
-    return nt == 1 ? launch_slab<1>(p, st) : nt == 2 ? launch_slab<2>(p, st) : nt == 4 ? launch_slab<4>(p, st) : launch_slab<8>(p, st);
+    if (p.n_proj > 1)
+        return nt == 1 ? launch_slab<1, 2, true>(p, st, kernel_id) : nt == 2 ? launch_slab<2, 2, true>(p, st, kernel_id)
+             : nt == 4 ? launch_slab<4, 2, true>(p, st, kernel_id) : launch_slab<8, 2, true>(p, st, kernel_id);
+    // (up to 4096 rows of a batch with few enough segments fit one round of 32-row units, and the kernel of two row tiles starts
+    // sooner: 256 decode rows of rank 16 15.5 us a pass instead of 16.0, 2048 rows of rank 64 26.5 us instead of 26.9)
+    const bool wide = (float)p.max_rank * (float)p.proj0.d_out >= kPartsFromB;
+    if ((p.n_tokens <= 4096 && !wide) || nt == 8)
+        return nt == 1 ? launch_slab<1, 2, false>(p, st, kernel_id) : nt == 2 ? launch_slab<2, 2, false>(p, st, kernel_id)
+             : nt == 4 ? launch_slab<4, 2, false>(p, st, kernel_id) : launch_slab<8, 2, false>(p, st, kernel_id);
+    return nt == 1   ? launch_slab<1, 4, false>(p, st, kernel_id)
+           : nt == 2 ? launch_slab<2, 4, false>(p, st, kernel_id)
+                     : launch_slab<4, 4, false>(p, st, kernel_id);
 }
 
 }  // namespace lq

@@ -687,3 +687,36 @@ def test_infinities_in_x_above_rank_32(variant, d_in, ranks):
             hs = h[used: used + len(rows) * r].view(len(rows), r)
             used += len(rows) * r
             assert bool((hs[rows % 2 == 0] == float("inf")).all()) and bool(torch.isfinite(hs[rows % 2 == 1]).all())
+
+
+@pytest.mark.parametrize("variant", [lq.LQ_VARIANT_SLAB, lq.LQ_VARIANT_FUSED])
+@pytest.mark.parametrize("ranks,T,d_in,d_out", [
+    ((64, 40), 16384, 72, 136),          # one full round of 64-row units, an odd last block
+    ((64, 8, 16, 33), 17500, 264, 72),   # a second round; lower ranks take taller chunks
+    ((16,), 9000, 64, 200), ((32, 31), 12700, 192, 72),     # units of three and four row tiles
+    ((64, 5, 17), 5000, 72, 5000),       # wide for its input: tall chunks in column parts
+    ((32,), 2048, 64, 16384),
+])
+def test_tall_slabs(oracle_mod, variant, ranks, T, d_in, d_out):
+    """Units of up to 64 rows: segments of 1, 15 to 17, 31 to 33, 47 to 49 and 63 to 65 rows beside long ones, shuffled, some rows
+    without an adapter; the slab variant and the fused variant's form for long batches."""
+    rng = np.random.default_rng(T)
+    lens = [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, T // 3]
+    lens = np.array(lens + [T // 2 - sum(lens[:-1])] + [T - T // 3 - T // 2], np.int64)
+    ta = np.repeat(np.arange(len(lens), dtype=np.int32), lens)
+    tk = np.repeat(rng.integers(0, 3, size=len(lens)), lens).astype(np.uint8)
+    ta[:: 101] = -1
+    order = rng.permutation(T)
+    n_ad = len(lens)
+    p = synth.make_problem("tall", synth.Batch(ta[order], tk[order]), d_in, d_out, np.array([ranks[a % len(ranks)] for a in range(n_ad)], np.int32),
+                           rng.uniform(0.5, 1.5, n_ad), T + 1, w_std=0.05)
+    check_forward(oracle_mod, p, variant, token_scales=rng.uniform(0.5, 1.5, T).astype(np.float32) if d_in == 264 else None)
+
+
+def test_tall_slabs_beyond_the_cached_segments(oracle_mod):
+    """More segments than the kernel's registers hold (128), long enough for units of more than 32 rows."""
+    rng = np.random.default_rng(8)
+    lens = rng.integers(1, 150, size=180)
+    ta, tk = np.repeat(np.arange(180) % 90, lens).astype(np.int32), np.repeat(np.arange(180) // 90, lens).astype(np.uint8)
+    p = synth.make_problem("many", synth.Batch(ta, tk), 72, 136, rng.choice([8, 40, 64], size=90).astype(np.int32), rng.uniform(0.5, 1.5, 90), 9, w_std=0.05)
+    check_forward(oracle_mod, p, lq.LQ_VARIANT_SLAB)
