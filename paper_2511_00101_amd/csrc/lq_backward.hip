@@ -6,6 +6,8 @@
 // the forward's expand with (y, B, d_out) := (dx, A, d_in); both reuse those kernels, restricted to
 // fine-tune segments.  The two weight gradients are contractions over the TOKEN axis, which is the
 // strided axis of every operand, so they get a kernel of their own:
+//   (Small and medium batches behind the slab kernel run in units of whole segments instead, without a reduction: see
+//   whole_unit and whole_segments_win.)
 //   weight-gradient unit : 512 rows of a fine-tune segment x 256 columns of dy (for dB, with h) or of x
 //                          (for dA, with g).  32 rows at a time are staged in LDS with coalesced loads
 //                          (four steps in flight in registers, two LDS buffers) and read back
@@ -49,6 +51,8 @@ struct BwdParams {
     const float* h_saved; const long long* h_offsets;
     const float* g;      // g = dy B^T of the fine-tune rows, laid out like h_saved
     int rstride;
+    const u16* frag_g; const u16* frag_h;  // g and h as MFMA operands (see frag_at); frag_tiles 16-rank tiles per step
+    int frag_tiles;
     float* wpart;        // [chunk of a segment with more than 512 rows][rstride][d_out + d_in] partial weight gradients
     int* err;
 };
@@ -209,6 +213,216 @@ __device__ __forceinline__ void wgrad_unit(const BwdParams& p, const Unit& u, in
             }
 }
 
+// =================================================================================================
+// Whole segments: behind the slab kernel, which leaves g and h as ready-made operands (frag_at), a unit takes ALL rows of
+// a segment x 64 columns, so that there are no partials and no reduction launch.  The 8 waves take alternate 32-position
+// steps: the step's rows of dy or x (8 rows x 128 bytes per instruction) go through LDS of the wave's own and come back
+// transposed, the operands of h or g come straight from memory (L2: every unit of a segment reads them).  No workgroup
+// barrier in the loop; the waves' results are added up at the end in a fixed order.
+// What bounds it: a unit's fixed part (tables, adapter, first loads, the sum over the waves, about 5 us) and, in long segments,
+// the column walk; so two steps in flight per wave and few registers do better than four (2048 + 2048 rows of rank 32,
+// 4096 -> 4096: 20.5 us instead of 24; with h as 32-bit rows that every unit splits for itself 21.4, with 144 columns per unit
+// 22.1).  2 x 1024 rows of rank 8: 13.1 + 4.1 us with chunks and reduction, 9.7 whole (3.5 TB/s).
+// =================================================================================================
+constexpr int kWholeCols = 64;  // columns of a unit: a 128-byte line of a row
+constexpr int kWholeTiles = kWholeCols / 16;
+constexpr int kWholePitch = kWholeCols + 8;  // u16 elements per staged row
+
+template <int NT>
+struct WholeCfg {
+    static constexpr int DEPTH = 2;                           // steps in flight
+    static constexpr int RED = NT * 16 < 32 ? NT * 16 : 32;      // accumulator registers that the waves add up at a time
+};
+constexpr size_t kWholeWaveBytes = 32 * kWave * sizeof(float);   // LDS of a wave: its rows, later its share of the sum
+static_assert((size_t)kStepRows * kWholePitch * sizeof(u16) <= kWholeWaveBytes, "a step's rows fit");
+constexpr size_t kWholeLdsBytes = kWaves * kWholeWaveBytes;
+
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// NT: 16-rank tiles of this unit, from rank j0 on
+template <int NT>
+__device__ __forceinline__ void whole_unit(const BwdParams& p, int begin, int end, int rank, float scale, bool for_b, int col_block,
+                                           int j0, float* dst, unsigned char* lds)
+{
+    using C = WholeCfg<NT>;
+    constexpr int D = C::DEPTH, NJ = kStepRows / 8;
+    const int lane = lane_id(), w = uniform((int)threadIdx.x / kWave), c = lane & 15, kg = lane >> 4;
+    const int r8 = lane >> 3, piece = lane & 7;  // an instruction covers 8 rows x 128 bytes
+    const u16* Y = for_b ? p.dy : p.x;
+    const long long ldy = for_b ? p.lddy : p.ldx;
+    const int d = for_b ? p.d_out : p.d_in;
+    const int n0 = col_block * kWholeCols;
+    const bool col_live = n0 + piece * 8 < d;
+    const u16* ycol = Y + min(n0 + piece * 8, d - 8);
+    typedef const __attribute__((address_space(1))) u32x4* gfrag;
+    const gfrag frag = (gfrag)reinterpret_cast<const u32x4*>(for_b ? p.frag_h : p.frag_g) + (j0 >> 4) * 2 * kWave + lane;
+    u16* ly = reinterpret_cast<u16*>(lds + (size_t)w * kWholeWaveBytes);
+
+    const int s0 = (begin >> 5) + w, total = ((end + 31) >> 5) - (begin >> 5);
+    const int n_mine = w < total ? (total - w + kWaves - 1) / kWaves : 0;  // steps w, w + 8, ...
+    auto step_at = [&](int j) { return s0 + kWaves * min(j, n_mine - 1); };  // (past the end: the last step again)
+
+    f32x4 acc[NT][kWholeTiles];
+#pragma unroll
+    for (int jt = 0; jt < NT; ++jt)
+#pragma unroll
+        for (int nt = 0; nt < kWholeTiles; ++nt) acc[jt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    if (n_mine > 0) {  // wave uniform
+        u32x4 gy[D][NJ], gf[D][NT][2];
+        int row_in[D];  // row index of position lane % 32 of the step, as loaded
+        int rows[2];    // the same, a step or two ahead of the loads that need it
+        // All loads are unconditional (clamped addresses), so the number in flight is static.  The table's entry is kept as
+        // it is: checking it where it is loaded would wait for it, and with it for everything in flight.
+        const int32_t* tab = p.perm ? p.perm : p.seg_starts;
+        auto position = [&](int j) { return min(max(step_at(j) * 32 + (lane & 31), begin), end - 1); };
+        auto row_load = [&](int j) { return tab[p.perm ? position(j) : 0]; };
+        auto load = [&](int j, int raw, u32x4 (&y)[NJ], u32x4 (&f)[NT][2], int& row) {
+            row = p.perm ? raw : position(j);
+            const int safe = (unsigned)row < (unsigned)p.n_tokens ? row : 0;
+#pragma unroll
+            for (int i = 0; i < NJ; ++i) y[i] = *reinterpret_cast<const u32x4*>(ycol + (long long)__shfl(safe, r8 + 8 * i, kWave) * ldy);
+            const long long at = (long long)step_at(j) * p.frag_tiles * 2 * kWave;
+#pragma unroll
+            for (int jt = 0; jt < NT; ++jt)
+#pragma unroll
+                for (int part = 0; part < 2; ++part) f[jt][part] = frag[at + (jt * 2 + part) * kWave];
+        };
+        auto step = [&](int j, auto slot) {
+            constexpr int J = decltype(slot)::value, S = J % D;
+            const int first = step_at(j) * 32;
+            const bool inside = first >= begin && first + 32 <= end;  // wave uniform
+            if (!inside || !__all(col_live && (unsigned)row_in[S] < (unsigned)p.n_tokens)) {
+                // positions outside the segment belong to other segments: nothing of them may reach the sums, not even a NaN
+#pragma unroll
+                for (int i = 0; i < NJ; ++i) {
+                    const int pos = first + r8 + 8 * i;
+                    const bool live = col_live && pos >= begin && pos < end && (unsigned)__shfl(row_in[S], r8 + 8 * i, kWave) < (unsigned)p.n_tokens;
+                    gy[S][i] = live ? gy[S][i] : u32x4{0u, 0u, 0u, 0u};
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int pos = first + 8 * kg + 2 * e;
+                    const unsigned int keep = (pos >= begin && pos < end ? 0xffffu : 0u) | (pos + 1 >= begin && pos + 1 < end ? 0xffff0000u : 0u);
+#pragma unroll
+                    for (int jt = 0; jt < NT; ++jt)
+#pragma unroll
+                        for (int part = 0; part < 2; ++part) gf[S][jt][part][e] &= keep;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NJ; ++i) *reinterpret_cast<u32x4*>(ly + (r8 + 8 * i) * kWholePitch + piece * 8) = gy[S][i];
+            u32x4 f[NT][2];
+#pragma unroll
+            for (int jt = 0; jt < NT; ++jt)
+#pragma unroll
+                for (int part = 0; part < 2; ++part) f[jt][part] = gf[S][jt][part];
+            load(j + D, rows[J & 1], gy[S], gf[S], row_in[S]);  // the registers are free: the step D ahead
+            rows[J & 1] = row_load(j + D + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            wave_fence();
+            // the staged rows are the MFMA's k axis: read back transposed
+#pragma unroll
+            for (int nt = 0; nt < kWholeTiles; ++nt) {
+                const u32x4 yf = lds_read_transposed_16x32(ly + nt * 16, kWholePitch);
+#pragma unroll
+                for (int jt = 0; jt < NT; ++jt) {
+                    acc[jt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f[jt][1]), as_bf16x8(yf), acc[jt][nt], 0, 0, 0);
+                    acc[jt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f[jt][0]), as_bf16x8(yf), acc[jt][nt], 0, 0, 0);
+                }
+            }
+            wave_fence();  // the rows are overwritten by the next step
+        };
+        {
+            int r[D];
+#pragma unroll
+            for (int dd = 0; dd < D; ++dd) r[dd] = row_load(dd);
+            rows[0] = row_load(D);  // step j takes rows[j & 1] for step j + D
+            rows[1] = row_load(D + 1);
+#pragma unroll
+            for (int dd = 0; dd < D; ++dd) load(dd, r[dd], gy[dd], gf[dd], row_in[dd]);
+        }
+        constexpr int U = D > 2 ? D : 2;
+        for (int j = 0; j < n_mine; j += U)
+            for_each_slot(std::make_integer_sequence<int, U>{}, [&](auto slot) {
+                if (j + decltype(slot)::value < n_mine) step(j + decltype(slot)::value, slot);
+            });
+    }
+
+    // the sum over the waves, RED accumulator registers at a time: every wave parks its own, then thread (w, lane) adds the
+    // eight partial sums of registers w, w + 8, ... of lane `lane` as a balanced tree
+    float* red = reinterpret_cast<float*>(lds);
+    constexpr int PER_WAVE = C::RED * kWave;
+#pragma unroll
+    for (int part = 0; part < NT * 16 / C::RED; ++part) {
+        __syncthreads();  // the rows (or the previous part's sums) have been read
+#pragma unroll
+        for (int r = 0; r < C::RED; ++r) {
+            const int reg = part * C::RED + r;
+            red[w * PER_WAVE + r * kWave + lane] = acc[reg >> 4][(reg >> 2) & 3][reg & 3];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < C::RED / kWaves; ++it) {
+            const int r = it * kWaves + w, reg = part * C::RED + r;
+            float t[kWaves];
+#pragma unroll
+            for (int ww = 0; ww < kWaves; ++ww) t[ww] = red[ww * PER_WAVE + r * kWave + lane];
+            const float sum = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+            const int jj = j0 + (reg >> 4) * 16 + 4 * kg + (reg & 3), n = n0 + ((reg >> 2) & 3) * 16 + c;
+            if (jj < rank && n < d) unsafeAtomicAdd(dst + (long long)jj * d + n, scale * sum);  // (one addition per segment, see wgrad_unit)
+        }
+    }
+    __syncthreads();  // before the next unit's rows
+}
+
+// segments of a unit by length, the long ones first, so that a launch ends evenly
+__device__ __forceinline__ LenClass whole_segments(bool is_long)
+{
+    return is_long ? LenClass{257, kBig, 1 << LQ_SEG_FINETUNE} : LenClass{1, 257, 1 << LQ_SEG_FINETUNE};
+}
+
+// NT: 16-rank tiles of the launch; every unit runs with its own adapter's.  Ranks above 64 are two units of up to 64 ranks
+// (eight tiles' accumulators and operands do not fit the registers: 175 spilled).
+template <int NT>
+__global__ __launch_bounds__(kThreads, 2) void wgrad_whole_kernel(BwdParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    constexpr int kWhole = 1 << 30;  // rows per unit: no segment is cut
+    int n_seg;
+    const SegCache c0 = load_seg_cache(p, n_seg);
+    const int blocks_b = (p.d_out + kWholeCols - 1) / kWholeCols, blocks_a = (p.d_in + kWholeCols - 1) / kWholeCols;
+    constexpr int HALVES = NT >= 8 ? 2 : 1;
+    const int per_seg = (blocks_b + blocks_a) * HALVES;
+    const int n_long = count_chunks(p, n_seg, c0, kWhole, whole_segments(true)) * per_seg;
+    const int n_units = n_long + count_chunks(p, n_seg, c0, kWhole, whole_segments(false)) * per_seg;
+    for (int id = (int)blockIdx.x; id < n_units; id += (int)gridDim.x) {
+        Unit u;
+        const int base = id < n_long ? 0 : n_long, seg = small_div(id - base, per_seg), at = id - base - seg * per_seg;
+        const int cb = at / HALVES, j0 = HALVES > 1 ? (at & 1) * 64 : 0;
+        if (!find_chunk(p, n_seg, c0, seg, kWhole, whole_segments(id < n_long), u)) continue;
+        if (u.ad < 0 || u.ad >= p.n_adapters) continue;  // flagged by the forward kernels already
+        const bool for_b = cb < blocks_b;
+        // (requested together: one round trip)
+        const int rank = p.ranks[u.ad];
+        const float adapter_scale = p.scales[u.ad];
+        float* const* const ptrs = for_b ? p.dB_ptrs : p.dA_ptrs;
+        float* const dst = ptrs ? ptrs[u.ad] : nullptr;
+        if (rank < 1 || rank > p.max_rank || j0 >= rank || !dst) continue;
+        const float scale = p.token_scales ? 1.f : adapter_scale;  // (per-token scales are in the operands)
+        const int end = u.first + u.seg_len, block = for_b ? cb : cb - blocks_b;
+        const int left = rank - j0;  // > 0
+        if (NT >= 4 && left > 32) whole_unit<(NT >= 4 ? 4 : NT)>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
+        else if (NT >= 2 && left > 16) whole_unit<(NT >= 2 ? 2 : NT)>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
+        else whole_unit<1>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
+    }
+}
+
 // (ranks up to 32: at most 128 registers, so that two workgroups share a compute unit and one's loads
 // overlap the other's barriers)
 // the fine-tune segments with more than 512 rows are cut into chunks (partials, then the reduction); the shorter
@@ -305,6 +519,21 @@ __global__ __launch_bounds__(kThreads) void wreduce_kernel(BwdParams p)
     }
 }
 
+// Whole segments or 512-row chunks, by the host's arguments.  Measured on the backward call (g / dx, weight gradients and,
+// with chunks of batches above 512 tokens, their reduction), us with chunks and whole, fine-tune rows only:
+//   rank 32, 4096 -> 4096, in one segment and in four: 64 rows 18.7 and 16.1, 500 28.5 and 21.4 (one), 24.6 and 24.7 (four), 1000
+//   34.5 and 24.0, 31.5 and 26.8, 2000 38.3 and 30.6, 38.7 and 32.7, 4000 50.8 and 57.9, 52.9 and 52.4; 4096 -> 1024, 4000 rows 40.9
+//   and 38.3, 43.9 and 37.8; 1024 -> 1024, 2000 rows 29.9 and 23.0, 30.2 and 19.1.
+//   rank 64, 4096 -> 4096, 2000 rows 46.9 and 39.6, 50.3 and 43.4; 4096 -> 1024, 4000 rows 53.7 and 55.5, 57.5 and 56.1.
+//   rank 128, 4096 -> 4096, 1000 rows 58.4 and 43.0, 57.6 and 58.3; 500 rows in four segments are the worst, 47.6 and 53.7.
+// Large batches lose because a unit walks down 64 columns, a line of every row, which streams slower from memory than 256
+// columns do; narrow layers of long segments because there are too few units.
+bool whole_segments_win(int n_tokens, int max_rank, int d_in, int d_out)
+{
+    const long long width = (long long)d_in + d_out;
+    return (n_tokens <= 2048 || width >= 5120) && n_tokens * width <= (max_rank <= 32 ? 29000000 : 18000000);
+}
+
 // finished g of the fine-tune rows: at most n_tokens x max_rank floats (a multiple of 16 bytes)
 size_t gsum_bytes(int n_tokens, int max_rank) { return ((size_t)n_tokens * (size_t)max_rank * sizeof(float) + 15) / 16 * 16; }
 
@@ -333,6 +562,14 @@ hipError_t launch_wgrad(const BwdParams& p, hipStream_t st)
         return cus * per_cu;
     });
     return launch_kernel(kKernelWgrad, wgrad_kernel<NT>, dim3(grid), dim3(kThreads), lds, st, p);
+}
+
+template <int NT>
+hipError_t launch_whole(const BwdParams& p, hipStream_t st)
+{
+    static DeviceGrid cache;
+    const int grid = cache.get([] { return resident_grid(wgrad_whole_kernel<NT>, kWholeLdsBytes); });
+    return launch_kernel(kKernelWgrad, wgrad_whole_kernel<NT>, dim3(grid), dim3(kThreads), kWholeLdsBytes, st, p);
 }
 
 }  // namespace
@@ -408,15 +645,22 @@ extern "C" lq_status lora_segmented_backward(const void* x, int64_t ldx, const v
     s1.ksplit = 1; s1.rstride = rstride_for(max_rank);
     s1.header = s1.err = reinterpret_cast<int*>(ws); s1.tickets = reinterpret_cast<int*>(ws) + 4;
     s1.ksplit_hint = 0; s1.kinds = kFinetuneOnly;
+    // whole segments' weight gradients behind the slab kernel: the operands lie in the g slices' region, which that kernel leaves free
+    const bool slabs = variant == LQ_VARIANT_SLAB || (variant == LQ_VARIANT_FUSED && slab_form(s1));
+    const int tiles = nt_for(max_rank);
+    const size_t frag = (frag_bytes(n_tokens, tiles) + 255) / 256 * 256;
+    const bool whole = want_w && slabs && 2 * frag <= h_slices_bytes(n_tokens, max_rank) && whole_segments_win(n_tokens, max_rank, d_in, d_out);
+    const SlabFrag operands = {reinterpret_cast<u16*>(ws + kWsHeaderBytes), reinterpret_cast<u16*>(ws + kWsHeaderBytes + frag), h_saved, tiles};
+    const SlabFrag* const leave = whole ? &operands : nullptr;
     // 2. dx += s g A on fine-tune rows: the forward's expand over d_in against A.  LQ_VARIANT_FUSED: both in a
     // single launch when its buffer descriptor can address the slices; else two launches with the same k split.
     // Whichever phase finishes g (the shrink without a split, the expand with one) also stores it to gsum.
     const bool one_launch = variant == LQ_VARIANT_FUSED && h_slices_bytes(n_tokens, max_rank) <= 0x7fffffffull;
     s1.coherent = one_launch; s1.hpart_bytes = one_launch ? (unsigned int)h_slices_bytes(n_tokens, max_rank) : 0;
     if (variant == LQ_VARIANT_SLAB) {
-        if (run_slab(s1, st, kKernelSlab) != hipSuccess) return LQ_ERR_HIP;
+        if (run_slab(s1, st, kKernelSlab, leave) != hipSuccess) return LQ_ERR_HIP;
     } else if (one_launch) {
-        if (run_shrink_expand(s1, LQ_VARIANT_FUSED, st) != hipSuccess) return LQ_ERR_HIP;
+        if (run_shrink_expand(s1, LQ_VARIANT_FUSED, st, leave) != hipSuccess) return LQ_ERR_HIP;
     } else {
         if (run_shrink_expand(s1, LQ_VARIANT_SHRINK_ONLY, st) != hipSuccess) return LQ_ERR_HIP;
         s1.ksplit_hint = s1.ksplit;
@@ -437,8 +681,14 @@ extern "C" lq_status lora_segmented_backward(const void* x, int64_t ldx, const v
         b.n_segments = n_segments; b.max_segments = max_segments;
         b.h_saved = h_saved; b.h_offsets = reinterpret_cast<const long long*>(h_offsets);
         b.g = gsum; b.rstride = s1.rstride;
+        b.frag_g = operands.g; b.frag_h = operands.h; b.frag_tiles = tiles;
         b.wpart = reinterpret_cast<float*>(ws + kWsHeaderBytes + h_slices_bytes(n_tokens, max_rank) + gsum_bytes(n_tokens, max_rank));
         b.err = reinterpret_cast<int*>(ws);
+        if (whole) {
+            const hipError_t e = tiles == 1 ? launch_whole<1>(b, st) : tiles == 2 ? launch_whole<2>(b, st)
+                               : tiles == 4 ? launch_whole<4>(b, st) : launch_whole<8>(b, st);
+            return e == hipSuccess ? LQ_OK : LQ_ERR_HIP;
+        }
         const hipError_t e = max_rank <= 16 ? launch_wgrad<1>(b, st) : max_rank <= 32 ? launch_wgrad<2>(b, st)
                            : max_rank <= 64 ? launch_wgrad<4>(b, st) : launch_wgrad<8>(b, st);
         if (e != hipSuccess) return LQ_ERR_HIP;

@@ -1374,7 +1374,6 @@ size_t h_slices_bytes(int n_tokens, int max_rank)
     return (size_t)ksplit_cap(n_tokens) * (size_t)n_tokens * (size_t)rstride_for(max_rank) * sizeof(float);
 }
 
-namespace {
 // The fused variant has two forms: the two phases with a device-wide barrier between them, and, for long batches, the row
 // slabs, whose units are up to 64 rows tall there: h stays on chip and each unit's matrices are re-read half as often as at
 // 32 rows.  Slabs, us by the barrier form and by the slabs (rank 64; mix: fine-tune, prefill and decode rows):
@@ -1394,13 +1393,12 @@ bool slab_form(const FwdParams& p)
     if (p.n_tokens > 49152 && p.d_in + 2ll * d_out < 3072) return false;
     return p.n_tokens >= (p.kinds == kAllKinds ? 2048 : p.d_in > 4096 ? 8192 : 4096);
 }
-}  // namespace
 
-hipError_t run_shrink_expand(FwdParams& p, int variant, hipStream_t st)
+hipError_t run_shrink_expand(FwdParams& p, int variant, hipStream_t st, const SlabFrag* frag)
 {
     const int nt = nt_for(p.max_rank);
     hipError_t e = hipSuccess;
-    if (variant == LQ_VARIANT_FUSED && slab_form(p)) return run_slab(p, st, kKernelFused);
+    if (variant == LQ_VARIANT_FUSED && slab_form(p)) return run_slab(p, st, kKernelFused, frag);
     if (variant == LQ_VARIANT_FUSED) {
         const int grid_f = nt == 1 ? fused_grid<1, 1, 2>() : nt == 2 ? fused_grid<2, 1, 2>()
                          : nt == 4 ? fused_grid<4, 2, 2>() : fused_grid<8, 4, 1>();

@@ -55,6 +55,12 @@ struct FwdParams : FwdCore {
     Proj more[kMaxProj - 1];  // the other linear layers of a grouped call
 };
 
+// The slab kernel of a backward call whose weight gradients take g and h as ready-made MFMA operands (see frag_at): where they
+// go, the saved h, and the 16-rank tiles per step.  (Its own block and instantiation: as members of FwdCore, with a test in the
+// forward's kernel, they cost a decode layer of 16 rows 2 us of 63 and the unified layer 5 of 351.)
+struct SlabFrag { u16* g; u16* h; const float* h_saved; int tiles; };
+struct FwdFrag : FwdCore { SlabFrag frag; };
+
 __device__ __forceinline__ int n_proj_of(const FwdCore&) { return 1; }
 __device__ __forceinline__ int n_proj_of(const FwdParams& p) { return p.n_proj; }
 __device__ __forceinline__ Proj proj_of(const FwdCore& p, int) { return p.proj0; }
@@ -138,8 +144,17 @@ inline int resident_grid(K kernel, size_t dyn_lds)
 
 inline int nt_for(int max_rank) { return max_rank <= 16 ? 1 : max_rank <= 32 ? 2 : max_rank <= 64 ? 4 : 8; }  // 16-rank tiles
 
+// The weight gradients' operands: h and g by 32-position steps of the segment order, [step][16-rank tile][high | low part][lane]
+// x 8 bf16: lane (rank % 16 + 16 (position % 32 / 8)) holds positions 8 (position % 32 / 8) .. + 7 of its rank.  Element of position
+// `pos` and rank j, high part (the low part follows 64 lanes further on):
+__device__ __forceinline__ long long frag_at(int pos, int j, int tiles)
+{
+    return (((long long)(pos >> 5) * tiles + (j >> 4)) * 2 * kWave + (((pos >> 3) & 3) * 16 + (j & 15))) * 8 + (pos & 7);
+}
+inline size_t frag_bytes(int n_tokens, int tiles) { return ((size_t)n_tokens + 31) / 32 * tiles * 2 * kWave * 16; }
+
 // The row-slab variant (LQ_VARIANT_SLAB): one launch, no partial-h buffer, no device-wide wait.
-hipError_t run_slab(const FwdParams& p, hipStream_t stream, int kernel_id);
+hipError_t run_slab(const FwdParams& p, hipStream_t stream, int kernel_id, const SlabFrag* frag = nullptr);
 
 constexpr int kAllKinds = 7;
 constexpr int kFinetuneOnly = 1 << LQ_SEG_FINETUNE;
@@ -173,9 +188,13 @@ int auto_variant(int max_rank, int n_tokens, bool all_rows, int n_proj, int in_c
 inline bool slab_reaches(int max_rank, int width) { return (long long)max_rank * width <= 1ll << 31; }
 size_t h_slices_bytes(int n_tokens, int max_rank);   // bytes of the partial-h region of a workspace
 
+// a call of the fused variant runs in row slabs
+bool slab_form(const FwdParams& p);
+
 // Fills p.ksplit and enqueues: variant LQ_VARIANT_SPLIT / _FUSED / _SHRINK_ONLY / _EXPAND_ONLY.
 // p.ksplit_hint > 0 forces that split (the expand half of a pair must use the shrink half's value).
-hipError_t run_shrink_expand(FwdParams& p, int variant, hipStream_t stream);
+// frag: passed on where the call runs in row slabs
+hipError_t run_shrink_expand(FwdParams& p, int variant, hipStream_t stream, const SlabFrag* frag = nullptr);
 
 // ---- device-wide barrier of a launch whose workgroups are all resident (grid = occupancy x compute units) ----
 // Data that crosses it must be written and read with device-scope accesses (the XCDs' L2 caches are not

@@ -430,6 +430,41 @@ __device__ __forceinline__ void slab_unit_rows(const PP& p, const Unit& u, const
     }
 }
 
+// a value as a bf16 high and low part (together ~16 mantissa bits).  (No low part of an infinity: the difference would be a NaN.)
+__device__ __forceinline__ void split_value(float v, unsigned int& hi, unsigned int& lo)
+{
+    hi = pack_bf16x2(v, 0.f) & 0xffffu;
+    lo = (hi & 0x7fffu) == 0x7f80u ? 0u : pack_bf16x2(v - bf16_lo(hi), 0.f) & 0xffffu;
+}
+__device__ __forceinline__ void store_frag(u16* frag, long long at, float v)
+{
+    unsigned int hi, lo;
+    split_value(v, hi, lo);
+    frag[at] = (u16)hi;
+    frag[at + kWave * 8] = (u16)lo;
+}
+
+// Backward: the unit's rows of the saved h as operands of the weight gradients, with their own scales where the call has
+// them.  One thread per (row, rank); run by the waves as they leave phase 2.
+template <class PP>
+__device__ __forceinline__ void slab_frag_h(const PP& p, const Unit& u, int rank, const float* lds_scale)
+{
+    const float* src = p.frag.h_saved + p.h_offsets[u.seg] + (long long)(u.pos - u.first) * rank;
+    const int n = u.len * rank;
+    for (int e0 = (int)threadIdx.x; e0 < n; e0 += 4 * kThreads) {
+        float v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = src[min(e0 + k * kThreads, n - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int e = e0 + k * kThreads;
+            if (e >= n) break;
+            const int i = small_div(e, rank), j = e - i * rank;
+            store_frag(p.frag.h, frag_at(u.pos + i, j, p.frag.tiles), p.token_scales ? v[k] * lds_scale[i] : v[k]);
+        }
+    }
+}
+
 // the adapters of the pass's projections; false (workgroup uniform, error bit set) if one of them is unusable
 template <int NP, class PP>
 __device__ __forceinline__ bool slab_adapters(const PP& p, const Unit& u0, const SegInfo& s0, int pi0, SegInfo (&s)[NP])

@@ -20,6 +20,8 @@ constexpr size_t kRowsOffset = kWorkOffset + kWaves * kWaveBytes;
 constexpr size_t kStashOffset = kRowsOffset + 2 * kSlabRows * sizeof(int);
 constexpr size_t kSlabLdsBytes = kStashOffset + kStashBytes;
 
+template <class PP> constexpr bool kFrag = std::is_same_v<PP, FwdFrag>;  // a backward call that leaves g and h as operands
+
 // =================================================================================================
 // one pass of a unit: NP projections (pi0 ..) through phase 1, the sum over the waves, and phase 2 (ZERO_X: see slab_shrink)
 // =================================================================================================
@@ -52,14 +54,15 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
     const bool save = u0.kd == LQ_SEG_FINETUNE && p.h_offsets && part == 0;
     slab_shrink_sum<NT, NP, MTM, ZERO_X>(p, u0, s, lds_row, work, [&](auto qc, int i, int j, float sum) {
         constexpr int q = decltype(qc)::value;
-        if (save) {
+        if (!kFrag<PP> && save) {
             float* h_out = proj_of(p, pi0 + q).h_out;
             if (h_out) h_out[p.h_offsets[u0.seg] + (long long)(u0.pos - u0.first + i) * rank + j] = sum;
         }
         const float scaled = sum * lds_scale[i];
-        const unsigned int hi = pack_bf16x2(scaled, 0.f) & 0xffffu;
-        // (no low part of an infinity: the difference would be a NaN)
-        const unsigned int lo = (hi & 0x7fffu) == 0x7f80u ? 0u : pack_bf16x2(scaled - bf16_lo(hi), 0.f) & 0xffffu;
+        unsigned int hi, lo;
+        split_value(scaled, hi, lo);
+        if constexpr (kFrag<PP>)
+            if (part == 0) store_frag(p.frag.g, frag_at(u0.pos + i, j, p.frag.tiles), p.token_scales ? scaled : sum);
         // fragment (projection q, row tile i / 16, k step j / 32): lane (j % 32 / 8) * 16 + i % 16 holds ranks 8 (j / 8) .. + 7
         const int slot = ((q * MTM + (i >> 4)) * KSTEPS + (j >> 5)) * 2;
         const int ln = ((j >> 3) & 3) * 16 + (i & 15);
@@ -82,14 +85,17 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
         else if (u0.len <= 48) slab_expand<NT, (MTM > 2 ? 3 : 2)>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
         else slab_expand<NT, (MTM > 2 ? 4 : 2)>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
     }
+    if constexpr (kFrag<PP>)
+        if (part == 0) slab_frag_h(p, u0, rank, lds_scale);
     __syncthreads();  // before the next pass or unit reuses the LDS
 }
 
-template <int NT, int MTM, bool GROUP, class PP>
+template <int NT, int MTM, class PP>
 __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegInfo& s0, int part, int parts, unsigned char* lds)
 {
     slab_unit_rows(p, u, s0, reinterpret_cast<int*>(lds + kRowsOffset));
     __syncthreads();
+    constexpr bool GROUP = std::is_same_v<PP, FwdParams>;
     const int n_proj = n_proj_of(p);
     if constexpr (NT >= 4 && !(GROUP && NT >= 8)) {
         // a launch with adapters of different ranks: every unit runs with as many 16-rank tiles as its own adapter needs.
@@ -114,13 +120,12 @@ __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegI
 }
 
 // NT: 16-rank tiles of the launch (ranks up to 16 NT); MTM: 16-row tiles of its tallest unit.
-template <int NT, int MTM, bool GROUP>
-__global__ __launch_bounds__(kThreads) void slab_kernel(KernelArg<GROUP> p)
+template <int NT, int MTM, class PP>
+__global__ __launch_bounds__(kThreads) void slab_kernel(PP p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     __shared__ int s_slot[2];
     auto sg = load_segs(p);
-    const int grid = (int)gridDim.x;
     const SlabPlan pl = slab_plan(p, sg, 16 * MTM);
     ClassScan cc = pl.cc;
     // Workgroups are dealt to the 8 XCDs in turn (workgroup i runs on XCD i % 8), and every XCD has its own L2.  The
@@ -146,44 +151,54 @@ __global__ __launch_bounds__(kThreads) void slab_kernel(KernelArg<GROUP> p)
         u.pi = 0;
         if (!slab_find(p, sg, cc, pl.per, chunk, u, s)) return;
         stash_tables(sg, cc, stash);
-        slab_unit<NT, MTM, GROUP>(p, u, s, part, parts, lds_raw);  // (has a workgroup barrier after its first step)
+        slab_unit<NT, MTM>(p, u, s, part, parts, lds_raw);  // (has a workgroup barrier after its first step)
         unstash_tables(sg, cc, stash);
     });
 }
 
 constexpr float kPartsFromB = 300000.f;  // elements of B (of all layers) from which a wide layer is cut into parts, see slab_plan
 
-template <int NT, int MTM, bool GROUP>
-hipError_t launch_slab(const FwdParams& p0, hipStream_t st, int kernel_id)
+template <int NT, int MTM, class PP>
+hipError_t launch_slab(PP p, const FwdParams& all, hipStream_t st, int kernel_id)
 {
     static DeviceGrid cache;
-    const int grid = cache.get([] { return resident_grid(slab_kernel<NT, MTM, GROUP>, kSlabLdsBytes); });
-    KernelArg<GROUP> p = p0;
-    float columns = (float)p0.proj0.d_out;
-    for (int k = 1; k < p0.n_proj; ++k) columns += (float)p0.more[k - 1].d_out;
+    const int grid = cache.get([] { return resident_grid(slab_kernel<NT, MTM, PP>, kSlabLdsBytes); });
+    float columns = (float)p.proj0.d_out;
+    for (int k = 1; k < p.n_proj; ++k) columns += (float)all.more[k - 1].d_out;
     const float b = (float)p.max_rank * columns, x_passes = NT >= 4 ? (float)p.n_proj : 1.f;
     p.slab_parts = b >= kPartsFromB ? 0.3f * b * (float)grid / ((float)p.d_in * x_passes) : 0.f;
     p.slab_rows_per_rank = 0.8f * ((float)p.d_in * (float)p.n_proj + columns) / ((float)p.d_in + 2.f * columns);
-    return launch_kernel(kernel_id, slab_kernel<NT, MTM, GROUP>, dim3(grid), dim3(kThreads), kSlabLdsBytes, st, p);
+    return launch_kernel(kernel_id, slab_kernel<NT, MTM, PP>, dim3(grid), dim3(kThreads), kSlabLdsBytes, st, p);
+}
+
+// (up to 4096 rows of a batch with few enough segments fit one round of 32-row units, and the kernel of two row tiles starts
+// sooner: 256 decode rows of rank 16 15.5 us a pass instead of 16.0, 2048 rows of rank 64 26.5 us instead of 26.9)
+template <class PP>
+hipError_t launch_single(const PP& p, const FwdParams& all, hipStream_t st, int kernel_id)
+{
+    const int nt = nt_for(p.max_rank);
+    const bool wide = (float)p.max_rank * (float)p.proj0.d_out >= kPartsFromB;
+    if ((p.n_tokens <= 4096 && !wide) || nt == 8)
+        return nt == 1 ? launch_slab<1, 2>(p, all, st, kernel_id) : nt == 2 ? launch_slab<2, 2>(p, all, st, kernel_id)
+             : nt == 4 ? launch_slab<4, 2>(p, all, st, kernel_id) : launch_slab<8, 2>(p, all, st, kernel_id);
+    return nt == 1   ? launch_slab<1, 4>(p, all, st, kernel_id)
+           : nt == 2 ? launch_slab<2, 4>(p, all, st, kernel_id)
+                     : launch_slab<4, 4>(p, all, st, kernel_id);
 }
 
 }  // namespace
 
-hipError_t run_slab(const FwdParams& p, hipStream_t st, int kernel_id)
+hipError_t run_slab(const FwdParams& p, hipStream_t st, int kernel_id, const SlabFrag* frag)
 {
     const int nt = nt_for(p.max_rank);
     if (p.n_proj > 1)
-        return nt == 1 ? launch_slab<1, 2, true>(p, st, kernel_id) : nt == 2 ? launch_slab<2, 2, true>(p, st, kernel_id)
-             : nt == 4 ? launch_slab<4, 2, true>(p, st, kernel_id) : launch_slab<8, 2, true>(p, st, kernel_id);
-    // (up to 4096 rows of a batch with few enough segments fit one round of 32-row units, and the kernel of two row tiles starts
-    // sooner: 256 decode rows of rank 16 15.5 us a pass instead of 16.0, 2048 rows of rank 64 26.5 us instead of 26.9)
-    const bool wide = (float)p.max_rank * (float)p.proj0.d_out >= kPartsFromB;
-    if ((p.n_tokens <= 4096 && !wide) || nt == 8)
-        return nt == 1 ? launch_slab<1, 2, false>(p, st, kernel_id) : nt == 2 ? launch_slab<2, 2, false>(p, st, kernel_id)
-             : nt == 4 ? launch_slab<4, 2, false>(p, st, kernel_id) : launch_slab<8, 2, false>(p, st, kernel_id);
-    return nt == 1   ? launch_slab<1, 4, false>(p, st, kernel_id)
-           : nt == 2 ? launch_slab<2, 4, false>(p, st, kernel_id)
-                     : launch_slab<4, 4, false>(p, st, kernel_id);
+        return nt == 1 ? launch_slab<1, 2>(p, p, st, kernel_id) : nt == 2 ? launch_slab<2, 2>(p, p, st, kernel_id)
+             : nt == 4 ? launch_slab<4, 2>(p, p, st, kernel_id) : launch_slab<8, 2>(p, p, st, kernel_id);
+    if (!frag) return launch_single(static_cast<const FwdCore&>(p), p, st, kernel_id);
+    FwdFrag q;
+    static_cast<FwdCore&>(q) = p;
+    q.frag = *frag;
+    return launch_single(q, p, st, kernel_id);
 }
 
 }  // namespace lq

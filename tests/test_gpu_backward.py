@@ -248,3 +248,53 @@ def test_automatic_choice_of_the_backward(max_rank, T, d_out, d_in, kernel):
     assert ran == ["forward_" + kernel]
     _, want = run({"slab": lq.LQ_VARIANT_SLAB, "fused": lq.LQ_VARIANT_FUSED}[kernel])
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("rank,lens,d_in,d_out", [
+    ((8, 16, 5), (1, 31, 32, 33, 64, 260, 7), 72, 200), ((32, 17), (300, 1, 95, 257, 96), 520, 264),
+    ((64, 40, 33), (100, 65, 500), 136, 72), ((128, 65, 96, 16), (40, 290, 31, 33), 264, 136)])
+@pytest.mark.parametrize("scaled", [False, True])
+def test_whole_segment_weight_gradients(rank, lens, d_in, d_out, scaled):
+    """Fine-tune segments that begin and end anywhere in the 32-position steps, decode rows between them in the batch: the
+    weight gradients of whole segments, against 64 bits.  What the workspace held before (NaN patterns) and an infinite row
+    of one segment must not reach another's gradients."""
+    gen = torch.Generator(device="cuda").manual_seed(sum(lens))
+    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    n = len(lens)
+    ranks = [rank[a % len(rank)] for a in range(n)]
+    ta = torch.repeat_interleave(torch.arange(n), torch.tensor(lens))
+    T = 2 * len(ta)
+    ta = torch.cat([ta, ta])[torch.randperm(T, generator=torch.Generator().manual_seed(1))].to(torch.int32)
+    first = torch.zeros(T, dtype=torch.bool)                    # the first len rows of an adapter are fine-tune rows
+    for a in range(n):
+        first[torch.nonzero(ta == a).flatten()[: lens[a]]] = True
+    tk = torch.where(first, 0, 2).to(torch.uint8)
+    A, B = [new(r, d_in, 0.05) for r in ranks], [new(r, d_out, 0.05) for r in ranks]
+    scales = [0.5 + 0.25 * a for a in range(n)]
+    ad = lq.AdapterTable.from_tensors(A, B, scales)
+    x, dy, dx = new(T, d_in, 1.0), new(T, d_out, 1.0), new(T, d_in, 1.0)
+    bad = int(torch.nonzero((ta == 0) & first).flatten()[0])    # adapter 0: its gradients become infinite or NaN, nobody else's
+    x[bad], dy[bad] = float("inf"), float("inf")
+    ts = torch.rand(T, device="cuda", generator=gen).add_(0.5) if scaled else None
+    seg = lq.SegmentTables.empty(T, n)
+    lq.lora_build_segments(ta.cuda(), tk.cuda(), ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, n)))
+    h = [x[((ta == a) & first).cuda()].double() @ A[a].double().T for a in range(n)]
+    h_saved = torch.cat([v.flatten() for v in h]).float()
+    ws = lq.workspace(lq.lora_backward_workspace_bytes(T, n, max(ranks), d_in, d_out))
+    ws[4096 // 8:] = -1
+    dA = [torch.ones(r, d_in, device="cuda") for r in ranks]
+    dB = [torch.ones(r, d_out, device="cuda") for r in ranks]
+    table = lambda g: torch.tensor([t.data_ptr() for t in g], dtype=torch.int64, device="cuda")
+    lq.lora_profile_enable(True)
+    lq.lora_segmented_backward(x, dy, dx, ad, table(dA), table(dB), seg, h_saved, ws, lq.LQ_VARIANT_SLAB, token_scales=ts)
+    ran = [name for name, (_, k) in lq.lora_profile_read().items() if k]
+    lq.lora_profile_enable(False)
+    lq.raise_on_device_error(ws)
+    assert sorted(ran) == ["forward_slab", "wgrad"]             # no reduction
+    for a in range(1, n):
+        rows = ((ta == a) & first).cuda()
+        s = ts[rows, None].double() if scaled else scales[a]
+        g = s * (dy[rows].double() @ B[a].double().T)
+        for got, want in ((dA[a], 1 + g.T @ x[rows].double()), (dB[a], 1 + (s * h[a]).T @ dy[rows].double())):
+            assert bool(torch.isfinite(got).all())
+            assert rel_frobenius(got.cpu().numpy(), want.cpu().numpy()) <= WGRAD_REL_FROBENIUS, a
