@@ -18,6 +18,24 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 
+// 16-byte accesses of data that a launch touches once, y (dx) above all: the non-temporal policy keeps it from displacing what
+// is used again (x, the adapters, dy for the weight gradients) in the last-level cache, and streams faster: 256 workgroups
+// that read 8 MB each, 6.85 TB/s against 5.95.
+template <bool STREAM>
+__device__ __forceinline__ u32x4 load_once(const void* p)
+{
+    const u32x4* at = reinterpret_cast<const u32x4*>(p);
+    if constexpr (STREAM) return __builtin_nontemporal_load(at);
+    else return *at;
+}
+template <bool STREAM>
+__device__ __forceinline__ void store_once(void* p, const u32x4& v)
+{
+    u32x4* at = reinterpret_cast<u32x4*>(p);
+    if constexpr (STREAM) __builtin_nontemporal_store(v, at);
+    else *at = v;
+}
+
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 
 // ---- bf16 <-> fp32 ---------------------------------------------------------------------------

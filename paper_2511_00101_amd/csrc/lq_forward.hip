@@ -576,7 +576,7 @@ __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, con
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             row_f[j] = lds_row[min(8 * j + (lane >> 3), C::CT - 1)];
-            y_f[j] = *reinterpret_cast<const u32x4*>(pj.y + (long long)(row_f[j] >= 0 ? row_f[j] : safe) * pj.ldy + n_ld);
+            y_f[j] = load_once<true>(pj.y + (long long)(row_f[j] >= 0 ? row_f[j] : safe) * pj.ldy + n_ld);
         }
     }
 #pragma unroll
@@ -611,7 +611,8 @@ __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, con
         // The products come out of the MFMA in that other layout, so every 16-row tile of them makes a round
         // trip through a 4 KB LDS slab of the wave (in the B block's space, free while y streams); the
         // 16-byte chunks of a slab row are XOR-swizzled with the row number against bank conflicts.
-        // Loads are unconditional (dead rows and columns read a live address); only the stores are masked.
+        // Loads are unconditional (dead rows and columns read a live address); only the stores are masked.  y is touched once:
+        // non-temporal (gate + up of the layer stack 163 -> 159 us).
         float* slab = reinterpret_cast<float*>(lds_b) + w * (16 * 64);
         const int r8 = lane >> 3, piece = lane & 7;
         const int n_c = n_wave + 8 * piece, n_ld = min(n_c, pj.d_out - 8);
@@ -621,7 +622,7 @@ __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, con
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 row_n[j] = lds_row[min(step * 32 + 8 * j + r8, C::CT - 1)];
-                y_n[j] = *reinterpret_cast<const u32x4*>(pj.y + (long long)(row_n[j] >= 0 ? row_n[j] : safe_row) * pj.ldy + n_ld);
+                y_n[j] = load_once<true>(pj.y + (long long)(row_n[j] >= 0 ? row_n[j] : safe_row) * pj.ldy + n_ld);
             }
         };
 #pragma unroll
@@ -677,7 +678,7 @@ __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, con
                         o.y = pack_bf16x2(yf[2] + d0[2], yf[3] + d0[3]);
                         o.z = pack_bf16x2(yf[4] + d1[0], yf[5] + d1[1]);
                         o.w = pack_bf16x2(yf[6] + d1[2], yf[7] + d1[3]);
-                        *reinterpret_cast<u32x4*>(pj.y + (long long)row[j] * pj.ldy + n_c) = o;
+                        store_once<true>(pj.y + (long long)row[j] * pj.ldy + n_c, o);
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

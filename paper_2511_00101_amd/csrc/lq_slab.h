@@ -206,7 +206,7 @@ __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegI
 // columns of a row; every 16-row tile of products makes a round trip through the wave's 4 KB slab to reach the
 // row-wise layout y is accessed in.
 // =================================================================================================
-template <int NT, int MT, class PP>
+template <int NT, int MT, bool STREAM, class PP>  // STREAM: y is large, see load_once
 __device__ __forceinline__ void slab_expand(const PP&, const Unit& u, const SegInfo& s, const Proj& pj,
                                             const int* lds_row, const u32x4* hf, u16* bs, float* ds, int blk_begin,
                                             int blk_end)
@@ -245,7 +245,7 @@ __device__ __forceinline__ void slab_expand(const PP&, const Unit& u, const SegI
     auto y_load = [&](int j, u32x4 (&v)[NJ]) {
         const int n_ld = min(n_of(j) + 8 * piece, pj.d_out - 8);
 #pragma unroll
-        for (int i = 0; i < NJ; ++i) v[i] = *reinterpret_cast<const u32x4*>(yrow[i] + n_ld);
+        for (int i = 0; i < NJ; ++i) v[i] = load_once<STREAM>(yrow[i] + n_ld);
     };
     auto b_load = [&](int j, auto chunk, u32x4 (&v)[NL]) {
         constexpr int N = decltype(chunk)::value;
@@ -335,7 +335,7 @@ __device__ __forceinline__ void slab_expand(const PP&, const Unit& u, const SegI
                     o.y = pack_bf16x2(yf[2] + d0[2], yf[3] + d0[3]);
                     o.z = pack_bf16x2(yf[4] + d1[0], yf[5] + d1[1]);
                     o.w = pack_bf16x2(yf[6] + d1[2], yf[7] + d1[3]);
-                    *reinterpret_cast<u32x4*>(pj.y + (long long)row[i] * pj.ldy + n_c) = o;
+                    store_once<STREAM>(pj.y + (long long)row[i] * pj.ldy + n_c, o);
                 }
             }
             wave_sync();  // the slab is rewritten by the next tile

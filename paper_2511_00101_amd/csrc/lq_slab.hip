@@ -30,6 +30,10 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
                                           unsigned char* lds)
 {
     constexpr int KSTEPS = (NT + 1) / 2;
+    // the non-temporal policy for y in the kernels of long batches and of groups (a short batch's y is small and soon used again):
+    // 5632 rows of rank 32 4096 -> 4096 40 -> 35 us, 14336 -> 4096 71 -> 65, q+k+v 63 -> 58; 8192 Zipf rows, 4096 -> 11008 110 -> 99
+    // (The same for x gains as much alone, nothing on top, and loses what the weight gradients find of dy in the cache: 41 -> 49 us.)
+    constexpr bool STREAM = MTM > 2 || std::is_same_v<PP, FwdParams>;
     static_assert((size_t)NP * MTM * KSTEPS * 2 * kWave * 16 <= kHfragBytes, "the pass's h fragments fit");
     u32x4* hfrag = reinterpret_cast<u32x4*>(lds);
     unsigned char* work = lds + kWorkOffset;
@@ -80,10 +84,10 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
         const int nblk = (pj.d_out + kKB - 1) / kKB;
         const int begin = small_div(part * nblk, parts), end = small_div((part + 1) * nblk, parts);
         const u32x4* hf = hfrag + q * MTM * KSTEPS * 2 * kWave;
-        if (u0.len <= 16) slab_expand<NT, 1>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);  // workgroup uniform
-        else if (MTM <= 2 || u0.len <= 32) slab_expand<NT, 2>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
-        else if (u0.len <= 48) slab_expand<NT, (MTM > 2 ? 3 : 2)>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
-        else slab_expand<NT, (MTM > 2 ? 4 : 2)>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
+        if (u0.len <= 16) slab_expand<NT, 1, STREAM>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);  // workgroup uniform
+        else if (MTM <= 2 || u0.len <= 32) slab_expand<NT, 2, STREAM>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
+        else if (u0.len <= 48) slab_expand<NT, (MTM > 2 ? 3 : 2), STREAM>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
+        else slab_expand<NT, (MTM > 2 ? 4 : 2), STREAM>(p, u0, s[q], pj, lds_row, hf, bs, ds, begin, end);
     }
     if constexpr (kFrag<PP>)
         if (part == 0) slab_frag_h(p, u0, rank, lds_scale);
