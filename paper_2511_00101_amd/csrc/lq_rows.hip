@@ -108,8 +108,8 @@ __global__ __launch_bounds__(kRowThreads) void move_rows_kernel(u16* src, long l
         u16* a = src + (long long)row * ld;
         u16* b = parts + (long long)i * d;
         for (int k = (int)threadIdx.x * 8; k < d; k += kRowThreads * 8) {
-            if (SPLIT) *reinterpret_cast<u32x4*>(b + k) = *reinterpret_cast<const u32x4*>(a + k);
-            else *reinterpret_cast<u32x4*>(a + k) = *reinterpret_cast<const u32x4*>(b + k);
+            if (SPLIT) *reinterpret_cast<u32x4*>(b + k) = load_once<true>(a + k);
+            else store_once<true>(a + k, *reinterpret_cast<const u32x4*>(b + k));
         }
     }
 }
