@@ -30,7 +30,7 @@
 namespace lq {
 namespace {
 
-constexpr int kWgRows = 512;    // token rows per weight-gradient unit
+constexpr int kWgRows = 512;    // token rows per weight-gradient unit (wide layers of long batches: twice as many)
 constexpr int kWgCols = 256;    // columns per unit (8 waves x 32)
 constexpr int kWgTiles = kWgCols / (8 * 16);  // 16-column MFMA tiles per wave
 
@@ -53,18 +53,19 @@ struct BwdParams {
     int rstride;
     const u16* frag_g; const u16* frag_h;  // g and h as MFMA operands (see frag_at); frag_tiles 16-rank tiles per step
     int frag_tiles;
-    float* wpart;        // [chunk of a segment with more than 512 rows][rstride][d_out + d_in] partial weight gradients
+    int wg_rows;         // token rows per weight-gradient unit (for the reduction; the units' kernel knows them)
+    float* wpart;        // [chunk of a segment with more than wg_rows rows][rstride][d_out + d_in] partial weight gradients
     int* err;
 };
 
-template <int NT>
+template <int NT, int ROWS = kWgRows>
 struct WgCfg {
     static constexpr int YPITCH = kWgCols + 8;                 // u16 elements per staged activation row
     static constexpr int HPITCH = 16 * NT + 8;                 // u16 elements per staged row of h / g (high or low parts)
     static constexpr size_t Y_BYTES = (size_t)kStepRows * YPITCH * sizeof(u16);
     static constexpr size_t H_BYTES = ((size_t)2 * kStepRows * HPITCH * sizeof(u16) + 15) / 16 * 16;  // high, then low
     static constexpr size_t BUF_BYTES = Y_BYTES + H_BYTES;
-    static constexpr size_t LDS_BYTES = 2 * BUF_BYTES + kWgRows * sizeof(int);
+    static constexpr size_t LDS_BYTES = 2 * BUF_BYTES + ROWS * sizeof(int);
 };
 
 // f(integral_constant<int, 0>), f(integral_constant<int, 1>), ...: a loop over register slots that have to be
@@ -80,11 +81,11 @@ __device__ __forceinline__ void for_each_slot(std::integer_sequence<int, Js...>,
 // of a 32-row step and receives D[rank 4 kg + v][col c].
 // chunk_id < 0: the unit covers its whole segment and accumulates into dA / dB (times scale); else it stores its
 // partial to slot chunk_id of wpart
-template <int NT>
+template <int NT, int ROWS>
 __device__ __forceinline__ void wgrad_unit(const BwdParams& p, const Unit& u, int rank, float scale, int chunk_id, bool for_b,
                                            int col_block, unsigned char* lds)
 {
-    using C = WgCfg<NT>;
+    using C = WgCfg<NT, ROWS>;
     constexpr int YQ = kWgCols / 128;  // 16-byte pieces of a staged activation row per thread
     const int lane = lane_id(), w = uniform((int)threadIdx.x / kWave), c = lane & 15, kg = lane >> 4;
     const u16* Y = for_b ? p.dy : p.x;
@@ -94,7 +95,7 @@ __device__ __forceinline__ void wgrad_unit(const BwdParams& p, const Unit& u, in
     int* lds_row = reinterpret_cast<int*>(lds + 2 * C::BUF_BYTES);
 
     __syncthreads();  // the previous unit's LDS reads are done
-    for (int i = (int)threadIdx.x; i < kWgRows; i += kThreads) lds_row[i] = i < u.len ? row_of(p, u.pos + i) : -1;
+    for (int i = (int)threadIdx.x; i < ROWS; i += kThreads) lds_row[i] = i < u.len ? row_of(p, u.pos + i) : -1;
     __syncthreads();
     const int safe_row = max(lds_row[0], 0);
 
@@ -109,7 +110,7 @@ __device__ __forceinline__ void wgrad_unit(const BwdParams& p, const Unit& u, in
     // outside the unit is zeroed when it is stored to LDS
     auto stage_load = [&](int step, u32x4 (&y)[YQ], float (&h)[NT + 1]) {
         const int i = step * kStepRows + y_row;
-        const int row = lds_row[min(i, kWgRows - 1)];
+        const int row = lds_row[min(i, ROWS - 1)];
         const u16* yrow = Y + (long long)(row >= 0 ? row : safe_row) * ldy;
 #pragma unroll
         for (int q = 0; q < YQ; ++q) y[q] = *reinterpret_cast<const u32x4*>(yrow + min(n0 + (y_piece + 16 * q) * 8, d - 8));
@@ -122,7 +123,7 @@ __device__ __forceinline__ void wgrad_unit(const BwdParams& p, const Unit& u, in
         u16* ly = reinterpret_cast<u16*>(lds + buf * C::BUF_BYTES);
         u16* lh = reinterpret_cast<u16*>(lds + buf * C::BUF_BYTES + C::Y_BYTES);
         const int i = step * kStepRows + y_row;
-        const bool row_live = i < u.len && lds_row[min(i, kWgRows - 1)] >= 0;
+        const bool row_live = i < u.len && lds_row[min(i, ROWS - 1)] >= 0;
 #pragma unroll
         for (int q = 0; q < YQ; ++q) {
             const bool live = row_live && n0 + (y_piece + 16 * q) * 8 < d;
@@ -427,25 +428,25 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_whole_kernel(BwdParams p)
 // overlap the other's barriers)
 // the fine-tune segments with more than 512 rows are cut into chunks (partials, then the reduction); the shorter
 // ones are one unit per column block
-__device__ __forceinline__ LenClass cut_class() { return LenClass{kWgRows + 1, kBig, 1 << LQ_SEG_FINETUNE}; }
-__device__ __forceinline__ LenClass whole_class() { return LenClass{1, kWgRows + 1, 1 << LQ_SEG_FINETUNE}; }
+__device__ __forceinline__ LenClass cut_class(int rows) { return LenClass{rows + 1, kBig, 1 << LQ_SEG_FINETUNE}; }
+__device__ __forceinline__ LenClass whole_class(int rows) { return LenClass{1, rows + 1, 1 << LQ_SEG_FINETUNE}; }
 
-template <int NT>
+template <int NT, int ROWS>
 __global__ __launch_bounds__(kThreads, NT <= 2 ? 4 : 2) void wgrad_kernel(BwdParams p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     int n_seg;
     const SegCache c0 = load_seg_cache(p, n_seg);
-    const LenClass cut = cut_class(), whole = whole_class();
+    const LenClass cut = cut_class(ROWS), whole = whole_class(ROWS);
     const int blocks_b = (p.d_out + kWgCols - 1) / kWgCols, blocks_a = (p.d_in + kWgCols - 1) / kWgCols;
     const int per_chunk = blocks_b + blocks_a;
-    const int n_cut = count_chunks(p, n_seg, c0, kWgRows, cut) * per_chunk;  // the (larger) chunks first
-    const int n_units = n_cut + count_chunks(p, n_seg, c0, kWgRows, whole) * per_chunk;
+    const int n_cut = count_chunks(p, n_seg, c0, ROWS, cut) * per_chunk;  // the (larger) chunks first
+    const int n_units = n_cut + count_chunks(p, n_seg, c0, ROWS, whole) * per_chunk;
     for (int id = (int)blockIdx.x; id < n_units; id += (int)gridDim.x) {
         Unit u;
         const bool is_cut = id < n_cut;
         const int chunk_id = small_div(is_cut ? id : id - n_cut, per_chunk), cb = (is_cut ? id : id - n_cut) - chunk_id * per_chunk;
-        if (!(is_cut ? find_chunk(p, n_seg, c0, chunk_id, kWgRows, cut, u) : find_chunk(p, n_seg, c0, chunk_id, kWgRows, whole, u)))
+        if (!(is_cut ? find_chunk(p, n_seg, c0, chunk_id, ROWS, cut, u) : find_chunk(p, n_seg, c0, chunk_id, ROWS, whole, u)))
             continue;
         if (u.ad < 0 || u.ad >= p.n_adapters) continue;  // flagged by the forward kernels already
         const int rank = p.ranks[u.ad];
@@ -454,7 +455,7 @@ __global__ __launch_bounds__(kThreads, NT <= 2 ? 4 : 2) void wgrad_kernel(BwdPar
         if (for_b ? (p.dB_ptrs == nullptr || p.dB_ptrs[u.ad] == nullptr) : (p.dA_ptrs == nullptr || p.dA_ptrs[u.ad] == nullptr))
             continue;
         const float scale = p.token_scales ? 1.f : p.scales[u.ad];  // (per-token scales were applied row by row)
-        wgrad_unit<NT>(p, u, rank, scale, is_cut ? chunk_id : -1, for_b, for_b ? cb : cb - blocks_b, lds_raw);
+        wgrad_unit<NT, ROWS>(p, u, rank, scale, is_cut ? chunk_id : -1, for_b, for_b ? cb : cb - blocks_b, lds_raw);
     }
 }
 
@@ -467,19 +468,19 @@ __global__ __launch_bounds__(kThreads) void wreduce_kernel(BwdParams p)
 {
     int n_seg;
     const SegCache c0 = load_seg_cache(p, n_seg);
-    const LenClass cut = cut_class();
+    const LenClass cut = cut_class(p.wg_rows);
     const int dsum = p.d_out + p.d_in;
     const int col_blocks = (dsum + kThreads - 1) / kThreads;
     const int rank_groups = (p.max_rank + kRedRanks - 1) / kRedRanks;
     const int per_chunk = col_blocks * rank_groups;
-    const int n_units = count_chunks(p, n_seg, c0, kWgRows, cut) * per_chunk;
+    const int n_units = count_chunks(p, n_seg, c0, p.wg_rows, cut) * per_chunk;
     for (int id = (int)blockIdx.x; id < n_units; id += (int)gridDim.x) {
         Unit u;
         const int chunk_id = small_div(id, per_chunk), sub = id - chunk_id * per_chunk;
-        if (!find_chunk(p, n_seg, c0, chunk_id, kWgRows, cut, u)) continue;
+        if (!find_chunk(p, n_seg, c0, chunk_id, p.wg_rows, cut, u)) continue;
         if (u.pos != u.first) continue;  // only the segment's first chunk adds up the segment
         if (u.ad < 0 || u.ad >= p.n_adapters) continue;
-        const int n_chunks = (u.seg_len + kWgRows - 1) / kWgRows;
+        const int n_chunks = (u.seg_len + p.wg_rows - 1) / p.wg_rows;
         const int j0 = (sub / col_blocks) * kRedRanks;
         const int col = (sub % col_blocks) * kThreads + (int)threadIdx.x;
         if (col >= dsum) continue;
@@ -545,23 +546,23 @@ size_t wpart_bytes(int n_tokens, int max_rank, int d_in, int d_out)
     return chunks * (size_t)rstride_for(max_rank) * ((size_t)d_in + d_out) * sizeof(float);
 }
 
-template <int NT>
+template <int NT, int ROWS = kWgRows>
 hipError_t launch_wgrad(const BwdParams& p, hipStream_t st)
 {
     static DeviceGrid cache;
-    constexpr size_t lds = WgCfg<NT>::LDS_BYTES;
+    constexpr size_t lds = WgCfg<NT, ROWS>::LDS_BYTES;
     const int grid = cache.get([] {
         int dev = 0, cus = 0, per_cu = 0;
         if (lds > 48 * 1024)
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_kernel<NT>),
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_kernel<NT, ROWS>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         (void)hipGetDevice(&dev);
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, wgrad_kernel<NT>, kThreads, lds) != hipSuccess || per_cu <= 0)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, wgrad_kernel<NT, ROWS>, kThreads, lds) != hipSuccess || per_cu <= 0)
             per_cu = 1;
         return cus * per_cu;
     });
-    return launch_kernel(kKernelWgrad, wgrad_kernel<NT>, dim3(grid), dim3(kThreads), lds, st, p);
+    return launch_kernel(kKernelWgrad, wgrad_kernel<NT, ROWS>, dim3(grid), dim3(kThreads), lds, st, p);
 }
 
 template <int NT>
@@ -689,11 +690,17 @@ extern "C" lq_status lora_segmented_backward(const void* x, int64_t ldx, const v
                                : tiles == 4 ? launch_whole<4>(b, st) : launch_whole<8>(b, st);
             return e == hipSuccess ? LQ_OK : LQ_ERR_HIP;
         }
-        const hipError_t e = max_rank <= 16 ? launch_wgrad<1>(b, st) : max_rank <= 32 ? launch_wgrad<2>(b, st)
+        // 1024-row units where 512-row ones are well above one round of the grid (two workgroups per compute unit up to rank 32): half
+        // the partials, and no second round for a few units.  2048 + 2048 rows of rank 32, us of the units and of the reduction with
+        // 512 and 1024 rows: 4096 -> 14336 40.2 + 9.6 and 39.9 + 7.6, 14336 -> 4096 42.9 + 9.6 and 43.1 + 7.7; below, the machine is not full: 4096 -> 4096 17.6 + 5.1 and 26.5 + 4.6.
+        const bool tall = max_rank <= 32 && (n_tokens + kWgRows - 1ll) / kWgRows * (((long long)d_in + d_out) / kWgCols) > 600;
+        b.wg_rows = tall ? 2 * kWgRows : kWgRows;
+        const hipError_t e = tall ? (max_rank <= 16 ? launch_wgrad<1, 2 * kWgRows>(b, st) : launch_wgrad<2, 2 * kWgRows>(b, st))
+                           : max_rank <= 16 ? launch_wgrad<1>(b, st) : max_rank <= 32 ? launch_wgrad<2>(b, st)
                            : max_rank <= 64 ? launch_wgrad<4>(b, st) : launch_wgrad<8>(b, st);
         if (e != hipSuccess) return LQ_ERR_HIP;
-        // (no segment of a batch of up to 512 tokens is cut into chunks: nothing to reduce)
-        if (n_tokens > kWgRows && launch_kernel(kKernelWreduce, wreduce_kernel, dim3(512), dim3(kThreads), 0, st, b) != hipSuccess)
+        // (no segment of a batch of up to wg_rows tokens is cut into chunks: nothing to reduce)
+        if (n_tokens > b.wg_rows && launch_kernel(kKernelWreduce, wreduce_kernel, dim3(512), dim3(kThreads), 0, st, b) != hipSuccess)
             return LQ_ERR_HIP;
     }
     return LQ_OK;

@@ -298,3 +298,30 @@ def test_whole_segment_weight_gradients(rank, lens, d_in, d_out, scaled):
         for got, want in ((dA[a], 1 + g.T @ x[rows].double()), (dB[a], 1 + (s * h[a]).T @ dy[rows].double())):
             assert bool(torch.isfinite(got).all())
             assert rel_frobenius(got.cpu().numpy(), want.cpu().numpy()) <= WGRAD_REL_FROBENIUS, a
+
+
+@pytest.mark.parametrize("rank", [16, 32])
+def test_weight_gradients_in_units_of_1024_rows(rank):
+    """Wide layers of long batches: segments of up to 1024 rows are one unit, longer ones are cut and reduced; against 64 bits."""
+    gen = torch.Generator(device="cuda").manual_seed(rank)
+    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    lens, d_in, d_out = (1024, 1025, 2049, 33), 2056, 16400
+    T, n = sum(lens), len(lens)
+    A, B = [new(rank, d_in, 0.05) for _ in lens], [new(rank, d_out, 0.05) for _ in lens]
+    ad = lq.AdapterTable.from_tensors(A, B, [0.5, 1.0, 2.0, 1.5])
+    ta = torch.repeat_interleave(torch.arange(n), torch.tensor(lens))[torch.randperm(T, generator=torch.Generator().manual_seed(2))].to(torch.int32)
+    seg = lq.SegmentTables.empty(T, n)
+    lq.lora_build_segments(ta.cuda(), torch.zeros(T, dtype=torch.uint8, device="cuda"), ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, n)))
+    x, dy, dx = new(T, d_in, 1.0), new(T, d_out, 1.0), new(T, d_in, 1.0)
+    h = [x[(ta == a).cuda()].double() @ A[a].double().T for a in range(n)]
+    ws = lq.workspace(lq.lora_backward_workspace_bytes(T, n, rank, d_in, d_out))
+    dA, dB = [torch.zeros(rank, d_in, device="cuda") for _ in lens], [torch.zeros(rank, d_out, device="cuda") for _ in lens]
+    table = lambda g: torch.tensor([t.data_ptr() for t in g], dtype=torch.int64, device="cuda")
+    lq.lora_segmented_backward(x, dy, dx, ad, table(dA), table(dB), seg, torch.cat([v.flatten() for v in h]).float(), ws, lq.LQ_VARIANT_AUTO)
+    torch.cuda.synchronize()
+    lq.raise_on_device_error(ws)
+    for a, s in enumerate([0.5, 1.0, 2.0, 1.5]):
+        rows = (ta == a).cuda()
+        g = s * (dy[rows].double() @ B[a].double().T)
+        for got, want in ((dA[a], g.T @ x[rows].double()), (dB[a], (s * h[a]).T @ dy[rows].double())):
+            assert rel_frobenius(got.cpu().numpy(), want.cpu().numpy()) <= WGRAD_REL_FROBENIUS, a
