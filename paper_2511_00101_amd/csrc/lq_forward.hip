@@ -612,7 +612,8 @@ __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, con
         // trip through a 4 KB LDS slab of the wave (in the B block's space, free while y streams); the
         // 16-byte chunks of a slab row are XOR-swizzled with the row number against bank conflicts.
         // Loads are unconditional (dead rows and columns read a live address); only the stores are masked.  y is touched once:
-        // non-temporal (gate + up of the layer stack 163 -> 159 us).
+        // non-temporal.  In the layer stack gate + up alone takes longer so (147 -> 163 us), but the launches behind it no longer pay
+        // for what it left to be written back (o, down and q+k+v 63 -> 56 us on average): a step 10.88 -> 10.69 ms.
         float* slab = reinterpret_cast<float*>(lds_b) + w * (16 * 64);
         const int r8 = lane >> 3, piece = lane & 7;
         const int n_c = n_wave + 8 * piece, n_ld = min(n_c, pj.d_out - 8);
