@@ -331,7 +331,8 @@ lq_status lora_concat_rows(const void* parts, int32_t d, const int32_t* perm, in
  *   lora_profile_enable(on)  on != 0 starts recording, 0 stops; both discard what was recorded.
  *   lora_profile_read(total_us, launches, n_kernels)  host arrays of n_kernels >= LQ_KERNEL_IDS entries,
  *       indexed by lq_kernel_id: summed duration in microseconds and number of launches since
- *       recording started; waits for the recorded launches to finish, then discards the records.
+ *       recording started; waits for the recorded launches to finish, then discards the records.  The id names the
+ *       kernel that ran: a call of LQ_VARIANT_FUSED that runs in row slabs counts under LQ_KERNEL_SLAB.
  * Host-side state shared by all threads of the process: call from one thread at a time.  At most
  * 65536 launches are recorded between reads; further ones run untimed.
  * ------------------------------------------------------------------------------------------- */

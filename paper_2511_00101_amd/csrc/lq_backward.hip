@@ -659,7 +659,7 @@ extern "C" lq_status lora_segmented_backward(const void* x, int64_t ldx, const v
     const bool one_launch = variant == LQ_VARIANT_FUSED && h_slices_bytes(n_tokens, max_rank) <= 0x7fffffffull;
     s1.coherent = one_launch; s1.hpart_bytes = one_launch ? (unsigned int)h_slices_bytes(n_tokens, max_rank) : 0;
     if (variant == LQ_VARIANT_SLAB) {
-        if (run_slab(s1, st, kKernelSlab, leave) != hipSuccess) return LQ_ERR_HIP;
+        if (run_slab(s1, st, leave) != hipSuccess) return LQ_ERR_HIP;
     } else if (one_launch) {
         if (run_shrink_expand(s1, LQ_VARIANT_FUSED, st, leave) != hipSuccess) return LQ_ERR_HIP;
     } else {

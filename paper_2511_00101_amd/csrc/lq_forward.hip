@@ -1400,7 +1400,7 @@ hipError_t run_shrink_expand(FwdParams& p, int variant, hipStream_t st, const Sl
 {
     const int nt = nt_for(p.max_rank);
     hipError_t e = hipSuccess;
-    if (variant == LQ_VARIANT_FUSED && slab_form(p)) return run_slab(p, st, kKernelFused, frag);
+    if (variant == LQ_VARIANT_FUSED && slab_form(p)) return run_slab(p, st, frag);
     if (variant == LQ_VARIANT_FUSED) {
         const int grid_f = nt == 1 ? fused_grid<1, 1, 2>() : nt == 2 ? fused_grid<2, 1, 2>()
                          : nt == 4 ? fused_grid<4, 2, 2>() : fused_grid<8, 4, 1>();
@@ -1505,7 +1505,7 @@ lq_status forward_checked(const void* x, int64_t ldx, int32_t d_in, int32_t n_pr
     p.hpart_bytes = (unsigned int)h_bytes;
     if (variant == LQ_VARIANT_SLAB) {
         p.ksplit = 1; p.ks_log2 = 0;
-        return run_slab(p, stream, kKernelSlab) == hipSuccess ? LQ_OK : LQ_ERR_HIP;
+        return run_slab(p, stream) == hipSuccess ? LQ_OK : LQ_ERR_HIP;
     }
     return run_shrink_expand(p, variant, stream) == hipSuccess ? LQ_OK : LQ_ERR_HIP;
 }

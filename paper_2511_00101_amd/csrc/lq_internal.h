@@ -154,7 +154,7 @@ __device__ __forceinline__ long long frag_at(int pos, int j, int tiles)
 inline size_t frag_bytes(int n_tokens, int tiles) { return ((size_t)n_tokens + 31) / 32 * tiles * 2 * kWave * 16; }
 
 // The row-slab variant (LQ_VARIANT_SLAB): one launch, no partial-h buffer, no device-wide wait.
-hipError_t run_slab(const FwdParams& p, hipStream_t stream, int kernel_id, const SlabFrag* frag = nullptr);
+hipError_t run_slab(const FwdParams& p, hipStream_t stream, const SlabFrag* frag = nullptr);
 
 constexpr int kAllKinds = 7;
 constexpr int kFinetuneOnly = 1 << LQ_SEG_FINETUNE;
@@ -267,7 +267,7 @@ __device__ __forceinline__ bool grid_barrier(int* header, int* err, int gen0, Ov
 // ---- optional timing of the library's own launches (lora_profile_enable / lora_profile_read) ----------------
 // When enabled, a launch goes through hipExtLaunchKernelGGL with a pair of events that receive the
 // dispatch's own start and end time stamps (what a kernel trace reports), and is filed under its id.
-// (kKernelFused: the launch of a call in the fused variant, in either of its two forms)
+// (By the kernel that runs: a call of the fused variant in its row-slab form is filed under kKernelSlab.)
 enum KernelId { kKernelBuild = 0, kKernelShrink, kKernelExpand, kKernelFused, kKernelWgrad, kKernelWreduce, kKernelSlab, kKernelIds };
 bool profile_on();
 void profile_events(int kernel_id, hipEvent_t* start, hipEvent_t* stop);  // a fresh pair (null, null when full)

@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void slab_kernel(PP p)
 constexpr float kPartsFromB = 300000.f;  // elements of B (of all layers) from which a wide layer is cut into parts, see slab_plan
 
 template <int NT, int MTM, class PP>
-hipError_t launch_slab(PP p, const FwdParams& all, hipStream_t st, int kernel_id)
+hipError_t launch_slab(PP p, const FwdParams& all, hipStream_t st)
 {
     static DeviceGrid cache;
     const int grid = cache.get([] { return resident_grid(slab_kernel<NT, MTM, PP>, kSlabLdsBytes); });
@@ -172,37 +172,37 @@ hipError_t launch_slab(PP p, const FwdParams& all, hipStream_t st, int kernel_id
     const float b = (float)p.max_rank * columns, x_passes = NT >= 4 ? (float)p.n_proj : 1.f;
     p.slab_parts = b >= kPartsFromB ? 0.3f * b * (float)grid / ((float)p.d_in * x_passes) : 0.f;
     p.slab_rows_per_rank = 0.8f * ((float)p.d_in * (float)p.n_proj + columns) / ((float)p.d_in + 2.f * columns);
-    return launch_kernel(kernel_id, slab_kernel<NT, MTM, PP>, dim3(grid), dim3(kThreads), kSlabLdsBytes, st, p);
+    return launch_kernel(kKernelSlab, slab_kernel<NT, MTM, PP>, dim3(grid), dim3(kThreads), kSlabLdsBytes, st, p);
 }
 
 // (up to 4096 rows of a batch with few enough segments fit one round of 32-row units, and the kernel of two row tiles starts
 // sooner: 256 decode rows of rank 16 15.5 us a pass instead of 16.0, 2048 rows of rank 64 26.5 us instead of 26.9)
 template <class PP>
-hipError_t launch_single(const PP& p, const FwdParams& all, hipStream_t st, int kernel_id)
+hipError_t launch_single(const PP& p, const FwdParams& all, hipStream_t st)
 {
     const int nt = nt_for(p.max_rank);
     const bool wide = (float)p.max_rank * (float)p.proj0.d_out >= kPartsFromB;
     if ((p.n_tokens <= 4096 && !wide) || nt == 8)
-        return nt == 1 ? launch_slab<1, 2>(p, all, st, kernel_id) : nt == 2 ? launch_slab<2, 2>(p, all, st, kernel_id)
-             : nt == 4 ? launch_slab<4, 2>(p, all, st, kernel_id) : launch_slab<8, 2>(p, all, st, kernel_id);
-    return nt == 1   ? launch_slab<1, 4>(p, all, st, kernel_id)
-           : nt == 2 ? launch_slab<2, 4>(p, all, st, kernel_id)
-                     : launch_slab<4, 4>(p, all, st, kernel_id);
+        return nt == 1 ? launch_slab<1, 2>(p, all, st) : nt == 2 ? launch_slab<2, 2>(p, all, st)
+             : nt == 4 ? launch_slab<4, 2>(p, all, st) : launch_slab<8, 2>(p, all, st);
+    return nt == 1   ? launch_slab<1, 4>(p, all, st)
+           : nt == 2 ? launch_slab<2, 4>(p, all, st)
+                     : launch_slab<4, 4>(p, all, st);
 }
 
 }  // namespace
 
-hipError_t run_slab(const FwdParams& p, hipStream_t st, int kernel_id, const SlabFrag* frag)
+hipError_t run_slab(const FwdParams& p, hipStream_t st, const SlabFrag* frag)
 {
     const int nt = nt_for(p.max_rank);
     if (p.n_proj > 1)
-        return nt == 1 ? launch_slab<1, 2>(p, p, st, kernel_id) : nt == 2 ? launch_slab<2, 2>(p, p, st, kernel_id)
-             : nt == 4 ? launch_slab<4, 2>(p, p, st, kernel_id) : launch_slab<8, 2>(p, p, st, kernel_id);
-    if (!frag) return launch_single(static_cast<const FwdCore&>(p), p, st, kernel_id);
+        return nt == 1 ? launch_slab<1, 2>(p, p, st) : nt == 2 ? launch_slab<2, 2>(p, p, st)
+             : nt == 4 ? launch_slab<4, 2>(p, p, st) : launch_slab<8, 2>(p, p, st);
+    if (!frag) return launch_single(static_cast<const FwdCore&>(p), p, st);
     FwdFrag q;
     static_cast<FwdCore&>(q) = p;
     q.frag = *frag;
-    return launch_single(q, p, st, kernel_id);
+    return launch_single(q, p, st);
 }
 
 }  // namespace lq

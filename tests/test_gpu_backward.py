@@ -185,8 +185,9 @@ def test_backward_caller_tables_with_repeated_finetune_adapter(oracle_mod):
 
 @pytest.mark.parametrize("ranks", [[64, 33, 32, 17, 16, 5], [128, 65, 64, 33, 32, 16]])
 def test_backward_of_mixed_ranks(oracle_mod, ranks):
-    """Adapters that need 1, 2, 4 and 8 rank tiles in one launch.  The slab kernel's units (g and dx) run with their own
-    adapter's, all weight-gradient units with those of the largest rank: whole segments and (over 512 rows) cut ones."""
+    """Adapters that need 1, 2, 4 and 8 rank tiles in one launch.  AUTO: the slab kernel's units (g and dx) and the weight
+    gradients' of whole segments run with their own adapter's tiles.  SPLIT: all weight-gradient units run with those of the
+    largest rank, segments of up to 512 rows whole and longer ones cut."""
     lens = [700, 3, 32, 33, 520, 513]
     rng = np.random.default_rng(ranks[0])
     order = rng.permutation(sum(lens))
@@ -194,7 +195,8 @@ def test_backward_of_mixed_ranks(oracle_mod, ranks):
     tk = np.zeros(len(ta), np.uint8)
     p = synth.make_problem("own_rank", synth.Batch(ta, tk), 520, 264, np.array(ranks, np.int32), rng.uniform(0.5, 1.5, len(ranks)),
                            9, with_dy=True, w_std=0.02)
-    run_backward(oracle_mod, p, lq.LQ_VARIANT_AUTO)
+    for variant in (lq.LQ_VARIANT_AUTO, lq.LQ_VARIANT_SPLIT):
+        run_backward(oracle_mod, p, variant)
 
 
 def test_backward_of_a_matrix_beyond_4_gib():
@@ -223,7 +225,7 @@ def test_backward_of_a_matrix_beyond_4_gib():
     (32, 500, 264, 16384, "slab"), (32, 500, 264, 16392, "fused"),            # the forward takes the slab kernel for both
     (64, 500, 4096, 8192, "slab"), (64, 500, 2048, 8200, "slab"), (64, 500, 2056, 8200, "fused"),
     (128, 500, 4096, 4096, "slab"), (128, 500, 2048, 8192, "slab"), (128, 500, 2056, 4104, "fused"),
-    (64, 1500, 4104, 264, "fused"), (64, 8193, 264, 264, "fused")])
+    (64, 1500, 4104, 264, "fused"), (64, 8193, 264, 264, "fused in slabs")])
 def test_automatic_choice_of_the_backward(max_rank, T, d_out, d_in, kernel):
     """Only the fine-tune rows run (here one token in ten), so the branches of the rule that need many rows are not taken."""
     gen = torch.Generator(device="cuda").manual_seed(T + d_in)
@@ -245,8 +247,8 @@ def test_automatic_choice_of_the_backward(max_rank, T, d_out, d_in, kernel):
         return ran, dx
 
     ran, got = run(lq.LQ_VARIANT_AUTO)
-    assert ran == ["forward_" + kernel]
-    _, want = run({"slab": lq.LQ_VARIANT_SLAB, "fused": lq.LQ_VARIANT_FUSED}[kernel])
+    assert ran == ["forward_fused" if kernel == "fused" else "forward_slab"]
+    _, want = run(lq.LQ_VARIANT_SLAB if kernel == "slab" else lq.LQ_VARIANT_FUSED)
     assert torch.equal(got, want)
 
 
@@ -325,3 +327,56 @@ def test_weight_gradients_in_units_of_1024_rows(rank):
         g = s * (dy[rows].double() @ B[a].double().T)
         for got, want in ((dA[a], g.T @ x[rows].double()), (dB[a], (s * h[a]).T @ dy[rows].double())):
             assert rel_frobenius(got.cpu().numpy(), want.cpu().numpy()) <= WGRAD_REL_FROBENIUS, a
+
+
+def backward_against_64_bits(ranks, scales, ta, tk, d_in, d_out, variant, seed, dA_skip=(), dB_skip=()):
+    """One backward call on random operands, dx and the weight gradients compared with 64 bits; the kernels that ran."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    T, n = len(ta), len(ranks)
+    A, B = [new(r, d_in, 0.05) for r in ranks], [new(r, d_out, 0.05) for r in ranks]
+    ad = lq.AdapterTable.from_tensors(A, B, scales)
+    x, dy, dx = new(T, d_in, 1.0), new(T, d_out, 1.0), new(T, d_in, 1.0)
+    dx0 = dx.clone()
+    seg = lq.SegmentTables.empty(T, n)
+    lq.lora_build_segments(ta.cuda(), tk.cuda(), ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, n)))
+    live = [torch.nonzero((ta == a) & (tk == 0)).flatten().cuda() for a in range(n)]
+    h = [x[r].double() @ A[a].double().T for a, r in enumerate(live)]
+    h_saved = torch.cat([v.flatten() for v in h] + [torch.zeros(1, dtype=torch.float64, device="cuda")]).float()
+    ws = lq.workspace(lq.lora_backward_workspace_bytes(T, n, max(ranks), d_in, d_out))
+    ws[4096 // 8:] = -1                                          # (NaN patterns: nothing of an earlier call may be read)
+    dA, dB = [torch.ones(r, d_in, device="cuda") for r in ranks], [torch.ones(r, d_out, device="cuda") for r in ranks]
+    table = lambda g, skip: torch.tensor([0 if a in skip else t.data_ptr() for a, t in enumerate(g)], dtype=torch.int64, device="cuda")
+    lq.lora_profile_enable(True)
+    lq.lora_segmented_backward(x, dy, dx, ad, table(dA, dA_skip), table(dB, dB_skip), seg, h_saved, ws, variant)
+    ran = [name for name, (_, k) in lq.lora_profile_read().items() if k]
+    lq.lora_profile_enable(False)
+    lq.raise_on_device_error(ws)
+    want_dx = dx0.double()
+    for a, rows in enumerate(live):
+        g = scales[a] * (dy[rows].double() @ B[a].double().T)
+        want_dx[rows] += g @ A[a].double()
+        for got, want, skip in ((dA[a], g.T @ x[rows].double(), dA_skip), (dB[a], (scales[a] * h[a]).T @ dy[rows].double(), dB_skip)):
+            if a in skip or not len(rows):
+                assert bool((got == 1).all())
+            else:
+                assert rel_frobenius(got.cpu().numpy(), 1 + want.cpu().numpy()) <= WGRAD_REL_FROBENIUS, a
+    assert rel_frobenius(dx.double().cpu().numpy(), want_dx.cpu().numpy()) <= 5e-3
+    others = torch.ones(T, dtype=torch.bool, device="cuda")
+    for rows in live:
+        others[rows] = False
+    assert torch.equal(dx[others], dx0[others])
+    return ran, ws
+
+
+@pytest.mark.parametrize("rank,T,d_in,d_out,kernel", [
+    (64, 4095, 136, 72, "fused"), (64, 4096, 136, 72, "slab"), (64, 8191, 72, 4104, "fused"), (64, 8192, 72, 4104, "slab"),
+    (64, 5000, 16384, 72, "slab"), (64, 5000, 16392, 72, "fused"), (32, 5000, 136, 256, "slab"), (32, 5000, 136, 264, "fused"),
+    (65, 5000, 136, 72, "fused"), (16, 49153, 72, 64, "fused"), (16, 49152, 72, 64, "slab")])
+def test_forms_of_the_fused_variant_in_the_backward(rank, T, d_in, d_out, kernel):
+    """Either side of the lines between the two forms of g and dx (dy is read, dx written), one token in three a fine-tune row."""
+    ta = torch.repeat_interleave(torch.arange(6, dtype=torch.int32), torch.tensor([T // 2, T // 4, 33, 64, 1, T - T // 2 - T // 4 - 98]))
+    ta, tk = ta[torch.randperm(T, generator=torch.Generator().manual_seed(T))], (torch.arange(T) % 3).to(torch.uint8)
+    ranks = [rank, max(1, rank // 2), rank, 5, 16, rank]
+    ran, _ = backward_against_64_bits(ranks, [0.5, 1.0, 1.5, 2.0, 0.75, 1.25], ta, tk, d_in, d_out, lq.LQ_VARIANT_FUSED, T + d_in)
+    assert [name for name in ran if name.startswith("forward")] == ["forward_" + kernel]

@@ -542,7 +542,8 @@ def test_every_unit_runs_with_its_own_rank(oracle_mod, variant, ranks):
     check_forward(oracle_mod, p, variant)
 
 
-# either side of every line of the automatic rule: max_rank, tokens, d_in, d_out of each layer, the kernel it picks
+# either side of every line of the automatic rule: max_rank, tokens, d_in, d_out of each layer, the variant it picks ("fused": the kernel
+# with the device-wide barrier, "fused in slabs": that variant's form for long batches)
 AUTO_LINES = [
     # ranks up to 32: output columns, tokens, layers, input columns
     (32, 40, 264, [16384], "slab"), (32, 40, 264, [16392], "fused"), (16, 383, 264, [16392], "fused"),
@@ -550,16 +551,16 @@ AUTO_LINES = [
     (16, 500, 264, [28680], "fused"), (32, 500, 4096, [8200, 8200], "slab"), (32, 500, 4104, [8200, 8200], "fused"),
     (32, 500, 4104, [16400], "slab"), (32, 500, 264, [5528, 5528, 5528], "fused"), (32, 2000, 264, [5456, 5456, 5456], "slab"),
     # above: groups, tokens, rows x output columns
-    (33, 500, 264, [520], "slab"), (33, 500, 264, [520, 520], "fused"), (64, 8192, 264, [264], "slab"), (64, 8193, 264, [264], "fused"),
-    (64, 6591, 264, [4096], "slab"), (64, 6592, 264, [4096], "fused"), (65, 5859, 264, [4096], "slab"), (65, 5860, 264, [4096], "fused"),
+    (33, 500, 264, [520], "slab"), (33, 500, 264, [520, 520], "fused"), (64, 8192, 264, [264], "slab"), (64, 8193, 264, [264], "fused in slabs"),
+    (64, 6591, 264, [4096], "slab"), (64, 6592, 264, [4096], "fused in slabs"), (65, 5859, 264, [4096], "slab"), (65, 5860, 264, [4096], "fused"),
     (128, 2441, 264, [8192], "slab"), (128, 2442, 264, [8192], "fused"), (64, 1464, 264, [16384], "slab"), (64, 1465, 264, [16384], "fused"),
-    (64, 700, 264, [16392], "fused"), (64, 12000, 4096, [4096], "fused"),
+    (64, 700, 264, [16392], "fused"), (64, 12000, 4096, [4096], "fused in slabs"),
     # few rows, by the widths
     (64, 1, 4096, [8192], "slab"), (64, 1, 2048, [8200], "slab"), (64, 255, 2056, [8200], "fused"), (64, 256, 2056, [8200], "slab"),
     (128, 1, 4096, [4096], "slab"), (128, 1, 2048, [8192], "slab"), (128, 255, 2056, [4104], "fused"), (128, 256, 2056, [4104], "slab"),
     (128, 255, 264, [8200], "fused"), (128, 256, 264, [8200], "slab"),
     # wide inputs
-    (64, 1023, 4104, [264], "fused"), (64, 1024, 4104, [264], "slab"), (64, 3000, 4104, [264], "slab"), (64, 3001, 4104, [264], "fused"),
+    (64, 1023, 4104, [264], "fused"), (64, 1024, 4104, [264], "slab"), (64, 3000, 4104, [264], "slab"), (64, 3001, 4104, [264], "fused in slabs"),
     (128, 1024, 4104, [264], "fused"), (64, 1024, 8200, [264], "fused"), (64, 1024, 4104, [8200], "fused"),
 ]
 
@@ -592,8 +593,8 @@ def test_automatic_choice(max_rank, T, d_in, d_outs, kernel):
         return ran, ys + hs
 
     ran, got = run(lq.LQ_VARIANT_AUTO)
-    assert ran == ["forward_" + kernel]
-    _, want = run({"slab": lq.LQ_VARIANT_SLAB, "fused": lq.LQ_VARIANT_FUSED}[kernel])
+    assert ran == ["forward_fused" if kernel == "fused" else "forward_slab"]
+    _, want = run(lq.LQ_VARIANT_SLAB if kernel == "slab" else lq.LQ_VARIANT_FUSED)
     assert all(torch.equal(a, b) for a, b in zip(got, want))
 
 
@@ -720,3 +721,49 @@ def test_tall_slabs_beyond_the_cached_segments(oracle_mod):
     ta, tk = np.repeat(np.arange(180) % 90, lens).astype(np.int32), np.repeat(np.arange(180) // 90, lens).astype(np.uint8)
     p = synth.make_problem("many", synth.Batch(ta, tk), 72, 136, rng.choice([8, 40, 64], size=90).astype(np.int32), rng.uniform(0.5, 1.5, 90), 9, w_std=0.05)
     check_forward(oracle_mod, p, lq.LQ_VARIANT_SLAB)
+
+
+@pytest.mark.parametrize("rank,T,d_in,d_out,kernel", [
+    (64, 2047, 72, 136, "fused"), (64, 2048, 72, 136, "slab"),                    # tokens
+    (64, 2100, 72, 16384, "slab"), (64, 2100, 72, 16392, "fused"), (16, 2600, 64, 16392, "fused"), (32, 4100, 128, 16392, "fused"),
+    (32, 6000, 256, 136, "slab"), (32, 6000, 264, 136, "fused"), (16, 6000, 1032, 72, "fused"),   # widths no multiple of 64
+    (64, 3000, 264, 136, "slab"), (65, 3000, 264, 136, "fused"), (128, 5000, 264, 136, "fused"),  # ranks
+    (16, 49152, 64, 72, "slab"), (16, 49153, 64, 72, "fused"), (64, 49153, 72, 136, "fused"),     # narrow layers of many rows
+    (32, 49153, 1024, 1016, "fused"), (32, 49153, 1024, 1024, "slab")])
+def test_forms_of_the_fused_variant(rank, T, d_in, d_out, kernel):
+    """Either side of every line between the fused variant's two forms (single calls): which kernel ran, and y and the saved h
+    against 64 bits, on long segments, short ones and rows without an adapter, in shuffled order."""
+    gen = torch.Generator(device="cuda").manual_seed(T + d_in + d_out)
+    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    lens = [T // 3, T // 4, 1, 15, 16, 17, 31, 33, 63, 65, 127, 129, 300]
+    n, order = len(lens), torch.randperm(T, generator=torch.Generator().manual_seed(T))
+    ta = torch.full((T,), -1, dtype=torch.int32)
+    ta[: sum(lens)] = torch.repeat_interleave(torch.arange(n, dtype=torch.int32), torch.tensor(lens))
+    ta, tk = ta[order], (torch.arange(T) * 7 % 3).to(torch.uint8)[order]
+    ranks = [rank if a % 3 else max(1, rank // 2 - 3) for a in range(n)]
+    A, B = [new(r, d_in, d_in ** -0.5) for r in ranks], [new(r, d_out, 0.1) for r in ranks]
+    ad = lq.AdapterTable.from_tensors(A, B, [0.5 + 0.125 * a for a in range(n)])
+    x, y = new(T, d_in, 1.0), new(T, d_out, 1.0)
+    want = y.double()
+    seg = lq.SegmentTables.empty(T, n)
+    lq.lora_build_segments(ta.cuda(), tk.cuda(), ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, n)))
+    h = torch.full((T * rank,), float("nan"), device="cuda")
+    ws = lq.workspace(lq.lora_forward_workspace_bytes(T, ad.max_rank, d_in, d_out, lq.LQ_VARIANT_FUSED))
+    lq.lora_profile_enable(True)
+    lq.lora_segmented_forward(x, y, ad, seg, h, ws, lq.LQ_VARIANT_FUSED)
+    ran = [name for name, (_, k) in lq.lora_profile_read().items() if k]
+    lq.lora_profile_enable(False)
+    lq.raise_on_device_error(ws)
+    assert ran == ["forward_" + kernel]
+    at = 0
+    for a in range(n):
+        rows = torch.nonzero(ta == a).flatten().cuda()
+        hs = x[rows].double() @ A[a].double().T
+        want[rows] += (0.5 + 0.125 * a) * (hs @ B[a].double())
+        ft = hs[(tk[rows.cpu()] == 0).cuda()]
+        assert rel_frobenius(h[at: at + ft.numel()].view_as(ft).cpu().numpy(), ft.cpu().numpy()) <= 1e-4, a
+        at += ft.numel()
+    for a in range(-1, n):
+        rows = torch.nonzero(ta == a).flatten().cuda()
+        assert rel_frobenius(y[rows].double().cpu().numpy(), want[rows].cpu().numpy()) <= (REL_FROBENIUS if a >= 0 else 0.0), a
+    assert bool(torch.isnan(h[at:]).all())
