@@ -133,8 +133,8 @@ __device__ __forceinline__ void wgrad_unit(const BwdParams& p, const Unit& u, in
 #pragma unroll
         for (int q = 0; q < NT; ++q) {
             const float v = (i < u.len && y_piece + 16 * q < rank) ? h[q] * h[NT] : 0.f;
-            const unsigned int hi = pack_bf16x2(v, 0.f) & 0xffffu;
-            const unsigned int lo = pack_bf16x2(v - bf16_lo(hi), 0.f) & 0xffffu;
+            unsigned int hi, lo;
+            split_value(v, hi, lo);
             lh[y_row * C::HPITCH + y_piece + 16 * q] = (u16)hi;
             lh[(kStepRows + y_row) * C::HPITCH + y_piece + 16 * q] = (u16)lo;
         }
@@ -238,13 +238,6 @@ constexpr size_t kWholeWaveBytes = 32 * kWave * sizeof(float);   // LDS of a wav
 static_assert((size_t)kStepRows * kWholePitch * sizeof(u16) <= kWholeWaveBytes, "a step's rows fit");
 constexpr size_t kWholeLdsBytes = kWaves * kWholeWaveBytes;
 
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // NT: 16-rank tiles of this unit, from rank j0 on
 template <int NT>
 __device__ __forceinline__ void whole_unit(const BwdParams& p, int begin, int end, int rank, float scale, bool for_b, int col_block,
@@ -326,7 +319,7 @@ __device__ __forceinline__ void whole_unit(const BwdParams& p, int begin, int en
             load(j + D, rows[J & 1], gy[S], gf[S], row_in[S]);  // the registers are free: the step D ahead
             rows[J & 1] = row_load(j + D + 2);
             __builtin_amdgcn_sched_barrier(0);
-            wave_fence();
+            wave_sync();
             // the staged rows are the MFMA's k axis: read back transposed
 #pragma unroll
             for (int nt = 0; nt < kWholeTiles; ++nt) {
@@ -337,7 +330,7 @@ __device__ __forceinline__ void whole_unit(const BwdParams& p, int begin, int en
                     acc[jt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f[jt][0]), as_bf16x8(yf), acc[jt][nt], 0, 0, 0);
                 }
             }
-            wave_fence();  // the rows are overwritten by the next step
+            wave_sync();  // the rows are overwritten by the next step
         };
         {
             int r[D];

@@ -67,6 +67,21 @@ __device__ __forceinline__ void unpack8(const u32x4& w, float* f)
     f[6] = bf16_lo(w.w); f[7] = bf16_hi(w.w);
 }
 
+// a value as a bf16 high and low part (together ~16 mantissa bits).  (No low part of an infinity: the difference would be a NaN.)
+__device__ __forceinline__ void split_value(float v, unsigned int& hi, unsigned int& lo)
+{
+    hi = pack_bf16x2(v, 0.f) & 0xffffu;
+    lo = (hi & 0x7fffu) == 0x7f80u ? 0u : pack_bf16x2(v - bf16_lo(hi), 0.f) & 0xffffu;
+}
+
+// LDS that belongs to one wave: what its lanes have written is there for all of them
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- transposing LDS read (gfx950 ds_read_b64_tr_b16) ------------------------------------------
 // A 16 x 32 block of 16-bit elements that lies row-major in LDS ([k row][column], `pitch` elements per row)
 // as the 16x16x32 MFMA wants it: lane (c = lane % 16, kg = lane / 16) gets column c, rows 8 kg .. 8 kg + 7.

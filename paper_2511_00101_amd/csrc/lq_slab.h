@@ -21,13 +21,6 @@ constexpr int kSlabBig = 0x7fffffff;
 constexpr int kMaxParts = 8;           // column parts a chunk of rows is cut into
 constexpr size_t kWaveBytes = 16384;   // LDS of one wave: its slabs, later its share of the reduction buffer
 
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // 16 bytes of an adapter matrix at element offset `off` (< 2^31, see slab_reaches): a wave-uniform base and a 32-bit byte offset per
 // lane, the form that needs no 64-bit address arithmetic in vector registers
 __device__ __forceinline__ u32x4 load_at(gconst_u16 base, unsigned int off)
@@ -430,12 +423,6 @@ __device__ __forceinline__ void slab_unit_rows(const PP& p, const Unit& u, const
     }
 }
 
-// a value as a bf16 high and low part (together ~16 mantissa bits).  (No low part of an infinity: the difference would be a NaN.)
-__device__ __forceinline__ void split_value(float v, unsigned int& hi, unsigned int& lo)
-{
-    hi = pack_bf16x2(v, 0.f) & 0xffffu;
-    lo = (hi & 0x7fffu) == 0x7f80u ? 0u : pack_bf16x2(v - bf16_lo(hi), 0.f) & 0xffffu;
-}
 __device__ __forceinline__ void store_frag(u16* frag, long long at, float v)
 {
     unsigned int hi, lo;

@@ -380,3 +380,35 @@ def test_forms_of_the_fused_variant_in_the_backward(rank, T, d_in, d_out, kernel
     ranks = [rank, max(1, rank // 2), rank, 5, 16, rank]
     ran, _ = backward_against_64_bits(ranks, [0.5, 1.0, 1.5, 2.0, 0.75, 1.25], ta, tk, d_in, d_out, lq.LQ_VARIANT_FUSED, T + d_in)
     assert [name for name in ran if name.startswith("forward")] == ["forward_" + kernel]
+
+
+@pytest.mark.parametrize("variant", [lq.LQ_VARIANT_SPLIT, lq.LQ_VARIANT_SLAB])
+@pytest.mark.parametrize("rank,T", [(8, 700), (32, 700), (64, 1100), (128, 1100)])
+def test_infinite_gradients(rank, T, variant):
+    """One infinite value in the saved h and one in dy: with positive operands the weight gradients that sum over an infinite h
+    or g are infinite, not NaN, and all that no infinity reaches finite, in both weight-gradient kernels (chunks of 512 rows with SPLIT, whole segments with SLAB)."""
+    gen = torch.Generator(device="cuda").manual_seed(rank)
+    pos = lambda r, c: torch.rand(r, c, device="cuda", generator=gen).add_(0.5).to(torch.bfloat16)
+    d_in, d_out = 264, 136
+    ad = lq.AdapterTable.from_tensors([pos(rank, d_in) for _ in range(2)], [pos(rank, d_out) for _ in range(2)], [0.5, 0.5])
+    seg = lq.SegmentTables.empty(T, 2)
+    ta = (torch.arange(T, device="cuda") >= T - 30).to(torch.int32)                # one segment of more than a chunk, one of 30 rows
+    lq.lora_build_segments(ta, torch.zeros(T, dtype=torch.uint8, device="cuda"), ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, 2)))
+    x, dy, dx = pos(T, d_in), pos(T, d_out), pos(T, d_in)
+    h = torch.rand(T, rank, device="cuda", generator=gen).add_(0.5)
+    h[T // 2, 3] = float("inf")          # dB of adapter 0, rank row 3
+    dy[T - 7, 20] = float("inf")         # through g all of adapter 1's dA; and column 20 of its dB
+    ws = lq.workspace(lq.lora_backward_workspace_bytes(T, 2, rank, d_in, d_out))
+    dA, dB = [torch.zeros(rank, d_in, device="cuda") for _ in range(2)], [torch.zeros(rank, d_out, device="cuda") for _ in range(2)]
+    table = lambda g: torch.tensor([t.data_ptr() for t in g], dtype=torch.int64, device="cuda")
+    lq.lora_profile_enable(True)
+    lq.lora_segmented_backward(x, dy, dx, ad, table(dA), table(dB), seg, h.flatten(), ws, variant)
+    ran = [name for name, (_, k) in lq.lora_profile_read().items() if k]
+    lq.lora_profile_enable(False)
+    lq.raise_on_device_error(ws)
+    assert ("wreduce" in ran) == (variant == lq.LQ_VARIANT_SPLIT)
+    inf = lambda t: bool((t == float("inf")).all())
+    rows, cols = torch.arange(rank, device="cuda") != 3, torch.arange(d_out, device="cuda") != 20
+    assert inf(dB[0][3]) and bool(torch.isfinite(dB[0][rows]).all()) and bool(torch.isfinite(dA[0]).all())
+    assert inf(dA[1]) and bool(torch.isfinite(dB[1][:, cols]).all())
+    assert not bool(torch.isfinite(dB[1][:, 20]).any())          # (infinite or NaN: the parts of h that it meets have either sign)
