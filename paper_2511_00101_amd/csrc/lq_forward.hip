@@ -1385,8 +1385,8 @@ size_t h_slices_bytes(int n_tokens, int max_rank)
 // -> 28672 234 and 253), narrow layers of very many rows (100000 mix 264 -> 264 89 and 112, 40000 1024 -> 1024 88 and 85),
 // ranks above 64 (their units are 32 rows at most), groups, and shorter batches, whose d_in it can cut (700 rows of one
 // segment, 14336 -> 4096, 34 and 38).  In the backward n_tokens counts all rows but the fine-tune rows alone run, so it
-// takes more of them.  (Rank 32 and below, d_in no multiple of 64: the slab kernel's last block re-reads x's first columns against
-// zeros, which an infinity there would make a NaN.)
+// takes more of them.  (Rank 32 and below, d_in no multiple of 64: the slab kernel for units of up to 32 rows re-reads x's first
+// columns against zeros in the last block, which an infinity there would make a NaN.)
 bool slab_form(const FwdParams& p)
 {
     const int d_out = p.proj0.d_out;

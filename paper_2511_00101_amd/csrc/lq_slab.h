@@ -76,8 +76,9 @@ __device__ __forceinline__ void slab_shrink(const PP& p, const Unit&, const SegI
     for (int i = 0; i < NA; ++i) aoff[i] = (unsigned int)(min(r8 + 8 * i, rank - 1) * p.d_in);
 
     // a lane's 8 columns lie wholly inside or wholly beyond d_in; beyond, it re-reads column 0 and A counts as zero.  With
-    // ZERO_X (launches above rank 32) so does x, or an infinity in column 0 would make the row's h a NaN: the zeros are the 16
-    // bytes that pad every row of the slab.  (It costs no time there; a rank-16 decode batch would pay up to 4 %.)
+    // ZERO_X (launches above rank 32 and those of units taller than 32 rows) so does x, or an infinity in column 0 would make the
+    // row's h a NaN: the zeros are the 16 bytes that pad every row of the slab.  (It costs no time there: 9000 rows of rank 16 to
+    // 64, five shapes, all within 0.3 us; a rank-16 decode batch would pay up to 4 %.)
     if (ZERO_X && lane < 32) {
         constexpr u32x4 zero = {0u, 0u, 0u, 0u};
         *reinterpret_cast<u32x4*>(xs + lane * kPitch + kKB) = zero;

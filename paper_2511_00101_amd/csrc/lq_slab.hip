@@ -116,10 +116,10 @@ __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegI
     constexpr int NPP = GROUP ? pass_projections<NT>() : 1;
     for (int pi0 = 0; pi0 < n_proj; pi0 += NPP) {
         const int np = min(NPP, n_proj - pi0);  // workgroup uniform
-        if (NPP >= 4 && np == 4) slab_pass<NT, (NPP >= 4 ? 4 : 1), MTM, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
-        else if (NPP >= 3 && np == 3) slab_pass<NT, (NPP >= 3 ? 3 : 1), MTM, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
-        else if (NPP >= 2 && np == 2) slab_pass<NT, (NPP >= 2 ? 2 : 1), MTM, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
-        else slab_pass<NT, 1, MTM, (NT >= 4)>(p, u, s0, pi0, part, parts, lds);
+        if (NPP >= 4 && np == 4) slab_pass<NT, (NPP >= 4 ? 4 : 1), MTM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
+        else if (NPP >= 3 && np == 3) slab_pass<NT, (NPP >= 3 ? 3 : 1), MTM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
+        else if (NPP >= 2 && np == 2) slab_pass<NT, (NPP >= 2 ? 2 : 1), MTM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
+        else slab_pass<NT, 1, MTM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
     }
 }
 

@@ -767,3 +767,32 @@ def test_forms_of_the_fused_variant(rank, T, d_in, d_out, kernel):
         rows = torch.nonzero(ta == a).flatten().cuda()
         assert rel_frobenius(y[rows].double().cpu().numpy(), want[rows].cpu().numpy()) <= (REL_FROBENIUS if a >= 0 else 0.0), a
     assert bool(torch.isnan(h[at:]).all())
+
+
+@pytest.mark.parametrize("rank,T,d_in", [(16, 9000, 72), (16, 12000, 200), (32, 9000, 264), (32, 12000, 520), (32, 16384, 136), (8, 20000, 1032)])
+def test_infinities_in_x_in_tall_slabs(rank, T, d_in):
+    """Ranks up to 32 in units of 33 to 64 rows (three and four row tiles), widths that are no multiple of the 64-column block:
+    an infinity in the first column, in the last ones or in between makes its row's h and y infinite, not NaN, and no other's."""
+    gen = torch.Generator(device="cuda").manual_seed(d_in)
+    pos = lambda r, c: torch.rand(r, c, device="cuda", generator=gen).add_(0.5).div_(c ** 0.5).to(torch.bfloat16)
+    A, B = pos(rank, d_in), pos(rank, 136)
+    x = torch.rand(T, d_in, device="cuda", generator=gen).to(torch.bfloat16)
+    rows, cols = torch.arange(0, T, 2, device="cuda"), torch.tensor([0, 5, 7, d_in - 8, d_in - 1, d_in // 2], device="cuda")
+    x[rows, cols[rows // 2 % 6]] = float("inf")
+    ad = lq.AdapterTable.from_tensors([A], [B], [0.5])
+    seg = lq.SegmentTables.empty(T, 1)
+    lq.lora_build_segments(torch.zeros(T, dtype=torch.int32, device="cuda"), torch.zeros(T, dtype=torch.uint8, device="cuda"), ad.ranks, seg,
+                           lq.workspace(lq.lora_build_workspace_bytes(T, 1)))
+    y, h = torch.zeros(T, 136, dtype=torch.bfloat16, device="cuda"), torch.zeros(T * rank, device="cuda")
+    ws = lq.workspace(lq.lora_forward_workspace_bytes(T, rank, d_in, 136, lq.LQ_VARIANT_AUTO))
+    lq.lora_profile_enable(True)
+    lq.lora_segmented_forward(x, y, ad, seg, h, ws, lq.LQ_VARIANT_AUTO)
+    ran = [name for name, (_, n) in lq.lora_profile_read().items() if n]
+    lq.lora_profile_enable(False)
+    lq.raise_on_device_error(ws)
+    assert ran == ["forward_slab"]
+    h = h.view(T, rank)
+    assert bool((y[::2] == float("inf")).all()) and bool((h[::2] == float("inf")).all())
+    want = x[1::2].double() @ A.double().T
+    assert rel_frobenius(h[1::2].cpu().numpy(), want.cpu().numpy()) <= 1e-4
+    assert rel_frobenius(y[1::2].float().cpu().numpy(), (0.5 * want @ B.double()).cpu().numpy()) <= REL_FROBENIUS
