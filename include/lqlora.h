@@ -240,7 +240,7 @@ lq_status lora_segmented_forward_static(const void* x, int64_t ldx, void* y, int
  *   dy       bf16 [n_tokens, d_out] (rows of fine-tune tokens are read)
  *   dx       bf16 [n_tokens, d_in], read-modify-write on fine-tune rows only (one rounding per call);
  *            must not alias x or dy
- *   h_saved  float, the h_out written by the forward (same h_offsets)
+ *   h_saved  float, the h_out written by the forward (same h_offsets); read where a dB is wanted only
  *   dA_ptrs / dB_ptrs  [n_adapters] device arrays of device pointers to float [r_a, d_in] / [r_a, d_out],
  *            accumulated into (caller zeroes); entries may be NULL (that gradient is skipped), and
  *            either table may be NULL; with both NULL only dx is computed

@@ -644,7 +644,7 @@ extern "C" lq_status lora_segmented_backward(const void* x, int64_t ldx, const v
     const int tiles = nt_for(max_rank);
     const size_t frag = (frag_bytes(n_tokens, tiles) + 255) / 256 * 256;
     const bool whole = want_w && slabs && 2 * frag <= h_slices_bytes(n_tokens, max_rank) && whole_segments_win(n_tokens, max_rank, d_in, d_out);
-    const SlabFrag operands = {reinterpret_cast<u16*>(ws + kWsHeaderBytes), reinterpret_cast<u16*>(ws + kWsHeaderBytes + frag), h_saved, tiles};
+    const SlabFrag operands = {reinterpret_cast<u16*>(ws + kWsHeaderBytes), reinterpret_cast<u16*>(ws + kWsHeaderBytes + frag), h_saved, dB_ptrs, tiles};
     const SlabFrag* const leave = whole ? &operands : nullptr;
     // 2. dx += s g A on fine-tune rows: the forward's expand over d_in against A.  LQ_VARIANT_FUSED: both in a
     // single launch when its buffer descriptor can address the slices; else two launches with the same k split.

@@ -56,9 +56,9 @@ struct FwdParams : FwdCore {
 };
 
 // The slab kernel of a backward call whose weight gradients take g and h as ready-made MFMA operands (see frag_at): where they
-// go, the saved h, and the 16-rank tiles per step.  (Its own block and instantiation: as members of FwdCore, with a test in the
+// go, the saved h, the gradients it is wanted for, and the 16-rank tiles per step.  (Its own block and instantiation: as members of FwdCore, with a test in the
 // forward's kernel, they cost a decode layer of 16 rows 2 us of 63 and the unified layer 5 of 351.)
-struct SlabFrag { u16* g; u16* h; const float* h_saved; int tiles; };
+struct SlabFrag { u16* g; u16* h; const float* h_saved; float* const* dB_ptrs; int tiles; };
 struct FwdFrag : FwdCore { SlabFrag frag; };
 
 __device__ __forceinline__ int n_proj_of(const FwdCore&) { return 1; }

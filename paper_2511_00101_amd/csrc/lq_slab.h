@@ -437,6 +437,7 @@ __device__ __forceinline__ void store_frag(u16* frag, long long at, float v)
 template <class PP>
 __device__ __forceinline__ void slab_frag_h(const PP& p, const Unit& u, int rank, const float* lds_scale)
 {
+    if (!p.frag.dB_ptrs || !p.frag.dB_ptrs[u.ad]) return;  // no dB wanted: the caller need not keep that adapter's h
     const float* src = p.frag.h_saved + p.h_offsets[u.seg] + (long long)(u.pos - u.first) * rank;
     const int n = u.len * rank;
     for (int e0 = (int)threadIdx.x; e0 < n; e0 += 4 * kThreads) {

@@ -412,3 +412,33 @@ def test_infinite_gradients(rank, T, variant):
     assert inf(dB[0][3]) and bool(torch.isfinite(dB[0][rows]).all()) and bool(torch.isfinite(dA[0]).all())
     assert inf(dA[1]) and bool(torch.isfinite(dB[1][:, cols]).all())
     assert not bool(torch.isfinite(dB[1][:, 20]).any())          # (infinite or NaN: the parts of h that it meets have either sign)
+
+
+@pytest.mark.parametrize("table", [False, True])
+def test_saved_h_is_read_where_dB_is_wanted_only(table):
+    """Adapters without a dB (no table at all, or null entries) need no saved h: here it ends before theirs.  Their dA and dx, and
+    everything of the others, are right; slabs, whose launch leaves h as the weight gradients' operand."""
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    lens, rank, d_in, d_out = (40, 70, 300), 16, 136, 264
+    T, n = sum(lens), len(lens)
+    A, B = [new(rank, d_in, 0.05) for _ in lens], [new(rank, d_out, 0.05) for _ in lens]
+    ad = lq.AdapterTable.from_tensors(A, B, [1.0] * n)
+    ta = torch.repeat_interleave(torch.arange(n, dtype=torch.int32), torch.tensor(lens)).cuda()
+    seg = lq.SegmentTables.empty(T, n)
+    lq.lora_build_segments(ta, torch.zeros(T, dtype=torch.uint8, device="cuda"), ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, n)))
+    x, dy, dx = new(T, d_in, 1.0), new(T, d_out, 1.0), torch.zeros(T, d_in, dtype=torch.bfloat16, device="cuda")
+    h = (x[:40].double() @ A[0].double().T).float().flatten() if table else torch.zeros(4, device="cuda")
+    dA, dB = [torch.zeros(rank, d_in, device="cuda") for _ in lens], torch.zeros(rank, d_out, device="cuda")
+    ptrs = lambda g: torch.tensor([t.data_ptr() if t is not None else 0 for t in g], dtype=torch.int64, device="cuda")
+    ws = lq.workspace(lq.lora_backward_workspace_bytes(T, n, rank, d_in, d_out))
+    lq.lora_segmented_backward(x, dy, dx, ad, ptrs(dA), ptrs([dB, None, None]) if table else None, seg, h, ws, lq.LQ_VARIANT_SLAB)
+    torch.cuda.synchronize()
+    lq.raise_on_device_error(ws)
+    for a in range(n):
+        rows = ta == a
+        g = dy[rows].double() @ B[a].double().T
+        assert rel_frobenius(dA[a].cpu().numpy(), (g.T @ x[rows].double()).cpu().numpy()) <= WGRAD_REL_FROBENIUS
+        assert rel_frobenius(dx[rows].double().cpu().numpy(), (g @ A[a].double()).cpu().numpy()) <= 5e-3
+    if table:
+        assert rel_frobenius(dB.cpu().numpy(), (h.view(40, rank).double().T @ dy[:40].double()).cpu().numpy()) <= WGRAD_REL_FROBENIUS
