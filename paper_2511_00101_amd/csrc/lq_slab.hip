@@ -23,17 +23,14 @@ constexpr size_t kSlabLdsBytes = kStashOffset + kStashBytes;
 template <class PP> constexpr bool kFrag = std::is_same_v<PP, FwdFrag>;  // a backward call that leaves g and h as operands
 
 // =================================================================================================
-// one pass of a unit: NP projections (pi0 ..) through phase 1, the sum over the waves, and phase 2 (ZERO_X: see slab_shrink)
+// one pass of a unit: NP projections (pi0 ..) through phase 1, the sum over the waves, and phase 2 (STREAM: y non-temporal, see
+// streams_y; ZERO_X: see slab_shrink)
 // =================================================================================================
-template <int NT, int NP, int MTM, bool ZERO_X, class PP>
+template <int NT, int NP, int MTM, bool STREAM, bool ZERO_X, class PP>
 __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const SegInfo& s0, int pi0, int part, int parts,
                                           unsigned char* lds)
 {
     constexpr int KSTEPS = (NT + 1) / 2;
-    // the non-temporal policy for y in the kernels of long batches and of groups (a short batch's y is small and soon used again):
-    // 5632 rows of rank 32 4096 -> 4096 40 -> 35 us, 14336 -> 4096 71 -> 65, q+k+v 63 -> 58; 8192 Zipf rows, 4096 -> 11008 110 -> 99
-    // (The same for x gains as much alone, nothing on top, and loses what the weight gradients find of dy in the cache: 41 -> 49 us.)
-    constexpr bool STREAM = MTM > 2 || std::is_same_v<PP, FwdParams>;
     static_assert((size_t)NP * MTM * KSTEPS * 2 * kWave * 16 <= kHfragBytes, "the pass's h fragments fit");
     u32x4* hfrag = reinterpret_cast<u32x4*>(lds);
     unsigned char* work = lds + kWorkOffset;
@@ -94,7 +91,7 @@ __device__ __forceinline__ void slab_pass(const PP& p, const Unit& u0, const Seg
     __syncthreads();  // before the next pass or unit reuses the LDS
 }
 
-template <int NT, int MTM, class PP>
+template <int NT, int MTM, bool STREAM, class PP>
 __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegInfo& s0, int part, int parts, unsigned char* lds)
 {
     slab_unit_rows(p, u, s0, reinterpret_cast<int*>(lds + kRowsOffset));
@@ -106,25 +103,25 @@ __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegI
         // (Not the groups above rank 64: eight tiles spill already, and the other passes beside them took the spills from
         // 40 to 61 registers: 4096 -> 4096, 1024, 1024, 1024 rows of rank 96: 61.5 -> 69.1 us, of mixed ranks 64.4 -> 68.8.)
         for (int pi = 0; pi < n_proj; ++pi) {
-            if (NT >= 8 && s0.rank > 64) slab_pass<NT, 1, MTM, true>(p, u, s0, pi, part, parts, lds);  // workgroup uniform
-            else if (s0.rank > 32) slab_pass<4, 1, MTM, true>(p, u, s0, pi, part, parts, lds);
-            else if (s0.rank > 16) slab_pass<2, 1, MTM, true>(p, u, s0, pi, part, parts, lds);
-            else slab_pass<1, 1, MTM, true>(p, u, s0, pi, part, parts, lds);
+            if (NT >= 8 && s0.rank > 64) slab_pass<NT, 1, MTM, STREAM, true>(p, u, s0, pi, part, parts, lds);  // workgroup uniform
+            else if (s0.rank > 32) slab_pass<4, 1, MTM, STREAM, true>(p, u, s0, pi, part, parts, lds);
+            else if (s0.rank > 16) slab_pass<2, 1, MTM, STREAM, true>(p, u, s0, pi, part, parts, lds);
+            else slab_pass<1, 1, MTM, STREAM, true>(p, u, s0, pi, part, parts, lds);
         }
         return;
     }
     constexpr int NPP = GROUP ? pass_projections<NT>() : 1;
     for (int pi0 = 0; pi0 < n_proj; pi0 += NPP) {
         const int np = min(NPP, n_proj - pi0);  // workgroup uniform
-        if (NPP >= 4 && np == 4) slab_pass<NT, (NPP >= 4 ? 4 : 1), MTM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
-        else if (NPP >= 3 && np == 3) slab_pass<NT, (NPP >= 3 ? 3 : 1), MTM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
-        else if (NPP >= 2 && np == 2) slab_pass<NT, (NPP >= 2 ? 2 : 1), MTM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
-        else slab_pass<NT, 1, MTM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
+        if (NPP >= 4 && np == 4) slab_pass<NT, (NPP >= 4 ? 4 : 1), MTM, STREAM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
+        else if (NPP >= 3 && np == 3) slab_pass<NT, (NPP >= 3 ? 3 : 1), MTM, STREAM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
+        else if (NPP >= 2 && np == 2) slab_pass<NT, (NPP >= 2 ? 2 : 1), MTM, STREAM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
+        else slab_pass<NT, 1, MTM, STREAM, (NT >= 4 || MTM > 2)>(p, u, s0, pi0, part, parts, lds);
     }
 }
 
 // NT: 16-rank tiles of the launch (ranks up to 16 NT); MTM: 16-row tiles of its tallest unit.
-template <int NT, int MTM, class PP>
+template <int NT, int MTM, bool STREAM, class PP>
 __global__ __launch_bounds__(kThreads) void slab_kernel(PP p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -155,54 +152,100 @@ __global__ __launch_bounds__(kThreads) void slab_kernel(PP p)
         u.pi = 0;
         if (!slab_find(p, sg, cc, pl.per, chunk, u, s)) return;
         stash_tables(sg, cc, stash);
-        slab_unit<NT, MTM>(p, u, s, part, parts, lds_raw);  // (has a workgroup barrier after its first step)
+        slab_unit<NT, MTM, STREAM>(p, u, s, part, parts, lds_raw);  // (has a workgroup barrier after its first step)
         unstash_tables(sg, cc, stash);
     });
 }
 
 constexpr float kPartsFromB = 300000.f;  // elements of B (of all layers) from which a wide layer is cut into parts, see slab_plan
 
-template <int NT, int MTM, class PP>
-hipError_t launch_slab(PP p, const FwdParams& all, hipStream_t st)
+template <int NT, int MTM, bool STREAM, class PP>
+int slab_grid()
 {
     static DeviceGrid cache;
-    const int grid = cache.get([] { return resident_grid(slab_kernel<NT, MTM, PP>, kSlabLdsBytes); });
-    float columns = (float)p.proj0.d_out;
-    for (int k = 1; k < p.n_proj; ++k) columns += (float)all.more[k - 1].d_out;
+    return cache.get([] { return resident_grid(slab_kernel<NT, MTM, STREAM, PP>, kSlabLdsBytes); });
+}
+
+template <int NT, int MTM, bool STREAM, class PP>
+hipError_t launch_slab(PP p, float columns, hipStream_t st)
+{
+    const int grid = slab_grid<NT, MTM, STREAM, PP>();
     const float b = (float)p.max_rank * columns, x_passes = NT >= 4 ? (float)p.n_proj : 1.f;
     p.slab_parts = b >= kPartsFromB ? 0.3f * b * (float)grid / ((float)p.d_in * x_passes) : 0.f;
     p.slab_rows_per_rank = 0.8f * ((float)p.d_in * (float)p.n_proj + columns) / ((float)p.d_in + 2.f * columns);
-    return launch_kernel(kKernelSlab, slab_kernel<NT, MTM, PP>, dim3(grid), dim3(kThreads), kSlabLdsBytes, st, p);
+    return launch_kernel(kKernelSlab, slab_kernel<NT, MTM, STREAM, PP>, dim3(grid), dim3(kThreads), kSlabLdsBytes, st, p);
 }
 
-// (up to 4096 rows of a batch with few enough segments fit one round of 32-row units, and the kernel of two row tiles starts
-// sooner: 256 decode rows of rank 16 15.5 us a pass instead of 16.0, 2048 rows of rank 64 26.5 us instead of 26.9)
 template <class PP>
-hipError_t launch_single(const PP& p, const FwdParams& all, hipStream_t st)
+bool wide_layer(const PP& p, float columns) { return (float)p.max_rank * columns >= kPartsFromB; }
+
+// Four row tiles where a unit can get more than 32 rows (single calls up to rank 64).  A batch of ranks up to 32 whose segments'
+// 32-row chunks fit one round of the grid (sum of ceil(rows / 32) <= tokens / 32 + segments) has none to speak of, and the kernel of
+// two tiles has half the accumulators to add up and starts sooner: 4864 rows of rank 16, 4096 -> 4096, 28.6 us with four tiles and
+// 28.4 with two; where it does not fit, 9000 rows, 44.9 and 47.8.  (Up to rank 64 two tiles gain as little, 40.9 and 40.8 us for 4864
+// rows, and adapters of lower rank lose their taller units: 7413 rows of ranks 8 to 64, 14336 -> 4096, 76.8 and 81.9.  A batch of
+// up to 4096 rows that does not fit has more than 128 segments; its units were never taller.)
+//   Wide layers take taller units in column parts, see slab_plan: not before their 16-row chunks leave room for fewer than
+// five parts, with 49 chunks, since the plan wants at least twice as many parts as there is room for: 16 rows of rank 32, 4096 ->
+// 14336, 12.5 and 12.0 us, 4000 of rank 64 75.5 and 86.
+template <int NT, class PP>
+bool tall_units(const PP& p, float columns)
+{
+    const int segments = p.max_segments < p.n_tokens ? p.max_segments : p.n_tokens;
+    if (wide_layer(p, columns) && p.n_tokens / 16 + segments >= 49) return true;
+    return p.n_tokens > 4096 && (NT > 2 || p.n_tokens / 32 + segments > slab_grid<NT, 2, false, PP>());
+}
+
+// y (dx) non-temporal in long batches, wide layers and groups, from 42 million elements of x and y on (84 MB).  Below, x and y of a few
+// calls stay in the 256 MB cache and the policy only takes them from whoever reads them next; above, it keeps y from displacing
+// what is used again.  Non-temporal over plain, 260 random calls of such shapes on three sets of operands in turn, mean by million elements: 28
+// to 36 1.08 to 1.20, 36 to 42 1.03 to 1.10, 42 to 46 0.93 to 1.02, 46 to 58 0.94 to 1.02 (single calls from 0.81 to 1.5: it depends on where the operands
+// lie).  us plain and non-temporal: rank 32, q+k+v of 2048 rows (21 M) 31.4 and 38.4, 4096 -> 14336 of 1500 (28 M) 27.8 and 33.6,
+// 1024 -> 4096 of 5632 (29 M) 25.2 and 28.4, q+k+v of 4000 (41 M) 46.0 and 47.6; 4096 -> 14336 of 3000 (55 M) 56.4 and 52.5, q+k+v of 5632
+// (58 M) 59.5 and 56.7, 8192 Zipf rows, 4096 -> 11008 (124 M), 110 and 99.  A shorter call with much y loses more than the others
+// gain, hence the batch's length: 2097 rows of rank 16, 4096 -> 14336 (39 M), 33.4 and 43.2.
+//   A backward call touches x too, behind this launch (42 million of dy, dx and x): 260 random calls, 0.98 to 1.02 from 42 to 60 million, 0.97 to 1.00
+// where most rows are fine-tune rows, below 1.02 to 1.08; 5632 rows of rank 32, 4096 -> 1024, among the calls of a decoder layer 5 us less.
+//   As in a model, with the base product that writes y in front and a reader of y behind, the sum of the three differs less, and
+// either way: 4096 -> 4096 of rank 32, 5632 rows 1.4 us less than plain, 8192 rows 3.9 more, 16384 2.7 more (rank 16 5.1 more);
+// q+k+v, 4096 rows 1.7 less, 5632 0.9 more, 16384 4.7 less.
+//   (The same for x gains as much alone, nothing on top, and loses what the weight gradients find of dy in the cache: 41 -> 49 us.)
+template <class PP>
+bool streams_y(const PP& p, float columns)
+{
+    const float width = (float)p.d_in + (p.kinds == kFinetuneOnly ? 2.f * columns : columns);
+    return (p.n_tokens > 4096 || p.n_proj > 1 || wide_layer(p, columns)) && (float)p.n_tokens * width >= 42e6f;
+}
+
+template <int NT, class PP>
+hipError_t launch_rank(const PP& p, float columns, hipStream_t st)
+{
+    const bool stream = streams_y(p, columns);
+    if constexpr (NT < 8 && !std::is_same_v<PP, FwdParams>)
+        if (tall_units<NT>(p, columns)) return stream ? launch_slab<NT, 4, true>(p, columns, st) : launch_slab<NT, 4, false>(p, columns, st);
+    return stream ? launch_slab<NT, 2, true>(p, columns, st) : launch_slab<NT, 2, false>(p, columns, st);
+}
+
+template <class PP>
+hipError_t launch_any(const PP& p, float columns, hipStream_t st)
 {
     const int nt = nt_for(p.max_rank);
-    const bool wide = (float)p.max_rank * (float)p.proj0.d_out >= kPartsFromB;
-    if ((p.n_tokens <= 4096 && !wide) || nt == 8)
-        return nt == 1 ? launch_slab<1, 2>(p, all, st) : nt == 2 ? launch_slab<2, 2>(p, all, st)
-             : nt == 4 ? launch_slab<4, 2>(p, all, st) : launch_slab<8, 2>(p, all, st);
-    return nt == 1   ? launch_slab<1, 4>(p, all, st)
-           : nt == 2 ? launch_slab<2, 4>(p, all, st)
-                     : launch_slab<4, 4>(p, all, st);
+    return nt == 1 ? launch_rank<1>(p, columns, st) : nt == 2 ? launch_rank<2>(p, columns, st)
+         : nt == 4 ? launch_rank<4>(p, columns, st) : launch_rank<8>(p, columns, st);
 }
 
 }  // namespace
 
 hipError_t run_slab(const FwdParams& p, hipStream_t st, const SlabFrag* frag)
 {
-    const int nt = nt_for(p.max_rank);
-    if (p.n_proj > 1)
-        return nt == 1 ? launch_slab<1, 2>(p, p, st) : nt == 2 ? launch_slab<2, 2>(p, p, st)
-             : nt == 4 ? launch_slab<4, 2>(p, p, st) : launch_slab<8, 2>(p, p, st);
-    if (!frag) return launch_single(static_cast<const FwdCore&>(p), p, st);
+    float columns = (float)p.proj0.d_out;
+    for (int k = 1; k < p.n_proj; ++k) columns += (float)p.more[k - 1].d_out;
+    if (p.n_proj > 1) return launch_any(p, columns, st);
+    if (!frag) return launch_any(static_cast<const FwdCore&>(p), columns, st);
     FwdFrag q;
     static_cast<FwdCore&>(q) = p;
     q.frag = *frag;
-    return launch_single(q, p, st);
+    return launch_any(q, columns, st);
 }
 
 }  // namespace lq

@@ -723,6 +723,49 @@ def test_tall_slabs_beyond_the_cached_segments(oracle_mod):
     check_forward(oracle_mod, p, lq.LQ_VARIANT_SLAB)
 
 
+def forward_against_64_bits(ranks, lens, T, d_in, d_outs, variant, seed):
+    """One call on random operands (segments of the given rows, the rest without an adapter, kinds and rows shuffled), y and the saved h
+    compared with 64 bits; the kernels that ran."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+    n, order = len(lens), torch.randperm(T, generator=torch.Generator().manual_seed(T))
+    ta = torch.full((T,), -1, dtype=torch.int32)
+    ta[: sum(lens)] = torch.repeat_interleave(torch.arange(n, dtype=torch.int32), torch.tensor(lens))
+    ta, tk = ta[order], (torch.arange(T) * 7 % 3).to(torch.uint8)[order]
+    scales = [0.5 + 0.125 * a for a in range(n)]
+    ads = [lq.AdapterTable.from_tensors([new(r, d_in, d_in ** -0.5) for r in ranks], [new(r, d, 0.1) for r in ranks], scales) for d in d_outs]
+    top = ads[0].max_rank
+    x, ys = new(T, d_in, 1.0), [new(T, d, 1.0) for d in d_outs]
+    wants = [y.double() for y in ys]
+    seg = lq.SegmentTables.empty(T, n)
+    lq.lora_build_segments(ta.cuda(), tk.cuda(), ads[0].ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, n)))
+    hs = [torch.full((T * top,), float("nan"), device="cuda") for _ in d_outs]
+    ws = lq.workspace(lq.lora_forward_group_workspace_bytes(len(d_outs), T, top))
+    lq.lora_profile_enable(True)
+    if len(ys) == 1:
+        lq.lora_segmented_forward(x, ys[0], ads[0], seg, hs[0], ws, variant)
+    else:
+        lq.lora_segmented_forward_group(x, ys, ads, seg, hs, ws, variant)
+    ran = [name for name, (_, k) in lq.lora_profile_read().items() if k]
+    lq.lora_profile_enable(False)
+    lq.raise_on_device_error(ws)
+    rows = [torch.nonzero(ta == a).flatten().cuda() for a in range(-1, n)]
+    for ad, y, want, saved in zip(ads, ys, wants, hs):
+        at = 0
+        for a in range(n):
+            r = rows[a + 1]
+            h = x[r].double() @ ad.A[a].double().T
+            want[r] += scales[a] * (h @ ad.B[a].double())
+            ft = h[(tk[r.cpu()] == 0).cuda()]
+            assert rel_frobenius(saved[at: at + ft.numel()].view_as(ft).cpu().numpy(), ft.cpu().numpy()) <= 1e-4, a
+            at += ft.numel()
+        assert bool(torch.isnan(saved[at:]).all())
+        for a in range(-1, n):
+            r = rows[a + 1]
+            assert rel_frobenius(y[r].double().cpu().numpy(), want[r].cpu().numpy()) <= (REL_FROBENIUS if a >= 0 else 0.0), a
+    return ran
+
+
 @pytest.mark.parametrize("rank,T,d_in,d_out,kernel", [
     (64, 2047, 72, 136, "fused"), (64, 2048, 72, 136, "slab"),                    # tokens
     (64, 2100, 72, 16384, "slab"), (64, 2100, 72, 16392, "fused"), (16, 2600, 64, 16392, "fused"), (32, 4100, 128, 16392, "fused"),
@@ -733,40 +776,24 @@ def test_tall_slabs_beyond_the_cached_segments(oracle_mod):
 def test_forms_of_the_fused_variant(rank, T, d_in, d_out, kernel):
     """Either side of every line between the fused variant's two forms (single calls): which kernel ran, and y and the saved h
     against 64 bits, on long segments, short ones and rows without an adapter, in shuffled order."""
-    gen = torch.Generator(device="cuda").manual_seed(T + d_in + d_out)
-    new = lambda r, c, std: torch.empty(r, c, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
     lens = [T // 3, T // 4, 1, 15, 16, 17, 31, 33, 63, 65, 127, 129, 300]
-    n, order = len(lens), torch.randperm(T, generator=torch.Generator().manual_seed(T))
-    ta = torch.full((T,), -1, dtype=torch.int32)
-    ta[: sum(lens)] = torch.repeat_interleave(torch.arange(n, dtype=torch.int32), torch.tensor(lens))
-    ta, tk = ta[order], (torch.arange(T) * 7 % 3).to(torch.uint8)[order]
-    ranks = [rank if a % 3 else max(1, rank // 2 - 3) for a in range(n)]
-    A, B = [new(r, d_in, d_in ** -0.5) for r in ranks], [new(r, d_out, 0.1) for r in ranks]
-    ad = lq.AdapterTable.from_tensors(A, B, [0.5 + 0.125 * a for a in range(n)])
-    x, y = new(T, d_in, 1.0), new(T, d_out, 1.0)
-    want = y.double()
-    seg = lq.SegmentTables.empty(T, n)
-    lq.lora_build_segments(ta.cuda(), tk.cuda(), ad.ranks, seg, lq.workspace(lq.lora_build_workspace_bytes(T, n)))
-    h = torch.full((T * rank,), float("nan"), device="cuda")
-    ws = lq.workspace(lq.lora_forward_workspace_bytes(T, ad.max_rank, d_in, d_out, lq.LQ_VARIANT_FUSED))
-    lq.lora_profile_enable(True)
-    lq.lora_segmented_forward(x, y, ad, seg, h, ws, lq.LQ_VARIANT_FUSED)
-    ran = [name for name, (_, k) in lq.lora_profile_read().items() if k]
-    lq.lora_profile_enable(False)
-    lq.raise_on_device_error(ws)
-    assert ran == ["forward_" + kernel]
-    at = 0
-    for a in range(n):
-        rows = torch.nonzero(ta == a).flatten().cuda()
-        hs = x[rows].double() @ A[a].double().T
-        want[rows] += (0.5 + 0.125 * a) * (hs @ B[a].double())
-        ft = hs[(tk[rows.cpu()] == 0).cuda()]
-        assert rel_frobenius(h[at: at + ft.numel()].view_as(ft).cpu().numpy(), ft.cpu().numpy()) <= 1e-4, a
-        at += ft.numel()
-    for a in range(-1, n):
-        rows = torch.nonzero(ta == a).flatten().cuda()
-        assert rel_frobenius(y[rows].double().cpu().numpy(), want[rows].cpu().numpy()) <= (REL_FROBENIUS if a >= 0 else 0.0), a
-    assert bool(torch.isnan(h[at:]).all())
+    ranks = [rank if a % 3 else max(1, rank // 2 - 3) for a in range(len(lens))]
+    assert forward_against_64_bits(ranks, lens, T, d_in, [d_out], lq.LQ_VARIANT_FUSED, T + d_in + d_out) == ["forward_" + kernel]
+
+
+@pytest.mark.parametrize("rank,lens,T,d_in,d_outs", [
+    # 32-row chunks that just fit one round of 256 units (two row tiles), and that just do not (four)
+    (16, [8159], 8160, 64, [72]), (16, [8191], 8192, 64, [72]), (32, [2700, 2700, 2590], 7999, 72, [136]), (32, [2800, 2800, 2700], 8330, 72, [136]),
+    (64, [4096], 4096, 72, [136]), (64, [4097], 4097, 72, [136]),
+    # y non-temporal from 42 million elements on: long batches, groups, wide layers
+    (16, [3000, 1200, 33], 4864, 4312, [4312]), (16, [3000, 1200, 33], 4864, 4320, [4320]), (32, [9000], 9100, 2312, [2312]), (64, [6000, 17], 6100, 3448, [3448]),
+    (128, [5000, 40], 5100, 4120, [4120]), (16, [2000, 33], 2100, 2056, [8968, 8976]), (32, [2000, 33], 2100, 2056, [8968, 8968]), (64, [1000], 1100, 2056, [36128]),
+    (16, [30, 9], 40, 4096, [18760]), (32, [300, 200], 700, 1024, [14336]),   # wide, few rows
+])
+def test_slab_kernels_by_size(rank, lens, T, d_in, d_outs):
+    """Either side of the host's choices between the slab kernels: row tiles and the policy for y."""
+    ranks = [rank, max(1, rank - 5), rank // 2][: len(lens)]
+    assert forward_against_64_bits(ranks, lens, T, d_in, d_outs, lq.LQ_VARIANT_SLAB, T + d_in) == ["forward_slab"]
 
 
 @pytest.mark.parametrize("rank,T,d_in", [(16, 9000, 72), (16, 12000, 200), (32, 9000, 264), (32, 12000, 520), (32, 16384, 136), (8, 20000, 1032)])
