@@ -253,8 +253,9 @@ lq_status lora_segmented_forward_static(const void* x, int64_t ldx, void* y, int
  *            Other values: LQ_ERR_INVALID_ARG.
  *   workspace lora_backward_workspace_bytes(...) bytes; its first 4096 bytes zero as for the forward.
  *   Then the weight gradients: small and medium batches take whole segments and accumulate straight into dA / dB;
- *   in the others a fine-tune segment of more than 512 rows (1024 in wide layers) is cut into row chunks whose partial
- *   sums go to the workspace and are added in chunk order by one more launch (skipped for batches of up to a chunk).
+ *   in the others a fine-tune segment of more than 512 rows (1024 where there are many fine-tune rows) is cut into row
+ *   chunks whose partial sums go to the workspace and are added in chunk order by one more launch (skipped for batches of
+ *   up to 512 tokens).
  *   dA / dB are accumulated with fp32 additions in memory (plain device allocations, not fine-grained
  *   host-visible memory), one addition per element and fine-tune segment, and every other sum has a fixed
  *   order: results are reproducible run to run when every adapter has at most one fine-tune segment

@@ -30,7 +30,7 @@
 namespace lq {
 namespace {
 
-constexpr int kWgRows = 512;    // token rows per weight-gradient unit (wide layers of long batches: twice as many)
+constexpr int kWgRows = 512;    // token rows per weight-gradient unit (where those are more than a round of the grid: twice as many)
 constexpr int kWgCols = 256;    // columns per unit (8 waves x 32)
 constexpr int kWgTiles = kWgCols / (8 * 16);  // 16-column MFMA tiles per wave
 
@@ -53,7 +53,7 @@ struct BwdParams {
     int rstride;
     const u16* frag_g; const u16* frag_h;  // g and h as MFMA operands (see frag_at); frag_tiles 16-rank tiles per step
     int frag_tiles;
-    int wg_rows;         // token rows per weight-gradient unit (for the reduction; the units' kernel knows them)
+    int wg_slots;        // > 0: units of 1024 rows where those of 512 rows are more than wg_slots, see unit_rows
     float* wpart;        // [chunk of a segment with more than wg_rows rows][rstride][d_out + d_in] partial weight gradients
     int* err;
 };
@@ -417,19 +417,27 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_whole_kernel(BwdParams p)
     }
 }
 
-// (ranks up to 32: at most 128 registers, so that two workgroups share a compute unit and one's loads
-// overlap the other's barriers)
-// the fine-tune segments with more than 512 rows are cut into chunks (partials, then the reduction); the shorter
+// the fine-tune segments with more rows than a unit are cut into chunks (partials, then the reduction); the shorter
 // ones are one unit per column block
 __device__ __forceinline__ LenClass cut_class(int rows) { return LenClass{rows + 1, kBig, 1 << LQ_SEG_FINETUNE}; }
 __device__ __forceinline__ LenClass whole_class(int rows) { return LenClass{1, rows + 1, 1 << LQ_SEG_FINETUNE}; }
 
-template <int NT, int ROWS>
-__global__ __launch_bounds__(kThreads, NT <= 2 ? 4 : 2) void wgrad_kernel(BwdParams p)
+// Token rows per unit, from the fine-tune rows that the tables hold (the batch's tokens are no measure of them).  1024 where units of 512 rows are
+// more than one round of the grid (ranks up to 32: two workgroups per compute unit, 512 units): half the partials.  us of the units
+// and of the reduction, 512 and 1024 rows, rank 32: 4096 -> 14336, 4096 rows (576 units) 50.2 and 48.1, 6144 rows (864) 61.4 and 54.5,
+// 8192 (1152) 82.8 and 86.3, 12000 (1728) 114.7 and 109.9; 4096 -> 11008, 6144 rows (708) 50.3 and 49.9, 8192 (944) 67.3 and 60.7; below,
+// the machine is not full: 4096 -> 4096, 2048 rows (128) 19.4 and 29.1, 4096 (256) 24.2 and 32.8, 4096 -> 11008, 4096 rows (472) 36.7 and 36.8.
+__device__ __forceinline__ int unit_rows(const BwdParams& p, int n_seg, const SegCache& c0)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    int n_seg;
-    const SegCache c0 = load_seg_cache(p, n_seg);
+    if (p.wg_slots == 0) return kWgRows;
+    const int per_chunk = (p.d_out + kWgCols - 1) / kWgCols + (p.d_in + kWgCols - 1) / kWgCols;
+    const int chunks = count_chunks(p, n_seg, c0, kWgRows, LenClass{1, kBig, 1 << LQ_SEG_FINETUNE});
+    return chunks * per_chunk > p.wg_slots ? 2 * kWgRows : kWgRows;
+}
+
+template <int NT, int ROWS>
+__device__ __forceinline__ void wgrad_units(const BwdParams& p, int n_seg, const SegCache& c0, unsigned char* lds)
+{
     const LenClass cut = cut_class(ROWS), whole = whole_class(ROWS);
     const int blocks_b = (p.d_out + kWgCols - 1) / kWgCols, blocks_a = (p.d_in + kWgCols - 1) / kWgCols;
     const int per_chunk = blocks_b + blocks_a;
@@ -448,8 +456,22 @@ __global__ __launch_bounds__(kThreads, NT <= 2 ? 4 : 2) void wgrad_kernel(BwdPar
         if (for_b ? (p.dB_ptrs == nullptr || p.dB_ptrs[u.ad] == nullptr) : (p.dA_ptrs == nullptr || p.dA_ptrs[u.ad] == nullptr))
             continue;
         const float scale = p.token_scales ? 1.f : p.scales[u.ad];  // (per-token scales were applied row by row)
-        wgrad_unit<NT, ROWS>(p, u, rank, scale, is_cut ? chunk_id : -1, for_b, for_b ? cb : cb - blocks_b, lds_raw);
+        wgrad_unit<NT, ROWS>(p, u, rank, scale, is_cut ? chunk_id : -1, for_b, for_b ? cb : cb - blocks_b, lds);
     }
+}
+
+// (ranks up to 32: at most 128 registers, so that two workgroups share a compute unit and one's loads
+// overlap the other's barriers)
+// EITHER: units of 512 or 1024 rows.  (A number of rows known at run time only slowed the units down: backward of a decoder layer
+// 512 -> 526 us.)
+template <int NT, bool EITHER>
+__global__ __launch_bounds__(kThreads, NT <= 2 ? 4 : 2) void wgrad_kernel(BwdParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    int n_seg;
+    const SegCache c0 = load_seg_cache(p, n_seg);
+    if (EITHER && unit_rows(p, n_seg, c0) > kWgRows) wgrad_units<NT, (EITHER ? 2 * kWgRows : kWgRows)>(p, n_seg, c0, lds_raw);  // grid uniform
+    else wgrad_units<NT, kWgRows>(p, n_seg, c0, lds_raw);
 }
 
 // dA / dB += scale * (sum of a cut segment's chunk partials, in chunk order).  One unit = the first chunk of
@@ -461,19 +483,20 @@ __global__ __launch_bounds__(kThreads) void wreduce_kernel(BwdParams p)
 {
     int n_seg;
     const SegCache c0 = load_seg_cache(p, n_seg);
-    const LenClass cut = cut_class(p.wg_rows);
+    const int rows = unit_rows(p, n_seg, c0);
+    const LenClass cut = cut_class(rows);
     const int dsum = p.d_out + p.d_in;
     const int col_blocks = (dsum + kThreads - 1) / kThreads;
     const int rank_groups = (p.max_rank + kRedRanks - 1) / kRedRanks;
     const int per_chunk = col_blocks * rank_groups;
-    const int n_units = count_chunks(p, n_seg, c0, p.wg_rows, cut) * per_chunk;
+    const int n_units = count_chunks(p, n_seg, c0, rows, cut) * per_chunk;
     for (int id = (int)blockIdx.x; id < n_units; id += (int)gridDim.x) {
         Unit u;
         const int chunk_id = small_div(id, per_chunk), sub = id - chunk_id * per_chunk;
-        if (!find_chunk(p, n_seg, c0, chunk_id, p.wg_rows, cut, u)) continue;
+        if (!find_chunk(p, n_seg, c0, chunk_id, rows, cut, u)) continue;
         if (u.pos != u.first) continue;  // only the segment's first chunk adds up the segment
         if (u.ad < 0 || u.ad >= p.n_adapters) continue;
-        const int n_chunks = (u.seg_len + p.wg_rows - 1) / p.wg_rows;
+        const int n_chunks = (u.seg_len + rows - 1) / rows;
         const int j0 = (sub / col_blocks) * kRedRanks;
         const int col = (sub % col_blocks) * kThreads + (int)threadIdx.x;
         if (col >= dsum) continue;
@@ -539,23 +562,19 @@ size_t wpart_bytes(int n_tokens, int max_rank, int d_in, int d_out)
     return chunks * (size_t)rstride_for(max_rank) * ((size_t)d_in + d_out) * sizeof(float);
 }
 
-template <int NT, int ROWS = kWgRows>
-hipError_t launch_wgrad(const BwdParams& p, hipStream_t st)
+template <int NT, bool EITHER>
+int wgrad_grid()
 {
     static DeviceGrid cache;
-    constexpr size_t lds = WgCfg<NT, ROWS>::LDS_BYTES;
-    const int grid = cache.get([] {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (lds > 48 * 1024)
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_kernel<NT, ROWS>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        (void)hipGetDevice(&dev);
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, wgrad_kernel<NT, ROWS>, kThreads, lds) != hipSuccess || per_cu <= 0)
-            per_cu = 1;
-        return cus * per_cu;
-    });
-    return launch_kernel(kKernelWgrad, wgrad_kernel<NT, ROWS>, dim3(grid), dim3(kThreads), lds, st, p);
+    return cache.get([] { return resident_grid(wgrad_kernel<NT, EITHER>, WgCfg<NT, EITHER ? 2 * kWgRows : kWgRows>::LDS_BYTES); });
+}
+template <int NT, bool EITHER>
+hipError_t launch_wgrad(BwdParams& p, hipStream_t st)
+{
+    constexpr size_t lds = WgCfg<NT, EITHER ? 2 * kWgRows : kWgRows>::LDS_BYTES;
+    const int grid = wgrad_grid<NT, EITHER>();
+    p.wg_slots = EITHER ? grid : 0;
+    return launch_kernel(kKernelWgrad, wgrad_kernel<NT, EITHER>, dim3(grid), dim3(kThreads), lds, st, p);
 }
 
 template <int NT>
@@ -683,17 +702,15 @@ extern "C" lq_status lora_segmented_backward(const void* x, int64_t ldx, const v
                                : tiles == 4 ? launch_whole<4>(b, st) : launch_whole<8>(b, st);
             return e == hipSuccess ? LQ_OK : LQ_ERR_HIP;
         }
-        // 1024-row units where 512-row ones are well above one round of the grid (two workgroups per compute unit up to rank 32): half
-        // the partials, and no second round for a few units.  2048 + 2048 rows of rank 32, us of the units and of the reduction with
-        // 512 and 1024 rows: 4096 -> 14336 40.2 + 9.6 and 39.9 + 7.6, 14336 -> 4096 42.9 + 9.6 and 43.1 + 7.7; below, the machine is not full: 4096 -> 4096 17.6 + 5.1 and 26.5 + 4.6.
-        const bool tall = max_rank <= 32 && (n_tokens + kWgRows - 1ll) / kWgRows * (((long long)d_in + d_out) / kWgCols) > 600;
-        b.wg_rows = tall ? 2 * kWgRows : kWgRows;
-        const hipError_t e = tall ? (max_rank <= 16 ? launch_wgrad<1, 2 * kWgRows>(b, st) : launch_wgrad<2, 2 * kWgRows>(b, st))
-                           : max_rank <= 16 ? launch_wgrad<1>(b, st) : max_rank <= 32 ? launch_wgrad<2>(b, st)
-                           : max_rank <= 64 ? launch_wgrad<4>(b, st) : launch_wgrad<8>(b, st);
+        // (the tokens bound the fine-tune rows; the kernel that can do both starts 0.5 to 1 us later)
+        const long long most_units = (n_tokens + kWgRows - 1ll) / kWgRows * (((long long)d_in + d_out) / kWgCols);
+        const bool either = max_rank <= 32 && most_units > (max_rank <= 16 ? wgrad_grid<1, true>() : wgrad_grid<2, true>());
+        const hipError_t e = max_rank <= 16   ? either ? launch_wgrad<1, true>(b, st) : launch_wgrad<1, false>(b, st)
+                             : max_rank <= 32 ? either ? launch_wgrad<2, true>(b, st) : launch_wgrad<2, false>(b, st)
+                             : max_rank <= 64 ? launch_wgrad<4, false>(b, st) : launch_wgrad<8, false>(b, st);
         if (e != hipSuccess) return LQ_ERR_HIP;
-        // (no segment of a batch of up to wg_rows tokens is cut into chunks: nothing to reduce)
-        if (n_tokens > b.wg_rows && launch_kernel(kKernelWreduce, wreduce_kernel, dim3(512), dim3(kThreads), 0, st, b) != hipSuccess)
+        // (no segment of a batch of up to 512 tokens is cut into chunks: nothing to reduce)
+        if (n_tokens > kWgRows && launch_kernel(kKernelWreduce, wreduce_kernel, dim3(512), dim3(kThreads), 0, st, b) != hipSuccess)
             return LQ_ERR_HIP;
     }
     return LQ_OK;

@@ -71,7 +71,8 @@ __device__ __forceinline__ void unpack8(const u32x4& w, float* f)
 __device__ __forceinline__ void split_value(float v, unsigned int& hi, unsigned int& lo)
 {
     hi = pack_bf16x2(v, 0.f) & 0xffffu;
-    lo = (hi & 0x7fffu) == 0x7f80u ? 0u : pack_bf16x2(v - bf16_lo(hi), 0.f) & 0xffffu;
+    const float rest = v - bf16_lo(hi);
+    lo = pack_bf16x2(fabsf(rest) < __builtin_inff() ? rest : 0.f, 0.f) & 0xffffu;
 }
 
 // LDS that belongs to one wave: what its lanes have written is there for all of them

@@ -442,3 +442,23 @@ def test_saved_h_is_read_where_dB_is_wanted_only(table):
         assert rel_frobenius(dx[rows].double().cpu().numpy(), (g @ A[a].double()).cpu().numpy()) <= 5e-3
     if table:
         assert rel_frobenius(dB.cpu().numpy(), (h.view(40, rank).double().T @ dy[:40].double()).cpu().numpy()) <= WGRAD_REL_FROBENIUS
+
+
+@pytest.mark.parametrize("rank", [16, 32])
+@pytest.mark.parametrize("live,tall", [(600, False), (2600, False), (3000, True), (8200, True)])
+def test_rows_per_weight_gradient_unit_go_by_the_fine_tune_rows(rank, live, tall):
+    """8200 tokens of a 4096 -> 14336 layer (72 column blocks), some of them fine-tune rows: units of 1024 rows where those of 512 are
+    more than the 512 that run at once.  The workspace's partials, one per chunk of a cut segment, show which ran."""
+    T, d_in, d_out = 8200, 4096, 14336
+    lens = [600] + ([live - 640, 40] if live > 600 else [])
+    lens += [T - live] if T > live else []
+    n_ft = 1 if live == 600 else 3
+    tk = torch.repeat_interleave(torch.tensor([0] * n_ft + [2] * (len(lens) - n_ft), dtype=torch.uint8), torch.tensor(lens))
+    ta = torch.repeat_interleave(torch.arange(len(lens), dtype=torch.int32), torch.tensor(lens))
+    ran, ws = backward_against_64_bits([rank] * len(lens), [0.5, 1.0, 2.0, 1.5][: len(lens)], ta, tk, d_in, d_out, lq.LQ_VARIANT_SLAB, live)
+    assert "wgrad" in ran and "wreduce" in ran
+    # the partials: [chunk][32 ranks][d_out + d_in] at the workspace's end, room for twice ceil(T / 512) chunks
+    partials = ws.view(torch.float32)[-2 * 17 * 32 * (d_in + d_out):].view(34, 32, d_out + d_in)
+    written = int((~torch.isnan(partials[:, :rank]).flatten(1).all(1)).sum())
+    rows = 1024 if tall else 512
+    assert written == sum(-(-n // rows) for n in lens[:n_ft] if n > rows)
