@@ -216,14 +216,19 @@ __device__ __forceinline__ void wgrad_unit(const BwdParams& p, const Unit& u, in
 
 // =================================================================================================
 // Whole segments: behind the slab kernel, which leaves g and h as ready-made operands (frag_at), a unit takes ALL rows of
-// a segment x 64 columns, so that there are no partials and no reduction launch.  The 8 waves take alternate 32-position
-// steps: the step's rows of dy or x (8 rows x 128 bytes per instruction) go through LDS of the wave's own and come back
+// a segment x 64 to 512 columns, so that there are no partials and no reduction launch.  The 8, 4, 2 or 1 waves that share 64
+// columns take alternate 32-position steps: the step's rows of dy or x (8 rows x 128 bytes per instruction) go through LDS of the wave's own and come back
 // transposed, the operands of h or g come straight from memory (L2: every unit of a segment reads them).  No workgroup
-// barrier in the loop; the waves' results are added up at the end in a fixed order.
+// barrier in the loop; the results of the waves that share columns are added up at the end in a fixed order.
 // What bounds it: a unit's fixed part (tables, adapter, first loads, the sum over the waves, about 5 us) and, in long segments,
 // the column walk; so two steps in flight per wave and few registers do better than four (2048 + 2048 rows of rank 32,
 // 4096 -> 4096: 20.5 us instead of 24; with h as 32-bit rows that every unit splits for itself 21.4, with 144 columns per unit
 // 22.1).  2 x 1024 rows of rank 8: 13.1 + 4.1 us with chunks and reduction, 9.7 whole (3.5 TB/s).
+//   Columns per unit: a compute unit holds one workgroup (192 registers at rank 32), so more 64-column units than compute units are
+// a second round, whose fixed parts several short segments do not repay.  So 128, 256 or 512 columns, the fewest that fit one
+// round: us of the backward call with chunks, with 64 columns, and now, rank 32, 4096 -> 4096: 4 segments of 62 rows 20.3, 22.5, 20.7, 16
+// of 31 rows 31.2, 42.5, 31.3, 40 of 25 rows 54.5, 85.3, 53.3, 4 of 500 rows 36.4, 33.4, 31.2; 4096 -> 11008, 4 of 125 rows 34.6,
+// 40.6, 34.3; rank 8, 4096 -> 14336, 16 of 12 rows 29.6, 63.2, 33.0 (the worst); 490 calls: 0.90 of the time with chunks on average.
 // =================================================================================================
 constexpr int kWholeCols = 64;  // columns of a unit: a 128-byte line of a row
 constexpr int kWholeTiles = kWholeCols / 16;
@@ -238,8 +243,9 @@ constexpr size_t kWholeWaveBytes = 32 * kWave * sizeof(float);   // LDS of a wav
 static_assert((size_t)kStepRows * kWholePitch * sizeof(u16) <= kWholeWaveBytes, "a step's rows fit");
 constexpr size_t kWholeLdsBytes = kWaves * kWholeWaveBytes;
 
-// NT: 16-rank tiles of this unit, from rank j0 on
-template <int NT>
+// NT: 16-rank tiles of this unit, from rank j0 on; SHARE: so many waves share 64 columns, in alternate steps; the unit has
+// kWaves / SHARE x 64 columns
+template <int NT, int SHARE>
 __device__ __forceinline__ void whole_unit(const BwdParams& p, int begin, int end, int rank, float scale, bool for_b, int col_block,
                                            int j0, float* dst, unsigned char* lds)
 {
@@ -250,16 +256,16 @@ __device__ __forceinline__ void whole_unit(const BwdParams& p, int begin, int en
     const u16* Y = for_b ? p.dy : p.x;
     const long long ldy = for_b ? p.lddy : p.ldx;
     const int d = for_b ? p.d_out : p.d_in;
-    const int n0 = col_block * kWholeCols;
+    const int group = w / SHARE, member = w % SHARE, n0 = (col_block * (kWaves / SHARE) + group) * kWholeCols;
     const bool col_live = n0 + piece * 8 < d;
     const u16* ycol = Y + min(n0 + piece * 8, d - 8);
     typedef const __attribute__((address_space(1))) u32x4* gfrag;
     const gfrag frag = (gfrag)reinterpret_cast<const u32x4*>(for_b ? p.frag_h : p.frag_g) + (j0 >> 4) * 2 * kWave + lane;
     u16* ly = reinterpret_cast<u16*>(lds + (size_t)w * kWholeWaveBytes);
 
-    const int s0 = (begin >> 5) + w, total = ((end + 31) >> 5) - (begin >> 5);
-    const int n_mine = w < total ? (total - w + kWaves - 1) / kWaves : 0;  // steps w, w + 8, ...
-    auto step_at = [&](int j) { return s0 + kWaves * min(j, n_mine - 1); };  // (past the end: the last step again)
+    const int s0 = (begin >> 5) + member, total = ((end + 31) >> 5) - (begin >> 5);
+    const int n_mine = member < total && n0 < d ? (total - member + SHARE - 1) / SHARE : 0;  // steps member, member + SHARE, ...
+    auto step_at = [&](int j) { return s0 + SHARE * min(j, n_mine - 1); };  // (past the end: the last step again)
 
     f32x4 acc[NT][kWholeTiles];
 #pragma unroll
@@ -348,28 +354,39 @@ __device__ __forceinline__ void whole_unit(const BwdParams& p, int begin, int en
             });
     }
 
-    // the sum over the waves, RED accumulator registers at a time: every wave parks its own, then thread (w, lane) adds the
-    // eight partial sums of registers w, w + 8, ... of lane `lane` as a balanced tree
-    float* red = reinterpret_cast<float*>(lds);
-    constexpr int PER_WAVE = C::RED * kWave;
+    auto add = [&](int reg, float sum) {
+        const int jj = j0 + (reg >> 4) * 16 + 4 * kg + (reg & 3), n = n0 + ((reg >> 2) & 3) * 16 + c;
+        if (jj < rank && n < d) unsafeAtomicAdd(dst + (long long)jj * d + n, scale * sum);  // (one addition per segment, see wgrad_unit)
+    };
+    if constexpr (SHARE == 1) {
 #pragma unroll
-    for (int part = 0; part < NT * 16 / C::RED; ++part) {
-        __syncthreads();  // the rows (or the previous part's sums) have been read
+        for (int reg = 0; reg < NT * 16; ++reg) add(reg, acc[reg >> 4][(reg >> 2) & 3][reg & 3]);
+    } else {
+        // the sum over the waves that share columns, RED accumulator registers at a time: every wave parks its own, then thread (w,
+        // lane) adds its group's partial sums of registers member, member + SHARE, ... of lane `lane` as a balanced tree
+        float* red = reinterpret_cast<float*>(lds);
+        constexpr int PER_WAVE = C::RED * kWave;
 #pragma unroll
-        for (int r = 0; r < C::RED; ++r) {
-            const int reg = part * C::RED + r;
-            red[w * PER_WAVE + r * kWave + lane] = acc[reg >> 4][(reg >> 2) & 3][reg & 3];
-        }
-        __syncthreads();
+        for (int part = 0; part < NT * 16 / C::RED; ++part) {
+            __syncthreads();  // the rows (or the previous part's sums) have been read
 #pragma unroll
-        for (int it = 0; it < C::RED / kWaves; ++it) {
-            const int r = it * kWaves + w, reg = part * C::RED + r;
-            float t[kWaves];
+            for (int r = 0; r < C::RED; ++r) {
+                const int reg = part * C::RED + r;
+                red[w * PER_WAVE + r * kWave + lane] = acc[reg >> 4][(reg >> 2) & 3][reg & 3];
+            }
+            __syncthreads();
 #pragma unroll
-            for (int ww = 0; ww < kWaves; ++ww) t[ww] = red[ww * PER_WAVE + r * kWave + lane];
-            const float sum = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-            const int jj = j0 + (reg >> 4) * 16 + 4 * kg + (reg & 3), n = n0 + ((reg >> 2) & 3) * 16 + c;
-            if (jj < rank && n < d) unsafeAtomicAdd(dst + (long long)jj * d + n, scale * sum);  // (one addition per segment, see wgrad_unit)
+            for (int it = 0; it < C::RED / SHARE; ++it) {
+                const int r = it * SHARE + member;
+                float t[SHARE];
+#pragma unroll
+                for (int ww = 0; ww < SHARE; ++ww) t[ww] = red[(group * SHARE + ww) * PER_WAVE + r * kWave + lane];
+#pragma unroll
+                for (int half = SHARE / 2; half > 0; half /= 2)
+#pragma unroll
+                    for (int ww = 0; ww < half; ++ww) t[ww] = t[2 * ww] + t[2 * ww + 1];
+                add(part * C::RED + r, t[0]);
+            }
         }
     }
     __syncthreads();  // before the next unit's rows
@@ -390,11 +407,18 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_whole_kernel(BwdParams p)
     constexpr int kWhole = 1 << 30;  // rows per unit: no segment is cut
     int n_seg;
     const SegCache c0 = load_seg_cache(p, n_seg);
-    const int blocks_b = (p.d_out + kWholeCols - 1) / kWholeCols, blocks_a = (p.d_in + kWholeCols - 1) / kWholeCols;
     constexpr int HALVES = NT >= 8 ? 2 : 1;
-    const int per_seg = (blocks_b + blocks_a) * HALVES;
-    const int n_long = count_chunks(p, n_seg, c0, kWhole, whole_segments(true)) * per_seg;
-    const int n_units = n_long + count_chunks(p, n_seg, c0, kWhole, whole_segments(false)) * per_seg;
+    const int segs_long = count_chunks(p, n_seg, c0, kWhole, whole_segments(true));
+    const int segs = segs_long + count_chunks(p, n_seg, c0, kWhole, whole_segments(false));
+    // columns per unit: 64 where the units fit one round of the grid, else the fewest up to 512 that do
+    int cols_log2 = 6, blocks_b, per_seg;
+    for (;; ++cols_log2) {
+        const int round_up = (1 << cols_log2) - 1;
+        blocks_b = (p.d_out + round_up) >> cols_log2;
+        per_seg = (blocks_b + ((p.d_in + round_up) >> cols_log2)) * HALVES;
+        if (cols_log2 == 9 || segs * per_seg <= (int)gridDim.x) break;
+    }
+    const int n_long = segs_long * per_seg, n_units = segs * per_seg;
     for (int id = (int)blockIdx.x; id < n_units; id += (int)gridDim.x) {
         Unit u;
         const int base = id < n_long ? 0 : n_long, seg = small_div(id - base, per_seg), at = id - base - seg * per_seg;
@@ -411,9 +435,16 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_whole_kernel(BwdParams p)
         const float scale = p.token_scales ? 1.f : adapter_scale;  // (per-token scales are in the operands)
         const int end = u.first + u.seg_len, block = for_b ? cb : cb - blocks_b;
         const int left = rank - j0;  // > 0
-        if (NT >= 4 && left > 32) whole_unit<(NT >= 4 ? 4 : NT)>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
-        else if (NT >= 2 && left > 16) whole_unit<(NT >= 2 ? 2 : NT)>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
-        else whole_unit<1>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
+        auto run = [&](auto tiles) {  // (all of this is workgroup uniform)
+            constexpr int N = decltype(tiles)::value;
+            if (cols_log2 == 6) whole_unit<N, 8>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
+            else if (cols_log2 == 7) whole_unit<N, 4>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
+            else if (cols_log2 == 8) whole_unit<N, 2>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
+            else whole_unit<N, 1>(p, u.first, end, rank, scale, for_b, block, j0, dst, lds_raw);
+        };
+        if (NT >= 4 && left > 32) run(std::integral_constant<int, (NT >= 4 ? 4 : NT)>{});
+        else if (NT >= 2 && left > 16) run(std::integral_constant<int, (NT >= 2 ? 2 : NT)>{});
+        else run(std::integral_constant<int, 1>{});
     }
 }
 
@@ -537,14 +568,15 @@ __global__ __launch_bounds__(kThreads) void wreduce_kernel(BwdParams p)
 }
 
 // Whole segments or 512-row chunks, by the host's arguments.  Measured on the backward call (g / dx, weight gradients and,
-// with chunks of batches above 512 tokens, their reduction), us with chunks and whole, fine-tune rows only:
-//   rank 32, 4096 -> 4096, in one segment and in four: 64 rows 18.7 and 16.1, 500 28.5 and 21.4 (one), 24.6 and 24.7 (four), 1000
-//   34.5 and 24.0, 31.5 and 26.8, 2000 38.3 and 30.6, 38.7 and 32.7, 4000 50.8 and 57.9, 52.9 and 52.4; 4096 -> 1024, 4000 rows 40.9
-//   and 38.3, 43.9 and 37.8; 1024 -> 1024, 2000 rows 29.9 and 23.0, 30.2 and 19.1.
-//   rank 64, 4096 -> 4096, 2000 rows 46.9 and 39.6, 50.3 and 43.4; 4096 -> 1024, 4000 rows 53.7 and 55.5, 57.5 and 56.1.
-//   rank 128, 4096 -> 4096, 1000 rows 58.4 and 43.0, 57.6 and 58.3; 500 rows in four segments are the worst, 47.6 and 53.7.
+// with chunks of batches above 512 tokens, their reduction) on three sets of operands in turn, us with chunks and whole, fine-tune
+// rows only, in one segment and in four:
+//   rank 32, 4096 -> 4096, 500 rows 27.1 and 20.7, 23.1 and 22.7, 2000 37.8 and 31.4, 36.4 and 31.2, 3500 51.5 and 45.7, 52.8 and 44.6;
+//   5632 67.8 and 70.0 (one segment); 4096 -> 1024, 3500 rows 39.7 and 36.4, 40.7 and 31.5, 5632 52.7 and 53.4 (one); 1024 -> 1024, 2000
+//   rows 29.5 and 22.6, 26.3 and 18.3; 4096 -> 14336, 1500 rows 49.0 and 49.0 (one), 2500 77.4 and 81.8 (one).
+//   rank 64, 4096 -> 4096, 2000 rows 48.3 and 41.0, 49.1 and 41.4; 4096 -> 1024, 4500 59.2 and 61.0 (one).
+//   rank 128, 4096 -> 4096, 500 rows 52.6 and 37.8, 48.2 and 48.6, 2000 67.8 and 51.4, 71.4 and 61.3; 16 segments of 31 rows 82.6 and 84.6.
 // Large batches lose because a unit walks down 64 columns, a line of every row, which streams slower from memory than 256
-// columns do; narrow layers of long segments because there are too few units.
+// columns do; narrow layers of one long segment because there are too few units (512 -> 512, rank 32, 5632 rows 32.2 and 35.7).
 bool whole_segments_win(int n_tokens, int max_rank, int d_in, int d_out)
 {
     const long long width = (long long)d_in + d_out;

@@ -462,3 +462,21 @@ def test_rows_per_weight_gradient_unit_go_by_the_fine_tune_rows(rank, live, tall
     written = int((~torch.isnan(partials[:, :rank]).flatten(1).all(1)).sum())
     rows = 1024 if tall else 512
     assert written == sum(-(-n // rows) for n in lens[:n_ft] if n > rows)
+
+
+@pytest.mark.parametrize("n,ranks", [(8, (32, 5)), (9, (16, 8)), (12, (32, 17)), (24, (8,)), (60, (16, 32)), (12, (64, 40, 8)), (24, (128, 16)), (60, (128, 64))])
+@pytest.mark.parametrize("shuffle", [False, True])
+def test_whole_segments_in_units_of_64_to_512_columns(n, ranks, shuffle):
+    """30 column blocks of 64 per segment: 8 segments fit one round of 256 workgroups in units of 64 columns, 9 to 60 take units
+    of 128, 256 and 512 (twice as many units above rank 64).  Widths that end inside a unit of every size."""
+    d_in, d_out = 1032, 776
+    lens = [(1, 90, 33, 40, 7, 30)[a % 6] + (260 if a == 1 and n < 60 else 0) for a in range(n)]
+    ta = torch.repeat_interleave(torch.arange(n, dtype=torch.int32), torch.tensor(lens))
+    tk = torch.zeros(len(ta), dtype=torch.uint8)
+    tk[torch.nonzero(ta % 5 == 3).flatten()[::2]] = 2                # some rows of some adapters are decode rows
+    if shuffle:
+        order = torch.randperm(len(ta), generator=torch.Generator().manual_seed(n))
+        ta, tk = ta[order], tk[order]
+    ran, _ = backward_against_64_bits([ranks[a % len(ranks)] for a in range(n)], [0.5 + 0.1 * (a % 9) for a in range(n)], ta, tk, d_in, d_out,
+                                      lq.LQ_VARIANT_SLAB, n, dA_skip=(2,), dB_skip=(1, 4))
+    assert sorted(ran) == ["forward_slab", "wgrad"]             # (no reduction: whole segments)
