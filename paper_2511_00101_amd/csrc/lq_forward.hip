@@ -462,7 +462,7 @@ struct LongAhead {
     u32x4 b[C::ROWS * (C::UN / 8) / kThreads];
 };
 
-template <int KSTEPS, int PAIRS, bool AHEAD, class PP>  // ranks up to 32 * KSTEPS; a wave covers 32 * PAIRS columns, a block 8 waves
+template <int KSTEPS, int PAIRS, bool AHEAD, bool STREAM, class PP>  // ranks up to 32 * KSTEPS; a wave covers 32 * PAIRS columns, a block 8 waves; STREAM: y non-temporal
 __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, const SegInfo& s, int nb_begin,
                                                  int nb_end, unsigned char* lds, const LongAhead<KSTEPS, PAIRS>& pre)
 {
@@ -576,7 +576,7 @@ __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, con
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             row_f[j] = lds_row[min(8 * j + (lane >> 3), C::CT - 1)];
-            y_f[j] = load_once<true>(pj.y + (long long)(row_f[j] >= 0 ? row_f[j] : safe) * pj.ldy + n_ld);
+            y_f[j] = load_once<STREAM>(pj.y + (long long)(row_f[j] >= 0 ? row_f[j] : safe) * pj.ldy + n_ld);
         }
     }
 #pragma unroll
@@ -611,9 +611,7 @@ __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, con
         // The products come out of the MFMA in that other layout, so every 16-row tile of them makes a round
         // trip through a 4 KB LDS slab of the wave (in the B block's space, free while y streams); the
         // 16-byte chunks of a slab row are XOR-swizzled with the row number against bank conflicts.
-        // Loads are unconditional (dead rows and columns read a live address); only the stores are masked.  y is touched once:
-        // non-temporal.  In the layer stack gate + up alone takes longer so (147 -> 163 us), but the launches behind it no longer pay
-        // for what it left to be written back (o, down and q+k+v 63 -> 56 us on average): a step 10.88 -> 10.69 ms.
+        // Loads are unconditional (dead rows and columns read a live address); only the stores are masked.
         float* slab = reinterpret_cast<float*>(lds_b) + w * (16 * 64);
         const int r8 = lane >> 3, piece = lane & 7;
         const int n_c = n_wave + 8 * piece, n_ld = min(n_c, pj.d_out - 8);
@@ -623,7 +621,7 @@ __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, con
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 row_n[j] = lds_row[min(step * 32 + 8 * j + r8, C::CT - 1)];
-                y_n[j] = load_once<true>(pj.y + (long long)(row_n[j] >= 0 ? row_n[j] : safe_row) * pj.ldy + n_ld);
+                y_n[j] = load_once<STREAM>(pj.y + (long long)(row_n[j] >= 0 ? row_n[j] : safe_row) * pj.ldy + n_ld);
             }
         };
 #pragma unroll
@@ -679,7 +677,7 @@ __device__ __forceinline__ void expand_long_unit(const PP& p, const Unit& u, con
                         o.y = pack_bf16x2(yf[2] + d0[2], yf[3] + d0[3]);
                         o.z = pack_bf16x2(yf[4] + d1[0], yf[5] + d1[1]);
                         o.w = pack_bf16x2(yf[6] + d1[2], yf[7] + d1[3]);
-                        store_once<true>(pj.y + (long long)row[j] * pj.ldy + n_c, o);
+                        store_once<STREAM>(pj.y + (long long)row[j] * pj.ldy + n_c, o);
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1153,7 +1151,7 @@ __device__ __forceinline__ LongAhead<KSTEPS, PAIRS> long_request(const PP& p, co
 }
 
 // AHEAD: this wave's first short unit and this workgroup's first long unit were requested into `ahead`, `lahead`
-template <int KSTEPS, int PAIRS, bool AHEAD, class PP>
+template <int KSTEPS, int PAIRS, bool AHEAD, bool STREAM, class PP>
 __device__ __forceinline__ void expand_phase(const PP& p, const Segs<PP>& sg, const ExpandPlan& e,
                                              unsigned char* lds_raw, ShortLds& sh, int* s_slot, const ShortAhead ahead,
                                              const LongAhead<KSTEPS, PAIRS> lahead)
@@ -1168,7 +1166,7 @@ __device__ __forceinline__ void expand_phase(const PP& p, const Segs<PP>& sg, co
         }
         if constexpr (AHEAD) {  // then the workgroup's first long unit (by now the short unit's registers are free)
             if (lahead.live)
-                expand_long_unit<KSTEPS, PAIRS, true>(p, lahead.u, lahead.s, lahead.nb_begin, lahead.nb_end, lds_raw, lahead);
+                expand_long_unit<KSTEPS, PAIRS, true, STREAM>(p, lahead.u, lahead.s, lahead.nb_begin, lahead.nb_end, lds_raw, lahead);
             __syncthreads();  // before the next long unit reuses the LDS
         }
         ShortAhead unused;
@@ -1191,12 +1189,12 @@ __device__ __forceinline__ void expand_phase(const PP& p, const Segs<PP>& sg, co
             SegInfo s;
             int nb_begin, nb_end;
             if (!find_long_unit(p, sg, e, id, u, s, nb_begin, nb_end)) return;
-            expand_long_unit<KSTEPS, PAIRS, false>(p, u, s, nb_begin, nb_end, lds_raw, none);
+            expand_long_unit<KSTEPS, PAIRS, false, STREAM>(p, u, s, nb_begin, nb_end, lds_raw, none);
         }, AHEAD ? 1 : 0);
     }
 }
 
-template <int KSTEPS, int PAIRS, bool GROUP>
+template <int KSTEPS, int PAIRS, bool STREAM, bool GROUP>
 __global__ __launch_bounds__(kThreads) void expand_kernel(KernelArg<GROUP> p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -1208,7 +1206,7 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(KernelArg<GROUP> p)
     none.live = false;
     LongAhead<KSTEPS, PAIRS> lnone;
     lnone.live = false;
-    expand_phase<KSTEPS, PAIRS, false>(p, sg, plan, lds_raw, sh, s_slot, none, lnone);
+    expand_phase<KSTEPS, PAIRS, false, STREAM>(p, sg, plan, lds_raw, sh, s_slot, none, lnone);
 }
 
 // =================================================================================================
@@ -1219,7 +1217,7 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(KernelArg<GROUP> p)
 // workspace error word instead of hanging.
 //   (header words: see kBarGen, kBarTop, kBarSub)
 // =================================================================================================
-template <int NT, int KSTEPS, int PAIRS, bool GROUP>
+template <int NT, int KSTEPS, int PAIRS, bool STREAM, bool GROUP>
 __global__ __launch_bounds__(kThreads) void fused_kernel(KernelArg<GROUP> p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -1242,7 +1240,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(KernelArg<GROUP> p)
     });
     // The wait ran out (somewhere): h is incomplete, so y is left as it is; bit 1 of the error word says so.
     if (!opened) return;
-    expand_phase<KSTEPS, PAIRS, true>(p, sg, plan, lds_raw, sh, s_slot, ahead, lahead);
+    expand_phase<KSTEPS, PAIRS, true, STREAM>(p, sg, plan, lds_raw, sh, s_slot, ahead, lahead);
 }
 
 int log2_of(int v)  // v is a power of two
@@ -1288,37 +1286,49 @@ hipError_t launch_shrink(const FwdParams& p, hipStream_t st)
     return launch_kernel(kKernelShrink, shrink_kernel<NT, true>, dim3(shrink_grid<NT>()), dim3(kThreads), shrink_lds_bytes<NT>(), st, p);
 }
 
-template <int KSTEPS, int PAIRS>
+// y (dx) non-temporal from 60 million elements of x and y on, see streams_y for the same choice in the slab kernels; only rows of whole
+// 128-byte lines.  Non-temporal over plain, 220 random calls of the fused variant on three sets of operands in turn, widths
+// multiples of 64, by million elements: 8 to 42 1.01 to 1.05, 42 to 60 0.99, 60 to 250 0.92 to 0.95 (with an elementwise writer of y in front
+// and a reader behind 6 to 15 % of the call more at 42 to 60 million, 1 to 8 at 60 to 80, 2 less from 110; multiples of 32 0.99 to 1.08 at any
+// size, other widths 1.10 to 1.45: lines written in parts).  us: rank 32, 4096 -> 2 x 14336, 1100 rows (36 M) 46.6 and 50.0, 4096 rows (134 M) 130
+// and 120, 5632 168 and 157; rank 16, 4096 -> 16392, 2600 rows (53 M) 63.6 and 78.5.  (Above rank 64 y is accessed in the MFMA's layout.)
+bool expand_streams_y(const FwdParams& p) { return whole_lines(p) && y_traffic(p) >= 60e6f; }
+
+template <int KSTEPS, int PAIRS, bool STREAM>
 hipError_t launch_expand(const FwdParams& p, hipStream_t st)
 {
     static DeviceGrid cache;
     constexpr size_t lds = ExpandCfg<KSTEPS, PAIRS>::LDS_BYTES;
     const int grid = cache.get([] {
-        return std::min(resident_grid(expand_kernel<KSTEPS, PAIRS, false>, lds), resident_grid(expand_kernel<KSTEPS, PAIRS, true>, lds));
+        return std::min(resident_grid(expand_kernel<KSTEPS, PAIRS, STREAM, false>, lds), resident_grid(expand_kernel<KSTEPS, PAIRS, STREAM, true>, lds));
     });
-    if (p.n_proj == 1) return launch_kernel(kKernelExpand, expand_kernel<KSTEPS, PAIRS, false>, dim3(grid), dim3(kThreads), lds, st, static_cast<const FwdCore&>(p));
-    return launch_kernel(kKernelExpand, expand_kernel<KSTEPS, PAIRS, true>, dim3(grid), dim3(kThreads), lds, st, p);
+    if (p.n_proj == 1) return launch_kernel(kKernelExpand, expand_kernel<KSTEPS, PAIRS, STREAM, false>, dim3(grid), dim3(kThreads), lds, st, static_cast<const FwdCore&>(p));
+    return launch_kernel(kKernelExpand, expand_kernel<KSTEPS, PAIRS, STREAM, true>, dim3(grid), dim3(kThreads), lds, st, p);
 }
 
-template <int NT, int KSTEPS, int PAIRS>
+// (the instantiations with y plain and non-temporal have the same registers and LDS as well)
+template <int NT, int KSTEPS, int PAIRS, bool STREAM>
 int fused_grid()
 {
     static DeviceGrid cache;
     constexpr size_t lds = shrink_lds_bytes<NT>() > ExpandCfg<KSTEPS, PAIRS>::LDS_BYTES ? shrink_lds_bytes<NT>()
                                                                                        : ExpandCfg<KSTEPS, PAIRS>::LDS_BYTES;
     return cache.get([] {
-        return std::min(resident_grid(fused_kernel<NT, KSTEPS, PAIRS, false>, lds), resident_grid(fused_kernel<NT, KSTEPS, PAIRS, true>, lds));
+        return std::min(resident_grid(fused_kernel<NT, KSTEPS, PAIRS, STREAM, false>, lds), resident_grid(fused_kernel<NT, KSTEPS, PAIRS, STREAM, true>, lds));
     });
 }
 
-template <int NT, int KSTEPS, int PAIRS>
-hipError_t launch_fused(const FwdParams& p, hipStream_t st)
+template <int NT, int KSTEPS, int PAIRS, bool STREAM = false>
+hipError_t launch_fused(FwdParams& p, hipStream_t st)
 {
+    const int grid = fused_grid<NT, KSTEPS, PAIRS, STREAM>();
+    p.ksplit = p.ksplit_hint > 0 ? p.ksplit_hint : choose_ksplit(p.n_tokens, p.n_proj, p.d_in, grid);
+    p.ks_log2 = log2_of(p.ksplit);
     const size_t lds = shrink_lds_bytes<NT>() > ExpandCfg<KSTEPS, PAIRS>::LDS_BYTES ? shrink_lds_bytes<NT>()
                                                                                    : ExpandCfg<KSTEPS, PAIRS>::LDS_BYTES;
     if (p.n_proj == 1)
-        return launch_kernel(kKernelFused, fused_kernel<NT, KSTEPS, PAIRS, false>, dim3(fused_grid<NT, KSTEPS, PAIRS>()), dim3(kThreads), lds, st, static_cast<const FwdCore&>(p));
-    return launch_kernel(kKernelFused, fused_kernel<NT, KSTEPS, PAIRS, true>, dim3(fused_grid<NT, KSTEPS, PAIRS>()), dim3(kThreads), lds, st, p);
+        return launch_kernel(kKernelFused, fused_kernel<NT, KSTEPS, PAIRS, STREAM, false>, dim3(grid), dim3(kThreads), lds, st, static_cast<const FwdCore&>(p));
+    return launch_kernel(kKernelFused, fused_kernel<NT, KSTEPS, PAIRS, STREAM, true>, dim3(grid), dim3(kThreads), lds, st, p);
 }
 
 }  // namespace
@@ -1402,12 +1412,13 @@ hipError_t run_shrink_expand(FwdParams& p, int variant, hipStream_t st, const Sl
     hipError_t e = hipSuccess;
     if (variant == LQ_VARIANT_FUSED && slab_form(p)) return run_slab(p, st, frag);
     if (variant == LQ_VARIANT_FUSED) {
-        const int grid_f = nt == 1 ? fused_grid<1, 1, 2>() : nt == 2 ? fused_grid<2, 1, 2>()
-                         : nt == 4 ? fused_grid<4, 2, 2>() : fused_grid<8, 4, 1>();
-        p.ksplit = p.ksplit_hint > 0 ? p.ksplit_hint : choose_ksplit(p.n_tokens, p.n_proj, p.d_in, grid_f);
-        p.ks_log2 = log2_of(p.ksplit);
-        return nt == 1 ? launch_fused<1, 1, 2>(p, st) : nt == 2 ? launch_fused<2, 1, 2>(p, st)
-             : nt == 4 ? launch_fused<4, 2, 2>(p, st) : launch_fused<8, 4, 1>(p, st);
+        if (nt == 8) return launch_fused<8, 4, 1>(p, st);
+        return expand_streams_y(p) ? nt == 1   ? launch_fused<1, 1, 2, true>(p, st)
+                                     : nt == 2 ? launch_fused<2, 1, 2, true>(p, st)
+                                               : launch_fused<4, 2, 2, true>(p, st)
+               : nt == 1           ? launch_fused<1, 1, 2>(p, st)
+               : nt == 2           ? launch_fused<2, 1, 2>(p, st)
+                                   : launch_fused<4, 2, 2>(p, st);
     }
     const int grid_s = nt == 1 ? shrink_grid<1>() : nt == 2 ? shrink_grid<2>() : nt == 4 ? shrink_grid<4>() : shrink_grid<8>();
     p.ksplit = p.ksplit_hint > 0 ? p.ksplit_hint : choose_ksplit(p.n_tokens, p.n_proj, p.d_in, grid_s);
@@ -1417,8 +1428,9 @@ hipError_t run_shrink_expand(FwdParams& p, int variant, hipStream_t st, const Sl
           : nt == 4 ? launch_shrink<4>(p, st) : launch_shrink<8>(p, st);
         if (e != hipSuccess || variant == LQ_VARIANT_SHRINK_ONLY) return e;
     }
-    return p.max_rank <= 32 ? launch_expand<1, 2>(p, st) : p.max_rank <= 64 ? launch_expand<2, 2>(p, st)
-                                                                            : launch_expand<4, 1>(p, st);
+    if (p.max_rank > 64) return launch_expand<4, 1, false>(p, st);
+    if (expand_streams_y(p)) return p.max_rank <= 32 ? launch_expand<1, 2, true>(p, st) : launch_expand<2, 2, true>(p, st);
+    return p.max_rank <= 32 ? launch_expand<1, 2, false>(p, st) : launch_expand<2, 2, false>(p, st);
 }
 
 }  // namespace lq

@@ -159,6 +159,29 @@ hipError_t run_slab(const FwdParams& p, hipStream_t stream, const SlabFrag* frag
 constexpr int kAllKinds = 7;
 constexpr int kFinetuneOnly = 1 << LQ_SEG_FINETUNE;
 
+inline float all_columns(const FwdParams& p)
+{
+    float columns = (float)p.proj0.d_out;
+    for (int k = 1; k < p.n_proj; ++k) columns += (float)p.more[k - 1].d_out;
+    return columns;
+}
+// elements of x and y that the call and what belongs to it touch (a backward call: dy, dx and, for the weight gradients, x)
+inline float y_traffic(const FwdParams& p)
+{
+    return (float)p.n_tokens * ((float)p.d_in + (p.kinds == kFinetuneOnly ? 2.f : 1.f) * all_columns(p));
+}
+// every row of y begins and ends with a 128-byte line.  (A line that two units write in parts goes to memory twice when its
+// stores are non-temporal.)
+inline bool whole_lines(const FwdParams& p)
+{
+    bool whole = true;
+    for (int k = 0; k < p.n_proj; ++k) {
+        const Proj& q = k == 0 ? p.proj0 : p.more[k - 1];
+        whole = whole && q.d_out % 64 == 0 && q.ldy % 64 == 0 && (reinterpret_cast<uintptr_t>(q.y) & 127u) == 0;
+    }
+    return whole;
+}
+
 // A launch grid that depends on the device (resident workgroups), worked out once per device: `compute` runs on
 // the first call on a device (two threads that race there store the same value).
 constexpr int kMaxDevices = 64;

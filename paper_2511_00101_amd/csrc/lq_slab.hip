@@ -210,42 +210,41 @@ bool tall_units(const PP& p, float columns)
 // either way: 4096 -> 4096 of rank 32, 5632 rows 1.4 us less than plain, 8192 rows 3.9 more, 16384 2.7 more (rank 16 5.1 more);
 // q+k+v, 4096 rows 1.7 less, 5632 0.9 more, 16384 4.7 less.
 //   (The same for x gains as much alone, nothing on top, and loses what the weight gradients find of dy in the cache: 41 -> 49 us.)
-template <class PP>
-bool streams_y(const PP& p, float columns)
+//   Only rows of whole 128-byte lines: 260 random calls, widths multiples of 64 0.92 to 0.99 of the plain policy from 42 million on, multiples
+// of 32 0.96 to 1.06 (but with a writer in front and a reader behind 3 to 37 % of the call more), other widths 1.14 to 1.75.
+bool streams_y(const FwdParams& p, float columns)
 {
-    const float width = (float)p.d_in + (p.kinds == kFinetuneOnly ? 2.f * columns : columns);
-    return (p.n_tokens > 4096 || p.n_proj > 1 || wide_layer(p, columns)) && (float)p.n_tokens * width >= 42e6f;
+    return (p.n_tokens > 4096 || p.n_proj > 1 || wide_layer(p, columns)) && y_traffic(p) >= 42e6f && whole_lines(p);
 }
 
 template <int NT, class PP>
-hipError_t launch_rank(const PP& p, float columns, hipStream_t st)
+hipError_t launch_rank(const PP& p, float columns, bool stream, hipStream_t st)
 {
-    const bool stream = streams_y(p, columns);
     if constexpr (NT < 8 && !std::is_same_v<PP, FwdParams>)
         if (tall_units<NT>(p, columns)) return stream ? launch_slab<NT, 4, true>(p, columns, st) : launch_slab<NT, 4, false>(p, columns, st);
     return stream ? launch_slab<NT, 2, true>(p, columns, st) : launch_slab<NT, 2, false>(p, columns, st);
 }
 
 template <class PP>
-hipError_t launch_any(const PP& p, float columns, hipStream_t st)
+hipError_t launch_any(const PP& p, float columns, bool stream, hipStream_t st)
 {
     const int nt = nt_for(p.max_rank);
-    return nt == 1 ? launch_rank<1>(p, columns, st) : nt == 2 ? launch_rank<2>(p, columns, st)
-         : nt == 4 ? launch_rank<4>(p, columns, st) : launch_rank<8>(p, columns, st);
+    return nt == 1 ? launch_rank<1>(p, columns, stream, st) : nt == 2 ? launch_rank<2>(p, columns, stream, st)
+         : nt == 4 ? launch_rank<4>(p, columns, stream, st) : launch_rank<8>(p, columns, stream, st);
 }
 
 }  // namespace
 
 hipError_t run_slab(const FwdParams& p, hipStream_t st, const SlabFrag* frag)
 {
-    float columns = (float)p.proj0.d_out;
-    for (int k = 1; k < p.n_proj; ++k) columns += (float)p.more[k - 1].d_out;
-    if (p.n_proj > 1) return launch_any(p, columns, st);
-    if (!frag) return launch_any(static_cast<const FwdCore&>(p), columns, st);
+    const float columns = all_columns(p);
+    const bool stream = streams_y(p, columns);
+    if (p.n_proj > 1) return launch_any(p, columns, stream, st);
+    if (!frag) return launch_any(static_cast<const FwdCore&>(p), columns, stream, st);
     FwdFrag q;
     static_cast<FwdCore&>(q) = p;
     q.frag = *frag;
-    return launch_any(q, columns, st);
+    return launch_any(q, columns, stream, st);
 }
 
 }  // namespace lq

@@ -789,11 +789,25 @@ def test_forms_of_the_fused_variant(rank, T, d_in, d_out, kernel):
     (16, [3000, 1200, 33], 4864, 4312, [4312]), (16, [3000, 1200, 33], 4864, 4320, [4320]), (32, [9000], 9100, 2312, [2312]), (64, [6000, 17], 6100, 3448, [3448]),
     (128, [5000, 40], 5100, 4120, [4120]), (16, [2000, 33], 2100, 2056, [8968, 8976]), (32, [2000, 33], 2100, 2056, [8968, 8968]), (64, [1000], 1100, 2056, [36128]),
     (16, [30, 9], 40, 4096, [18760]), (32, [300, 200], 700, 1024, [14336]),   # wide, few rows
+    # the same with rows of whole 128-byte lines, which the policy needs; a group of which one layer has others
+    (16, [3000, 1200, 33], 4864, 4288, [4288]), (16, [3000, 1200, 33], 4864, 4288, [4352]), (32, [9000], 9100, 2304, [2304]), (32, [9000], 9100, 2304, [2368]),
+    (64, [6000, 17], 6100, 3456, [3456]), (128, [5000, 40], 5100, 4160, [4096]), (32, [2000, 33], 2100, 2048, [8960, 8960]), (32, [2000, 33], 2100, 2048, [8960, 9024]),
+    (32, [2000, 33], 2100, 2048, [8960, 9032]), (64, [1000], 1100, 2048, [36160]),
 ])
 def test_slab_kernels_by_size(rank, lens, T, d_in, d_outs):
     """Either side of the host's choices between the slab kernels: row tiles and the policy for y."""
     ranks = [rank, max(1, rank - 5), rank // 2][: len(lens)]
     assert forward_against_64_bits(ranks, lens, T, d_in, d_outs, lq.LQ_VARIANT_SLAB, T + d_in) == ["forward_slab"]
+
+
+@pytest.mark.parametrize("variant", [lq.LQ_VARIANT_FUSED, lq.LQ_VARIANT_SPLIT])
+@pytest.mark.parametrize("rank,d_outs", [
+    (16, [12800, 12224]), (16, [12800, 12288]), (32, [12800, 12288]), (64, [12800, 12288]), (128, [12800, 12288]),   # either side of 60 million elements
+    (32, [12800, 12296]), (64, [25096]), (16, [25088]), (64, [25152])])                                              # rows of whole 128-byte lines or not
+def test_policy_for_y_in_the_expand_phase(rank, d_outs, variant):
+    """2300 rows, 1024 columns of x: either side of the choice of the non-temporal policy for y, groups and single layers."""
+    ran = forward_against_64_bits([rank, max(1, rank - 5), rank // 2], [1500, 600, 33], 2300, 1024, d_outs, variant, sum(d_outs))
+    assert ran == (["forward_fused"] if variant == lq.LQ_VARIANT_FUSED else ["shrink", "expand"])
 
 
 @pytest.mark.parametrize("rank,T,d_in", [(16, 9000, 72), (16, 12000, 200), (32, 9000, 264), (32, 12000, 520), (32, 16384, 136), (8, 20000, 1032)])
