@@ -94,8 +94,13 @@ __global__ __launch_bounds__(kWave) void kind_offsets_kernel(const int32_t* seg_
     }
 }
 
-// SPLIT: parts[i, :] = src[perm[i], :];  else: src[perm[i], :] = parts[i, :]   for the live positions i
-template <bool SPLIT>
+// SPLIT: parts[i, :] = src[perm[i], :];  else: src[perm[i], :] = parts[i, :]   for the live positions i.
+// The strided side is touched once: non-temporal stores in the concatenation, non-temporal loads (STREAM) in splits of 30 million
+// elements and more, of which nothing stays in the 256 MB cache.  us of a split and a concatenation with plain accesses, with such
+// stores, with such loads too, on three sets of operands in turn: 2048 x 4096 13.4, 13.2, 14.3, 3500 x 4096 20.3, 20.2, 21.7, 4864 x 4096 29.5,
+// 26.6, 28.3, 6500 x 4096 42.6, 36.7, 36.3, 8192 x 4096 47.4, 45.6, 45.1, 16384 x 4096 104.8, 89.7, 84.9 (with a writer in front of and a reader
+// behind each of the two 32.6, 33.9, 34.7; 51.4, 51.4, 51.6; 68.5, 69.1, 68.4; 87.8, 88.3, 87.2; 110.2, 108.9, 108.1; 218.2, 207.8, 207.7).
+template <bool SPLIT, bool STREAM>
 __global__ __launch_bounds__(kRowThreads) void move_rows_kernel(u16* src, long long ld, int d, const int32_t* perm, int n_tokens,
                                                                  const int32_t* seg_starts, const int32_t* n_segments,
                                                                  int max_segments, u16* parts)
@@ -108,8 +113,8 @@ __global__ __launch_bounds__(kRowThreads) void move_rows_kernel(u16* src, long l
         u16* a = src + (long long)row * ld;
         u16* b = parts + (long long)i * d;
         for (int k = (int)threadIdx.x * 8; k < d; k += kRowThreads * 8) {
-            if (SPLIT) *reinterpret_cast<u32x4*>(b + k) = load_once<true>(a + k);
-            else store_once<true>(a + k, *reinterpret_cast<const u32x4*>(b + k));
+            if (SPLIT) *reinterpret_cast<u32x4*>(b + k) = load_once<STREAM>(a + k);
+            else store_once<STREAM>(a + k, *reinterpret_cast<const u32x4*>(b + k));
         }
     }
 }
@@ -156,12 +161,11 @@ lq_status move_rows(bool split, void* rows, int64_t ld, int32_t d, const int32_t
     if ((d % 8) || (ld % 8) || !aligned16(rows) || !aligned16(parts)) return LQ_ERR_UNSUPPORTED;
     if (n_tokens == 0) return LQ_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (split)
-        hipLaunchKernelGGL(move_rows_kernel<true>, dim3(row_grid(n_tokens)), dim3(kRowThreads), 0, st, static_cast<u16*>(rows),
-                           (long long)ld, d, perm, n_tokens, seg_starts, n_segments, max_segments, static_cast<u16*>(parts));
-    else
-        hipLaunchKernelGGL(move_rows_kernel<false>, dim3(row_grid(n_tokens)), dim3(kRowThreads), 0, st, static_cast<u16*>(rows),
-                           (long long)ld, d, perm, n_tokens, seg_starts, n_segments, max_segments, static_cast<u16*>(parts));
+    const auto kernel = !split ? move_rows_kernel<false, true>
+                        : (long long)n_tokens * d >= 30000000ll ? move_rows_kernel<true, true>
+                        : move_rows_kernel<true, false>;
+    hipLaunchKernelGGL(kernel, dim3(row_grid(n_tokens)), dim3(kRowThreads), 0, st, static_cast<u16*>(rows), (long long)ld, d, perm, n_tokens,
+                       seg_starts, n_segments, max_segments, static_cast<u16*>(parts));
     return hipGetLastError() == hipSuccess ? LQ_OK : LQ_ERR_HIP;
 }
 }  // namespace

@@ -70,6 +70,25 @@ def test_split_and_concat_rows_by_kind(oracle_mod, seed, T, d):
     assert np.array_equal(lq.bits_from_bf16(dst), oracle_mod.concat_rows(want_parts, ref_seg, dst0))
 
 
+@pytest.mark.parametrize("T,d", [(3657, 8200), (3659, 8200)])
+def test_split_and_concat_of_many_rows(T, d):
+    """Either side of 30 million elements, where the split's loads change their policy."""
+    gen = torch.Generator().manual_seed(T)
+    ta, tk = torch.randint(-1, 3, (T,), generator=gen, dtype=torch.int32), torch.randint(0, 3, (T,), generator=gen, dtype=torch.uint8)
+    seg = lq.SegmentTables.empty(T, 3)
+    lq.lora_build_segments(ta.cuda(), tk.cuda(), torch.tensor([4, 8, 4], dtype=torch.int32, device="cuda"), seg,
+                           lq.workspace(lq.lora_build_workspace_bytes(T, 3)))
+    src = torch.randn(T, d, device="cuda").to(torch.bfloat16)
+    parts, dst = torch.zeros_like(src), torch.zeros_like(src)
+    lq.lora_split_rows(src, seg, parts)
+    lq.lora_concat_rows(parts, seg, dst)
+    live = (ta >= 0)
+    order = torch.argsort(tk[live].long() * 3 + ta[live], stable=True)
+    rows = torch.nonzero(live).flatten()[order].cuda()
+    assert torch.equal(parts[: len(rows)], src[rows]) and not parts[len(rows):].any()
+    assert torch.equal(dst, torch.where(live.cuda()[:, None], src, torch.zeros_like(src)))
+
+
 @pytest.mark.parametrize("variant", [lq.LQ_VARIANT_SPLIT, lq.LQ_VARIANT_FUSED])
 def test_forward_and_backward_with_dropout(oracle_mod, variant):
     """The fine-tuning path with LoRA dropout: x' = m * x on the fine-tuning rows (lora_dropout_rows), the
