@@ -1393,17 +1393,25 @@ size_t h_slices_bytes(int n_tokens, int max_rank)
 //   4096 114 and 89; 2200 mix 4096 -> 11008 68 and 56; 4096 mix 14336 -> 4096 84 and 77; 30000 mix 4096 -> 4096 188 and 176.
 // The barrier form stays where the slabs' re-reads of B or their number weigh more: outputs above 16384 columns (8000 mix 2048
 // -> 28672 234 and 253), narrow layers of very many rows (100000 mix 264 -> 264 89 and 112, 40000 1024 -> 1024 88 and 85),
-// ranks above 64 (their units are 32 rows at most), groups, and shorter batches, whose d_in it can cut (700 rows of one
-// segment, 14336 -> 4096, 34 and 38).  In the backward n_tokens counts all rows but the fine-tune rows alone run, so it
-// takes more of them.  (Rank 32 and below, d_in no multiple of 64: the slab kernel for units of up to 32 rows re-reads x's first
-// columns against zeros in the last block, which an infinity there would make a NaN.)
+// ranks above 64 (their units are 32 rows at most), groups, and shorter batches, whose d_in it can cut: 2048 rows, up to 8192
+// columns of x, and half as many rows as columns from there on (330 random calls of ranks 33 to 64 on either side, rows that take part
+// 2 to 100 % of the batch, slabs over barrier form on average and at worst, 9000 to 28672 columns: below half as many rows 1.12 and 1.87
+// (2244 rows of which 224 take part, 16384 -> 2048, 24.6 and 34.4 us; 2390, 28672 -> 1024, 54 and 87), from there on 0.81 and 1.15; up to 8192
+// columns 0.84 and 1.06).
+//   In the backward n_tokens counts all rows but the fine-tune rows alone run, so it takes more of them, 4096, or 8192 for dy of more than
+// 4096 columns: 860 calls of ranks 16 to 64, ten shapes, 8 fine-tune rows to all of them, in one segment and eight: slabs at most 0.97 of the
+// barrier form, with 1 % fine-tune rows 0.4 to 0.9 (which leaves the machine to the few rows only after a barrier of all workgroups); below
+// the lines up to 1.02.
+//   (Rank 32 and below, d_in no multiple of 64: the slab kernel for units of up to 32 rows re-reads x's first columns against zeros in
+// the last block, which an infinity there would make a NaN.)
 bool slab_form(const FwdParams& p)
 {
     const int d_out = p.proj0.d_out;
     if (p.n_proj > 1 || p.max_rank > 64 || d_out > 16384 || !slab_reaches(p.max_rank, p.d_in)) return false;
     if (p.max_rank <= 32 && p.d_in % 64 != 0) return false;
     if (p.n_tokens > 49152 && p.d_in + 2ll * d_out < 3072) return false;
-    return p.n_tokens >= (p.kinds == kAllKinds ? 2048 : p.d_in > 4096 ? 8192 : 4096);
+    if (p.kinds != kAllKinds) return p.n_tokens >= (p.d_in > 4096 ? 8192 : 4096);
+    return p.n_tokens >= 2048 && (p.d_in <= 8192 || 2ll * p.n_tokens >= p.d_in);
 }
 
 hipError_t run_shrink_expand(FwdParams& p, int variant, hipStream_t st, const SlabFrag* frag)

@@ -768,6 +768,7 @@ def forward_against_64_bits(ranks, lens, T, d_in, d_outs, variant, seed):
 
 @pytest.mark.parametrize("rank,T,d_in,d_out,kernel", [
     (64, 2047, 72, 136, "fused"), (64, 2048, 72, 136, "slab"),                    # tokens
+    (64, 2048, 8192, 72, "slab"), (64, 4099, 8200, 72, "fused"), (64, 4100, 8200, 72, "slab"), (40, 7167, 14336, 72, "fused"), (40, 7168, 14336, 72, "slab"),
     (64, 2100, 72, 16384, "slab"), (64, 2100, 72, 16392, "fused"), (16, 2600, 64, 16392, "fused"), (32, 4100, 128, 16392, "fused"),
     (32, 6000, 256, 136, "slab"), (32, 6000, 264, 136, "fused"), (16, 6000, 1032, 72, "fused"),   # widths no multiple of 64
     (64, 3000, 264, 136, "slab"), (65, 3000, 264, 136, "fused"), (128, 5000, 264, 136, "fused"),  # ranks
