@@ -552,16 +552,24 @@ __device__ __forceinline__ SlabPlan slab_plan(const PP& p, const Segs<PP>& sg, i
         };
         int spread = 0;
         if (__any(sg.a[0].rank < p.max_rank || sg.a[1].rank < p.max_rank)) {  // (lanes beyond the adapters repeat the last one)
-            bonus0 = bonus_of(sg.c[0].ad);
-            if (second) bonus1 = bonus_of(sg.c[1].ad);
-            spread = (int)((float)p.max_rank * p.slab_rows_per_rank);
+            const int b0 = bonus_of(sg.c[0].ad), b1 = second ? bonus_of(sg.c[1].ad) : 0;
+            // only where the batch's own adapters differ: a table may hold others
+            const unsigned long long in0 = __ballot(len0 > 0), in1 = __ballot(len1 > 0);
+            const int some = in0 ? lane_value(b0, uniform(__ffsll((long long)in0) - 1)) : lane_value(b1, uniform(__ffsll((long long)(in1 | 1ull << 63)) - 1));
+            if (__any((len0 > 0 && b0 != some) || (len1 > 0 && b1 != some))) {
+                bonus0 = b0;
+                bonus1 = b1;
+                spread = (int)((float)p.max_rank * p.slab_rows_per_rank);
+            }
         }
         // the smallest w with at most `target` chunks: of max(16, w + bonus) rows, at most `most`
         int lo = small_div(live, target) - 1 - spread;  // too many: sum of ceil(len / per) >= live / per
         int hi = target > n_live ? min(most, max(16, small_div(live, target - n_live) + 1)) : most;  // few enough: <= live / per + segments
-        // (equal ranks: hi itself.  The smallest w fits more, shorter units into the round, each with its own A and B to read: 4000
-        // Zipf rows of rank 16 in 110 segments, 4096 -> 4096, 27.6 us instead of 24.9)
-        while (spread > 0 && hi - lo > 1) {
+        // (equal ranks in the batch: hi itself.  The smallest w fits more, shorter units into the round, each with its own A and B to
+        // read: 4000 Zipf rows of rank 16 in 110 segments, 4096 -> 4096, 27.6 us instead of 24.9.  From 33 to 48 rows it takes a row tile
+        // less more often than not: 46 calls of equal or Zipf lengths 0.99 on average, 0.89 to 1.02, beyond 1.00 with equal lengths, 0.96 to 1.05)
+        const bool smallest = spread > 0 || (hi > 32 && hi <= 48);
+        while (smallest && hi - lo > 1) {
             const int mid = lo + ((hi - lo) >> 1);
             if (count(mid) > target) lo = mid;
             else hi = mid;
