@@ -62,8 +62,9 @@ enum { LQ_SEG_FINETUNE = 0, LQ_SEG_PREFILL = 1, LQ_SEG_DECODE = 2 };
  * LQ_VARIANT_SHRINK_ONLY / LQ_VARIANT_EXPAND_ONLY: the two halves of the split variant as separate
  * calls (same arguments, same workspace, shrink first), for callers that put other work between
  * them and for timing each kernel on its own.
- * (Long batches of ranks up to 64, from 2048 tokens in a single call, run in row slabs in this variant too, without the
- * device-wide wait; the residency requirement is then moot.)
+ * (Some long batches run in row slabs in LQ_VARIANT_FUSED too.  Which ones is a matter of speed and no promise: the
+ * residency requirement holds for every call of that variant.  Callers that share the device use LQ_VARIANT_SLAB or
+ * LQ_VARIANT_SPLIT.)
  * LQ_VARIANT_SLAB: one launch in which every workgroup takes a slab of at most 64 rows of one segment
  * through both products, so that h stays on the compute unit: no partial-h traffic and no device-wide wait
  * (hence no residency requirement); every slab re-reads its adapter's matrices, which come from the L2 cache
@@ -75,7 +76,8 @@ enum { LQ_SEG_FINETUNE = 0, LQ_SEG_PREFILL = 1, LQ_SEG_DECODE = 2 };
  * columns in all (from 384 to 1024 tokens up to 28672, for one layer or two that read up to 4096 columns); and above
  * rank 32 for single calls of up to 8192 tokens, 4096 input and 16384 output columns, as far as the rows are neither too
  * many (rows x output columns) nor too few for the width.  Fused otherwise, where re-reading A and B per slab costs more
- * than the partial-h round trip, or where the batch is long enough for that variant's own slabs.  Where it picks fused, that variant's residency requirement applies. */
+ * than the partial-h round trip, or where the batch is long enough for that variant's own slabs; its residency requirement
+ * then applies. */
 enum { LQ_VARIANT_SPLIT = 0, LQ_VARIANT_FUSED = 1, LQ_VARIANT_SHRINK_ONLY = 2, LQ_VARIANT_EXPAND_ONLY = 3,
        LQ_VARIANT_SLAB = 4, LQ_VARIANT_AUTO = 5 };
 
