@@ -116,15 +116,16 @@ def traffic_source(workload):
 
 
 def counter_traffic(workload, phase):
-    """HBM bytes per launch of `phase` from the committed rocprofv3 counter summary of this workload
-    (profiles/, FETCH_SIZE and WRITE_SIZE scaled by the copy calibration), or None."""
+    """HBM bytes per launch of `phase` (a kernel's label, or the labels of a step's kernels joined by "+") from the committed
+    rocprofv3 counter summary of this workload (profiles/, FETCH_SIZE and WRITE_SIZE scaled by the copy calibration);
+    None where there is none of these kernels: another kernel's bytes are no answer."""
     name = PROFILE_FILES.get(workload)
     path = os.path.join(ROOT, "profiles", name) if name else None
     if not path or not os.path.exists(path):
         return None
     for line in open(path):
         f = line.split()
-        if len(f) == 3 and f[0] == "traffic_bytes_per_launch" and (f[1] == phase or (phase in ONE_LAUNCH and (f[1] == "forward" or f[1] in ONE_LAUNCH))):
+        if len(f) == 3 and f[0] == "traffic_bytes_per_launch" and f[1] == phase:
             return int(f[2])
     return None
 
@@ -329,7 +330,7 @@ def measure_layer_stack(variant, steps, warmup, with_backward, grouped=True):
         dom_us = kern[dom]["avg_us"]
     dom_gbps = dom_bytes / (dom_us * 1e-6) / 1e9
     name = LAYER_STACK_NAME if grouped else LAYER_STACK_NAME + "_single_calls"
-    traffic = counter_traffic(name, one[0] if one else dom)
+    traffic = counter_traffic(name, "+".join(one) if one else dom)
     head = dict(
         workload=name, tokens=w["tokens"], calls=w["calls"], launches=w["launches"], ms_per_step=s_per_step * 1e3, per_step=per_step,
         tokens_per_s=w["tokens"] / s_per_step, forward_us=fwd_us,

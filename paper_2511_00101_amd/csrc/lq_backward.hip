@@ -494,7 +494,7 @@ __device__ __forceinline__ void wgrad_units(const BwdParams& p, int n_seg, const
 // (ranks up to 32: at most 128 registers, so that two workgroups share a compute unit and one's loads
 // overlap the other's barriers)
 // EITHER: units of 512 or 1024 rows.  (A number of rows known at run time only slowed the units down: backward of a decoder layer
-// 512 -> 526 us.)
+// 512 -> 526 us.  Spilled at rank 32: 6 registers, 14 with both heights, of which either path pays its own.)
 template <int NT, bool EITHER>
 __global__ __launch_bounds__(kThreads, NT <= 2 ? 4 : 2) void wgrad_kernel(BwdParams p)
 {
@@ -586,8 +586,8 @@ bool whole_segments_win(int n_tokens, int max_rank, int d_in, int d_out)
 // finished g of the fine-tune rows: at most n_tokens x max_rank floats (a multiple of 16 bytes)
 size_t gsum_bytes(int n_tokens, int max_rank) { return ((size_t)n_tokens * (size_t)max_rank * sizeof(float) + 15) / 16 * 16; }
 
-// Only segments with more than 512 rows keep partials: n such segments have at most n_tokens / 512 + n chunks
-// and n <= n_tokens / 513, whatever tables the caller passes.
+// Only segments with more rows than a unit (512, or 1024, which makes fewer chunks) keep partials: n segments of more than 512
+// have at most n_tokens / 512 + n chunks and n <= n_tokens / 513, whatever tables the caller passes.
 size_t wpart_bytes(int n_tokens, int max_rank, int d_in, int d_out)
 {
     const size_t chunks = 2 * ((size_t)(n_tokens + kWgRows - 1) / kWgRows);

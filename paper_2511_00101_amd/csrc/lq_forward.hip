@@ -1335,9 +1335,9 @@ hipError_t launch_fused(FwdParams& p, hipStream_t st)
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// LQ_VARIANT_AUTO: slab or fused, from the host arguments alone.  A slab re-reads its adapter's matrices for its 32 rows,
+// LQ_VARIANT_AUTO: slab or fused, from the host arguments alone.  A slab re-reads its adapter's matrices for its rows,
 // the fused kernel pays its barrier and the h slices' round trip through memory.  So the slab wins while the batch is one
-// round of slabs (8192 rows on 256 compute units), until the re-reads of B weigh more (rows x output columns), and where
+// round of 32-row slabs (8192 rows on 256 compute units), until the re-reads of B weigh more (rows x output columns), and where
 // there are enough rows for the A that every slab streams alone (the fused kernel cuts d_in instead).  all_rows: the
 // batch's rows all take part; otherwise (the backward: fine-tune rows only) n_tokens is no lower bound, and the
 // branches that need many rows are not taken.  Measured, slab vs fused, us (the worst of one segment, two, requests of 32

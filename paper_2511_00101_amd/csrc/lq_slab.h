@@ -29,7 +29,8 @@ __device__ __forceinline__ u32x4 load_at(gconst_u16 base, unsigned int off)
     return *reinterpret_cast<gconst_u32x4>(reinterpret_cast<gconst_char>(base) + (size_t)(off * 2u));
 }
 
-// projections a pass can hold in registers: its accumulators are NP x 2 x NT MFMA tiles
+// projections a pass can hold in registers: its accumulators are NP x MTM x NT MFMA tiles (MTM: 16-row tiles
+// of the kernel's tallest unit, two in groups)
 template <int NT> constexpr int pass_projections() { return NT == 1 ? kMaxProj : NT == 2 ? 3 : 1; }
 
 // =================================================================================================
@@ -411,7 +412,7 @@ __device__ __forceinline__ void slab_shrink_sum(const PP& p, const Unit& u0, con
     if constexpr (NP * PQ > 7) one(std::integral_constant<int, 7>{});
 }
 
-// the unit's row indices (rows[0 .. 32): -1 beyond the unit and for an invalid table entry) and, behind them, the
+// the unit's row indices (rows[0 .. 64): -1 beyond the unit and for an invalid table entry) and, behind them, the
 // rows' scales: the adapter's, or the tokens' own (dynamic scaling, Section 3.3).  The caller adds the barrier.
 template <class PP>
 __device__ __forceinline__ void slab_unit_rows(const PP& p, const Unit& u, const SegInfo& s0, int* rows)

@@ -120,7 +120,8 @@ __device__ __forceinline__ void slab_unit(const PP& p, const Unit& u, const SegI
     }
 }
 
-// NT: 16-rank tiles of the launch (ranks up to 16 NT); MTM: 16-row tiles of its tallest unit.
+// NT: 16-rank tiles of the launch (ranks up to 16 NT); MTM: 16-row tiles of its tallest unit.  (Spilled registers: four rank tiles with four
+// row tiles 16, or 19 where g and h are left as operands; eight rank tiles 26 in groups, 35 else; the others none.)
 template <int NT, int MTM, bool STREAM, class PP>
 __global__ __launch_bounds__(kThreads) void slab_kernel(PP p)
 {

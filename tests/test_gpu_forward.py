@@ -801,6 +801,17 @@ def test_slab_kernels_by_size(rank, lens, T, d_in, d_outs):
     assert forward_against_64_bits(ranks, lens, T, d_in, d_outs, lq.LQ_VARIANT_SLAB, T + d_in) == ["forward_slab"]
 
 
+@pytest.mark.parametrize("ranks,lens,T", [
+    ([16] * 20 + [8, 3], [2000, 900] + [110] * 18 + [0, 0], 5000),           # one rank in the batch, lower ones in the table
+    ([32] * 3 + [64], [1400, 1400, 1400, 0], 4300), ([16, 64, 5], [0, 4200, 0], 4300),   # ... a higher one
+    ([16] * 21 + [8] * 9, [150] * 30, 4700),                                 # 90 segments, the other rank among the last ones of each kind
+    ([16] * 100 + [5], [66] * 99 + [30, 0], 6600), ([64] * 12 + [16], [640] * 12 + [0], 8000)])
+def test_chunks_by_the_ranks_of_the_batch(ranks, lens, T):
+    """More rows than one round of 16-row chunks: equal ranks beside unused adapters of other ranks, and mixed ranks."""
+    for d_in, d_out in ((72, 136), (256, 72)):
+        assert forward_against_64_bits(ranks, lens, T, d_in, [d_out], lq.LQ_VARIANT_SLAB, T + d_in) == ["forward_slab"]
+
+
 @pytest.mark.parametrize("variant", [lq.LQ_VARIANT_FUSED, lq.LQ_VARIANT_SPLIT])
 @pytest.mark.parametrize("rank,d_outs", [
     (16, [12800, 12224]), (16, [12800, 12288]), (32, [12800, 12288]), (64, [12800, 12288]), (128, [12800, 12288]),   # either side of 60 million elements
