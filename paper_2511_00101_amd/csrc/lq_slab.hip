@@ -187,7 +187,7 @@ bool wide_layer(const PP& p, float columns) { return (float)p.max_rank * columns
 // rows, and adapters of lower rank lose their taller units: 7413 rows of ranks 8 to 64, 14336 -> 4096, 76.8 and 81.9.  A batch of
 // up to 4096 rows that does not fit has more than 128 segments; its units were never taller.)
 //   By itself two tiles are at most 0.2 us slower for 4864 to 6824 rows of ranks 16 and 32 in nine widths, and up to 0.7 us faster.  Behind gate and
-// up as single calls on operands of 32 layers, `down` of 5632 rows takes 70 us; 66 where every such call had four tiles and non-temporal y, but 70
+// up as single calls, every layer on operands of its own, `down` of 5632 rows takes 70 us; 66 where every such call had four tiles and non-temporal y, but 70
 // again with either alone.
 //   Wide layers take taller units in column parts, see slab_plan: not before their 16-row chunks leave room for fewer than
 // five parts, with 49 chunks, since the plan wants at least twice as many parts as there is room for: 16 rows of rank 32, 4096 ->
